@@ -15,10 +15,10 @@
 // a time: each lane loads one entry's geometry record with a vector load and
 // tests whether the entry's ellipse can reach the block at all (cull_hit); a
 // ballot gives the mask of entries to evaluate.  The wave then visits those
-// entries in list order.  What an entry carries is wave-uniform: its fields
-// are broadcast to SGPRs (v_readlane from the lane that loaded it, or a
-// scalar load) and used directly as VALU operands, so no LDS staging and no
-// per-lane gathers are needed.  The wave leaves the list as soon as a ballot
+// entries in list order.  What an entry carries is wave-uniform: its geometry
+// comes to SGPRs by a scalar load, requested one entry ahead, and is used
+// directly as VALU operands, its appearance goes to the matrix cores, so no
+// LDS staging of records is needed.  The wave leaves the list as soon as a ballot
 // shows every lane finished.  Waves pop blocks from per-XCD work queues
 // (persistent grid).
 //
@@ -113,16 +113,25 @@ __device__ __forceinline__ GeomRec load_rec_whole(const GeomRec* __restrict__ p)
   return g;
 }
 
+// The lowest set bit of a wave mask (~0 if none: as a lane index, 63) and a
+// mask without bit j (an empty mask stays empty): one scalar instruction each,
+// in loops where the scalar unit is nearly as busy as the vector unit.
+__device__ __forceinline__ uint32_t first_lane(uint64_t m) {
+  uint32_t j;
+  asm("s_ff1_i32_b64 %0, %1" : "=s"(j) : "s"(m));
+  return j;
+}
+__device__ __forceinline__ uint64_t without_lane(uint64_t m, uint32_t j) {
+  asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(j));
+  return m;
+}
+
 // Record of list entry j's Gaussian (rid in lane j) by a scalar load whose
 // offset is a 32-bit register (records sit below 2^32 bytes): one shift of
 // the index instead of 64-bit address arithmetic per entry.
 __device__ __forceinline__ GeomRec rec_of_lane(const GeomRec* __restrict__ geom, uint32_t rid_l, uint32_t j) {
   const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)rid_l, (int)j) << 5;
   return *(const GeomRec*)((const char*)geom + off);
-}
-
-__device__ __forceinline__ float bcast(float x, uint32_t j) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
 }
 
 // Appearance record words of Gaussian g (10 words in BF16 storage, 20 in
@@ -178,35 +187,82 @@ __device__ __forceinline__ uint32_t next_item(uint32_t* ctr, const uint32_t* __r
   return k < e - b ? b + k : n_items;
 }
 
+// The image planes' addresses come from tables in memory: said to be global
+// memory, their accesses are global ones and not flat ones (which wait on the
+// LDS counter too).
+typedef __attribute__((address_space(1))) float* gfloat_ptr;
+__device__ __forceinline__ void gstore(float* p, float x) { *(gfloat_ptr)p = x; }
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
-// Forward accumulation on the matrix cores (BF16 appearance).  The 20 sums
-// acc[p][s] = sum_e w[p][e] y[e][s] of a batch of 8 entries form one
-// v_mfma_f32_16x16x32_bf16 per group of 4 channel slots s and per term of
-// the weights: the K index runs over (pixel group g' = lane / 16, entry e),
-// the weights w (the B operand) are each lane's own, and the A operand is
-// block diagonal (the appearance y in the rows of the lane's own pixel group,
-// zero elsewhere), so the result lands in the lane of its pixel: lane l holds
-// acc[l][4 j + i] in register i of block j.  The weights are split exactly
-// into three BF16 terms (8 significant bits each) and the BF16 appearance is
-// exact, so every product is exact and only the FP32 accumulation rounds.
-// The depth slot is accumulated separately in FP32.
-// LDS of one wave: the batch's appearance [20 slots][8 entries] in rows 0-19
-// of a [64][8] area (lane l stores into row l, so the per-entry store needs
-// no lane mask; rows 20-63 are never read), a zero block [20][8], and the
-// weights [3 terms][64 pixels][8 entries] (BF16).
+// Forward accumulation on the matrix cores.
+//
+// FP32 appearance: an entry adds w[p] y[s] to the 20 sums of every pixel p, an
+// outer product, which v_mfma_f32_4x4x1_16b_f32 forms for 4 channels and all
+// 64 pixels at once.  Its 16 blocks are 4 x 4 x 1 products: with one block's
+// A broadcast to all of them (cbsz 4, abid j), the A operand is channels
+// 4 j .. 4 j + 3 (lane c of a register holding the entry's channel c, so one
+// load per entry brings all 20), the B operand is each lane's own weight, and
+// the result lands in the pixel's own lane (register i of block j: slot
+// 4 j + i).  Each step is an FP32 fused multiply-add, bit for bit that of
+// v_fmac_f32: five instructions of the matrix pipe in place of 20 of the VALU.
+//
+// BF16 appearance: the 20 sums acc[p][s] = sum_e w[p][e] y[e][s] of a batch
+// of 8 entries form one v_mfma_f32_16x16x32_bf16 per group of 4 channel slots
+// s and per term of the weights: the K index runs over (pixel group g' =
+// lane / 16, entry e), the weights w (the B operand) are each lane's own, and
+// the A operand is block diagonal (the appearance y in the rows of the lane's
+// own pixel group, zero elsewhere), so the result lands in the lane of its
+// pixel: lane l holds acc[l][4 j + i] in register i of block j.  The weights
+// are split exactly into three BF16 terms (8 significant bits each) and the
+// BF16 appearance is exact, so every product is exact and only the FP32
+// accumulation rounds.
+//
+// The depth slot is accumulated separately in FP32 in both.
+// LDS of one wave (BF16): the batch's weights [8 entries][64 pixels] (FP32, so
+// that an entry's store is one conflict-free word per lane; they are split
+// when the batch is full), its appearance [20 slots][8 entries] (BF16; the
+// lanes past the 20 slots store slot 19's value to its place too, so the
+// store needs no lane mask) and a zero block [20][8].
 constexpr int kFwdY = 20 * 8;
-constexpr int kFwdYRows = 64 * 8;
-constexpr int kFwdW = 64 * 8;
-constexpr int kFwdWaveLds = (kFwdYRows + kFwdY + 3 * kFwdW) * 2;
+constexpr int kFwdW = 8 * 64;
+constexpr int kFwdWaveLds = kFwdW * 4 + 2 * kFwdY * 2;
+constexpr int kAppAll = 4;   // cbsz of the FP32 form: one of the 16 blocks broadcast to all
 
-// FP32 appearance: eight waves per SIMD (64 VGPRs), measured faster than the
-// compiler's own register choice, which leaves room for only seven.  BF16
-// appearance: seven (72 VGPRs), so that a batch's weight operands stay in
-// registers across its five channel blocks (faster than eight waves that
-// re-read them).
+// Lane c's channel slot of Gaussian g's appearance (c < 20; the lanes past
+// them repeat the last one, which no product reads); slot 3 is 0.  A buffer
+// load takes the record's offset as a scalar and the lane's offset in it as a
+// fixed register, so it needs no address arithmetic on the vector side and no
+// registers for it.  (The records stay below 2^32 bytes.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t app_buffer(const void* app) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)app, 0, -1, 0x00020000);
+}
+template <bool BF16>
+__device__ __forceinline__ uint32_t load_app_lane(__amdgpu_buffer_rsrc_t app, uint32_t g, uint32_t ylane) {
+  if (BF16) return __builtin_amdgcn_raw_buffer_load_b16(app, 2u * ylane, g * 40u, 0);
+  return __builtin_amdgcn_raw_buffer_load_b32(app, 4u * ylane, g * 80u, 0);
+}
+
+// px - 8 bx0 for a pixel coordinate px and a record's first block bx0, both
+// offset by 2^23, where the FP32 spacing is 1: integer arithmetic on the
+// scalar side, one exact subtraction per lane.
+constexpr float kPixBias = 8388608.f;
+__device__ __forceinline__ float block_px_bias(uint32_t b0) { return __uint_as_float(0x4b000000u + (b0 << 3)); }
+
+// FP32 appearance: eight waves per SIMD (64 VGPRs).  BF16 appearance: seven
+// (72 VGPRs), so that a batch's weight operands stay in registers across its
+// five channel blocks (faster than eight waves that re-read them).
+//
+// What bounds it: instruction issue, the vector and the scalar unit together
+// (per visited entry 38 vector and 26 scalar instructions, of which 5 and few
+// are the 64-entry cull's), and in calls with few blocks the latency of one
+// wave's loop.  300k Gaussians, 640 x 480, FP32: 158 -> 103 us (products in
+// place of 20 multiply-adds; the records of the next entry in flight while one
+// is worked on, without the copies and branches that cost: 158 -> 120; scalar
+// mask arithmetic by single instructions: -> 103).  500k Gaussians, 8 views,
+// BF16: 690 -> 609 us.
 // NC: per-pixel contributor counts are written (a caller asked for them);
 // without them the entry loop keeps no count.
 template <bool BF16, bool CNT, bool NC>
@@ -218,18 +274,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
     Counters* __restrict__ cnt, int32_t* __restrict__ last_idx, float* __restrict__ T_state) {
   const int lane = threadIdx.x & 63;
   if (cnt->overflow) return;
-  extern __shared__ unsigned short lds_f[];
-  unsigned short* ys = lds_f + (threadIdx.x >> 6) * (kFwdWaveLds / 2);
-  unsigned short* yz = ys + kFwdYRows;
-  unsigned short* ws = yz + kFwdY;
+  extern __shared__ float lds_f[];
+  float* ws = lds_f + (threadIdx.x >> 6) * (kFwdWaveLds / 4);
+  unsigned short* ys = (unsigned short*)(ws + kFwdW);
+  unsigned short* yz = ys + kFwdY;
   // A-operand rows: lane l reads slot 4 j + (l & 3) when its row group
   // (l & 15) / 4 equals its k-block l / 16, else the zero block
   const unsigned short* abase = (((lane & 15) >> 2) == (lane >> 4) ? ys : yz) + (lane & 3) * 8;
-  // the appearance slot this lane loads per entry (lanes past the 20 slots
-  // repeat the last one, into rows no product reads); the records' byte
-  // offsets stay below 2^32, so each load takes a 32-bit lane offset
   const uint32_t ylane = lane < 20 ? (uint32_t)lane : 19u;
-  const unsigned short* __restrict__ app16 = (const unsigned short*)app;
+  const __amdgpu_buffer_rsrc_t app_b = app_buffer(app);
   if (BF16) {
     // the zero block, and the weights: a partial batch leaves the weights of
     // its unused entries as they were (their appearance is zeroed instead),
@@ -237,7 +290,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
     ((uint32_t*)yz)[lane] = 0u;
     if (lane < kFwdY / 2 - 64) ((uint32_t*)yz)[64 + lane] = 0u;
 #pragma unroll
-    for (int t = 0; t < 3; ++t) *(uint4*)(ws + t * kFwdW + lane * 8) = make_uint4(0u, 0u, 0u, 0u);
+    for (int e = 0; e < 8; ++e) ws[e * 64 + lane] = 0.f;
   }
   // this wave's work (CNT: the profiling variant), added to the 64-bit
   // counters once at the end (a wave's own count stays far below 2^32); the
@@ -253,14 +306,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
     const int W = V->W, H = V->H;
     const int px = (int)bx * kBlock + (lane & 7), py = (int)by * kBlock + (lane >> 3);
     const bool inside = px < W && py < H;
+    const float pxb = kPixBias + (float)px, pyb = kPixBias + (float)py;
     const uint32_t tile = (uint32_t)V->tile_off + (by >> st.tile_shift) * (uint32_t)V->tiles_x +
                           (bx >> st.tile_shift);
     const uint2 r = ranges[tile];
     float T = 1.f;
-    float acc[20];   // FP32 appearance
-#pragma unroll
-    for (int c = 0; c < 20; ++c) acc[c] = 0.f;
-    f32x4 D[5];      // BF16 appearance: slots 4 j .. 4 j + 3 of this lane's pixel
+    f32x4 D[5];      // slots 4 j .. 4 j + 3 of this lane's pixel
 #pragma unroll
     for (int jb = 0; jb < 5; ++jb) D[jb] = (f32x4){0.f, 0.f, 0.f, 0.f};
     float accz = 0.f;
@@ -268,152 +319,156 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
     auto flush = [&]() {
       if (nb < 8 && lane < 20)
         for (int e = nb; e < 8; ++e) ys[lane * 8 + e] = 0;
-      // the three weight terms (B) are the same for the five channel
-      // blocks: read once, 8 LDS reads per batch instead of 20 (12 more
-      // VGPRs, hence 7 waves per SIMD instead of 8)
+      // the weights (the B operand, the same for the five channel blocks):
+      // w = hi + mid + lo exactly, each term the top 8 significant bits of
+      // what is left (truncation), so each is a BF16 value: the high halves
+      // of two entries' words are packed by one byte permutation
+      uint32_t tw[3][4];
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        uint32_t u[2][3];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float w = ws[(e + i) * 64 + lane];
+          const float r1 = w - __uint_as_float(__float_as_uint(w) & 0xffff0000u);
+          const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+          u[i][0] = __float_as_uint(w);
+          u[i][1] = __float_as_uint(r1);
+          u[i][2] = __float_as_uint(r2);
+        }
+#pragma unroll
+        for (int t = 0; t < 3; ++t) tw[t][e / 2] = __builtin_amdgcn_perm(u[1][t], u[0][t], 0x07060302u);
+      }
       bf16x8_t bw[3];
 #pragma unroll
-      for (int t = 0; t < 3; ++t) bw[t] = *(const bf16x8_t*)(ws + t * kFwdW + lane * 8);
+      for (int t = 0; t < 3; ++t)
+        bw[t] = __builtin_bit_cast(bf16x8_t, make_uint4(tw[t][0], tw[t][1], tw[t][2], tw[t][3]));
+      // two channel blocks at a time, so that a product does not wait for the
+      // one before it
 #pragma unroll
-      for (int jb = 0; jb < 5; ++jb) {
-        const bf16x8_t a = *(const bf16x8_t*)(abase + 32 * jb);
+      for (int jb = 0; jb < 5; jb += 2) {
+        const bf16x8_t a0 = *(const bf16x8_t*)(abase + 32 * jb);
+        const bf16x8_t a1 = *(const bf16x8_t*)(abase + 32 * (jb < 4 ? jb + 1 : jb));
 #pragma unroll
-        for (int t = 0; t < 3; ++t) D[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[t], D[jb], 0, 0, 0);
+        for (int t = 0; t < 3; ++t) {
+          D[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bw[t], D[jb], 0, 0, 0);
+          if (jb < 4) D[jb + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bw[t], D[jb + 1], 0, 0, 0);
+        }
       }
       nb = 0;
     };
-    int32_t last = -1, ncon = 0;
+    // the last list entry a pixel can have taken: the one before that which
+    // would have ended it, else the list's last (set where a pixel ends, not at
+    // every contribution: what lies between its last contributor and this
+    // entry fails the same tests again in the backward)
+    int32_t last = (int32_t)r.y - 1, ncon = 0;
     // the lanes still compositing, as a wave mask in SGPRs: per-lane tests
     // enter it through ballots of single comparisons and leave it through
     // inverse ballots, so the bookkeeping costs scalar instructions only
     uint64_t live = __builtin_amdgcn_ballot_w64(inside);
-    bool finished = live == 0ull;
     // the list entries of the next chunk are requested a chunk ahead
     uint32_t rid_n = 0;
     if (r.x + (uint32_t)lane < r.y) rid_n = vals[r.x + (uint32_t)lane];
-    for (uint32_t base = r.x; base < r.y && !finished; base += 64) {
+    for (uint32_t base = r.x; base < r.y && live != 0ull; base += 64) {
       // lane l takes entry base + l and decides whether the wave visits it
       const uint32_t kl = base + (uint32_t)lane;
       const uint32_t rid_l = rid_n;
-      GeomRec g_l{};
       bool hit = false;
       if (kl < r.y) {
-        g_l = load_rec_whole(geom + rid_l);
+        const GeomRec g_l = load_rec_whole(geom + rid_l);
         hit = block_in_bbox(g_l.bbox, bx, by) && cull_hit(g_l, bx, by, st.cutoff2, st.log2_alpha_min);
       }
       if (kl + 64u < r.y) rid_n = vals[kl + 64u];
       uint64_t hm = __builtin_amdgcn_ballot_w64(hit);
-      // the appearance of the entry to visit next is requested at the end of
-      // the current one, so its latency overlaps that entry's evaluation
-      uint32_t j = hm ? (uint32_t)__builtin_ctzll(hm) : 0u;
-      uint32_t aw[20];
-      unsigned short yh = 0;   // BF16: this lane's channel slot of the entry's appearance
-      // the next entry's geometry: with BF16 appearance a scalar load issued
-      // one entry ahead (the appearance goes through vector loads, so the
-      // SGPRs are free for it); with FP32 appearance (20 scalar appearance
-      // words) broadcast from the lane that loaded it
-      GeomRec gn{};
-      if (hm) {
-        if (BF16) gn = rec_of_lane(geom, rid_l, j);
-        const uint32_t g0 = __builtin_amdgcn_readlane(rid_l, j) & npad_mask;
-        if (BF16) {
-          yh = *(const unsigned short*)((const char*)app16 + (g0 * 40u + 2u * ylane));
-        } else {
-          load_app_words<BF16>(app, g0, aw);
-        }
-      }
-      while (hm) {
-        hm &= hm - 1ull;
-        GeomRec gr;
-        if (BF16) {
-          gr = gn;
-        } else {
-          gr.mx = bcast(g_l.mx, j);
-          gr.my = bcast(g_l.my, j);
-          gr.qa = bcast(g_l.qa, j);
-          gr.qb2 = bcast(g_l.qb2, j);
-          gr.qc = bcast(g_l.qc, j);
-          gr.o = bcast(g_l.o, j);
-          gr.z = bcast(g_l.z, j);
-          gr.bbox = __builtin_amdgcn_readlane(g_l.bbox, j);
-        }
+      if (hm == 0ull) continue;
+      int left = __builtin_popcountll(hm);   // the entries to visit
+      // An entry's records (geometry by a scalar load, appearance by one lane
+      // load) are requested while the entry before it is worked on.  The loop
+      // takes two entries a turn, so that each of the two sets of registers
+      // is loaded in place (a copy from one to the other would wait for the
+      // load).  After the chunk's last entry the request repeats lane 63's
+      // records (a list entry's, or record 0 past the end), which nothing
+      // uses: no branch around it.
+      auto request = [&](uint32_t& j, GeomRec& gr, uint32_t& yw) {
+        j = first_lane(hm);
+        hm = without_lane(hm, j);
+        gr = rec_of_lane(geom, rid_l, j);
+        yw = load_app_lane<BF16>(app_b, __builtin_amdgcn_readlane(rid_l, j) & npad_mask, ylane);
+        // the requests stay here: the loads are not moved to their uses
+        asm volatile("" ::: "memory");
+      };
+      // the record has arrived (scalar loads return in any order, so this
+      // waits for all: the next request comes after it)
+      auto arrived = [&](const GeomRec& gr) {
+        asm volatile("" ::"s"(gr.mx), "s"(gr.my), "s"(gr.qa), "s"(gr.qb2), "s"(gr.qc), "s"(gr.o), "s"(gr.z),
+                     "s"(gr.bbox));
+      };
+      auto work = [&](uint32_t j, const GeomRec& gr, uint32_t yw) {
         const uint32_t bb = gr.bbox;
         if (CNT) {
           n_eval += (uint32_t)__popcll(live);
           ++n_ent;
         }
-        const float dx = (float)(px - 8 * (int)(bb & 255u)) - gr.mx;
-        const float dy = (float)(py - 8 * (int)((bb >> 16) & 255u)) - gr.my;
+        const float dx = (pxb - block_px_bias(bb & 255u)) - gr.mx;
+        const float dy = (pyb - block_px_bias((bb >> 16) & 255u)) - gr.my;
         const Eval e = eval_entry(dx, dy, gr.qa, gr.qb2, gr.qc, gr.o, st.cutoff2, st.alpha_max, st.alpha_min);
         const float Tn = T * (1.f - e.alpha);
         // e.pass, as a mask
         const uint64_t pm = live & __builtin_amdgcn_ballot_w64(e.m2 <= st.cutoff2) &
                             __builtin_amdgcn_ballot_w64(e.alpha >= st.alpha_min);
         const uint64_t tm = pm & __builtin_amdgcn_ballot_w64(Tn < st.T_eps);   // terminates here
-        live &= ~tm;
+        if (tm != 0ull) {
+          live &= ~tm;
+          if (live == 0ull) left = 1;   // nothing after this entry
+          last = __builtin_amdgcn_inverse_ballot_w64(tm) ? (int32_t)(base + j) - 1 : last;
+        }
         const uint64_t cmask = pm & ~tm;
         if (cmask != 0ull) {
           const bool con = __builtin_amdgcn_inverse_ballot_w64(cmask);
           if (CNT) n_con += (uint32_t)__popcll(cmask);
           const float w = con ? e.alpha * T : 0.f;
-          if (BF16) {
-            accz = __builtin_fmaf(w, gr.z, accz);
-            // w = hi + mid + lo exactly: each term keeps the top 8 significant
-            // bits of what is left (truncation), so each is a BF16 value
-            const float whi = __uint_as_float(__float_as_uint(w) & 0xffff0000u);
-            const float r1 = w - whi;
-            const float wmid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-            const float wlo = r1 - wmid;
-            ws[lane * 8 + nb] = (unsigned short)(__float_as_uint(whi) >> 16);
-            ws[kFwdW + lane * 8 + nb] = (unsigned short)(__float_as_uint(wmid) >> 16);
-            ws[2 * kFwdW + lane * 8 + nb] = (unsigned short)(__float_as_uint(wlo) >> 16);
-            ys[lane * 8 + nb] = yh;
-          } else {
-            float y[20];
-            y_from_words<BF16>(aw, y);
-            y[3] = gr.z;
-#pragma unroll
-            for (int c = 0; c < 20; ++c) acc[c] = __builtin_fmaf(w, y[c], acc[c]);
-          }
+          accz = __builtin_fmaf(w, gr.z, accz);
           T = con ? Tn : T;
-          last = con ? (int32_t)(base + j) : last;
           if (NC) ncon += con ? 1 : 0;
-          if (BF16 && ++nb == 8) flush();
-        }
-        if (live == 0ull) {
-          finished = true;
-          break;
-        }
-        if (hm) {
-          j = (uint32_t)__builtin_ctzll(hm);
-          if (BF16) gn = rec_of_lane(geom, rid_l, j);
-          const uint32_t g0 = __builtin_amdgcn_readlane(rid_l, j) & npad_mask;
           if (BF16) {
-            yh = *(const unsigned short*)((const char*)app16 + (g0 * 40u + 2u * ylane));
+            ws[nb * 64 + lane] = w;
+            ys[ylane * 8 + nb] = (unsigned short)yw;
+            if (++nb == 8) flush();
           } else {
-            load_app_words<BF16>(app, g0, aw);
+            const float y = __uint_as_float(yw);
+            D[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(y, w, D[0], kAppAll, 0, 0);
+            D[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(y, w, D[1], kAppAll, 1, 0);
+            D[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(y, w, D[2], kAppAll, 2, 0);
+            D[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(y, w, D[3], kAppAll, 3, 0);
+            D[4] = __builtin_amdgcn_mfma_f32_4x4x1f32(y, w, D[4], kAppAll, 4, 0);
           }
         }
+      };
+      uint32_t j0, j1, y0, y1;
+      GeomRec g0, g1;
+      request(j0, g0, y0);
+      for (;;) {
+        arrived(g0);
+        request(j1, g1, y1);
+        work(j0, g0, y0);
+        if (--left == 0) break;
+        arrived(g1);
+        request(j0, g0, y0);
+        work(j1, g1, y1);
+        if (--left == 0) break;
       }
     }
-    if (BF16) {
-      if (nb > 0) flush();
-#pragma unroll
-      for (int jb = 0; jb < 5; ++jb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[4 * jb + i] = D[jb][i];
-      acc[3] = accz;
-    }
+    if (BF16 && nb > 0) flush();
     if (inside) {
       const ViewImages o = out[v];
       const size_t HW = (size_t)W * H, p = (size_t)py * W + px;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) o.rgb[c * HW + p] = acc[c];
-      o.depth[p] = acc[3];
+      for (int c = 0; c < 3; ++c) gstore(o.rgb + c * HW + p, D[0][c]);
+      gstore(o.depth + p, accz);
 #pragma unroll
       for (int c = 0; c < 16; ++c)
-        if (c < st.nfeat) o.feat[c * HW + p] = acc[4 + c];
-      o.T[p] = T;
+        if (c < st.nfeat) gstore(o.feat + c * HW + p, D[1 + c / 4][c & 3]);
+      gstore(o.T + p, T);
       if (NC && o.n_contrib) o.n_contrib[p] = ncon;
       last_idx[(size_t)V->pix_off + p] = last;
       T_state[(size_t)V->pix_off + p] = T;
