@@ -11,7 +11,8 @@ namespace lgs {
 constexpr int kBlock = 8;
 constexpr int kMaxSide = 2048;          // 8-bit block coordinates in records
 constexpr int kChannels = 20;           // RGB 3 + depth 1 + feature 16
-constexpr int kPartials = 26;           // geometric moments 5, opacity 1, y 20
+constexpr int kPartials = 26;           // y 20, then the geometric sums Sx, Sy, Sxx, S0, Sxy, Syy
+constexpr int kPartGeo = 20;            // the first of the geometric sums
 constexpr int kSlotFloats = 32;         // a backward slot record: the kPartials floats padded to 128 bytes
 
 // Per-view constants, shared by every stage (device array of n_views).
@@ -217,11 +218,6 @@ void launch_raster_fwd(const Settings& st, const ViewDesc* views, const ViewImag
 // targets (loss_w), or the colour channels given and depth + features from
 // the L1 residual (the D-SSIM loss, whose colour gradient a kernel writes).
 enum UpMode { UP_EXPLICIT = 0, UP_L1 = 1, UP_RGB = 2 };
-// LDS upstream rows per wave: hi rows for the 20 channels plus lo rows for
-// the channels given as FP32 values
-__host__ __device__ constexpr int bwd_upstream_rows(int up_mode) {
-  return up_mode == UP_L1 ? 20 : (up_mode == UP_RGB ? 23 : 40);
-}
 void launch_raster_bwd(int up_mode, const Settings& st, const ViewDesc* views, const ViewImages* upstream,
                        const ViewImages* fwd_out, const ViewImages* targets, const float* loss_w,
                        const uint2* ranges, const uint32_t* vals, const GeomRec* geom,

@@ -253,12 +253,14 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   return x;
 }
 
-// grad2d layout per visible (view, Gaussian): [Sx, Sy, Sxx, Sxy, Syy,
-// opacity, r, g, b, z, f0..f15] (26 FP32), where S_* = sum over pixels of
-// dL/dalpha * alpha times dx, dy, dx^2, dx dy, dy^2 (m2 = Q_xx dx^2 +
-// 2 Q_xy dx dy + Q_yy dy^2, dx = pixel - mean, dL/dm2 = -1/2 dL/dalpha alpha):
-// so dL/dQ_xx = -1/2 Sxx, dL/dQ_xy (the symmetric off-diagonal entry,
-// counted twice in m2) = -Sxy, dL/dQ_yy = -1/2 Syy, and dL/dmean = Q (Sx, Sy).
+// grad2d layout per visible (view, Gaussian): [r, g, b, z, f0..f15, Sx, Sy,
+// Sxx, S0, Sxy, Syy] (26 FP32, the geometric sums from kPartGeo), where S_* =
+// sum over pixels of dL/dalpha * alpha (of pixels below the opacity clamp)
+// times dx, dy, dx^2, 1, dx dy, dy^2 (m2 = Q_xx dx^2 + 2 Q_xy dx dy + Q_yy
+// dy^2, dx = pixel - mean, dL/dm2 = -1/2 dL/dalpha alpha): so dL/dQ_xx = -1/2
+// Sxx, dL/dQ_xy (the symmetric off-diagonal entry, counted twice in m2) =
+// -Sxy, dL/dQ_yy = -1/2 Syy, dL/dmean = Q (Sx, Sy) and, with alpha = o G below
+// the clamp, dL/dlogit = (1 - o) S0.
 // The per-view chain rule, one thread per visible (view, Gaussian) c (in
 // (view, Gaussian) order, so a wave's 64 c belong to one view or a few
 // consecutive ones): its contributions to dL/d(world mean), dL/dM and
@@ -297,14 +299,15 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
       activate(p, ls, q, (double)logits[g], P);
       double gp[3] = {0, 0, 0}, gM[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, glogit = 0.0;
       const ViewDesc V = views[v];
-      const float* G = grad2d + (size_t)ci * kPartials;
+      const float* Y = grad2d + (size_t)ci * kPartials;
+      const float* G = Y + kPartGeo;
       Screen S;
       to_screen(V, p, P, (double)st.eps2d, S);
       const double z = S.xc[2], iz = 1.0 / z;
       // conic -> Sigma':  G_Sigma' = -Q Gq Q  (symmetric representation)
       const double inv = 1.0 / S.det;
       const double Qa = S.c * inv, Qb = -S.b * inv, Qc = S.a * inv;
-      const double ga_q = -0.5 * (double)G[2], gb_q = -0.5 * (double)G[3], gc_q = -0.5 * (double)G[4];
+      const double ga_q = -0.5 * (double)G[2], gb_q = -0.5 * (double)G[4], gc_q = -0.5 * (double)G[5];
       // T1 = Gq Q
       const double t00 = ga_q * Qa + gb_q * Qb, t01 = ga_q * Qb + gb_q * Qc;
       const double t10 = gb_q * Qa + gc_q * Qb, t11 = gb_q * Qb + gc_q * Qc;
@@ -356,7 +359,7 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
       } else {
         gx[2] += dJ[5] * (V.fy * S.Lcy * iz * iz);
       }
-      gx[2] += (double)G[9];
+      gx[2] += (double)Y[3];
       for (int j = 0; j < 3; ++j) gp[j] += V.R[j] * gx[0] + V.R[3 + j] * gx[1] + V.R[6 + j] * gx[2];
       // twist: rho = gx; phi = xc x gx - 2 vee(Sc Gc - Gc Sc)
       tw[0] = gx[0]; tw[1] = gx[1]; tw[2] = gx[2];
@@ -373,7 +376,7 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
       tw[3] = S.xc[1] * gx[2] - S.xc[2] * gx[1] - 2.0 * A[7];
       tw[4] = S.xc[2] * gx[0] - S.xc[0] * gx[2] - 2.0 * A[2];
       tw[5] = S.xc[0] * gx[1] - S.xc[1] * gx[0] - 2.0 * A[3];
-      glogit += (double)G[5] * P.o * (1.0 - P.o);
+      glogit += (double)G[3] * (1.0 - P.o);
       float* C = contrib + ci * 16;
       for (int k = 0; k < 3; ++k) C[k] = (float)gp[k];
       for (int k = 0; k < 9; ++k) C[3 + k] = (float)gM[k];
@@ -440,7 +443,7 @@ __global__ void __launch_bounds__(256) k_project_bwd(
         for (int k = 0; k < 9; ++k) gM[k] += (double)C[3 + k];
         glogit += (double)C[12];
         const float* G = grad2d + (size_t)cix[u] * kPartials;
-        for (int k = 0; k < 20; ++k) gy[k] += G[6 + k];
+        for (int k = 0; k < 20; ++k) gy[k] += G[k];
       }
     }
   }
@@ -520,7 +523,7 @@ __global__ void __launch_bounds__(256) k_group_geo_acc(const float* __restrict__
   const int64_t m = (int64_t)cnt->n_visible * 6;
   if (i >= m || cnt->overflow) return;
   const int64_t c = i / 6, k = i - 6 * c;
-  const float v = grad2d_g[(size_t)c * kPartials + k];
+  const float v = grad2d_g[(size_t)c * kPartials + kPartGeo + k];
   geo_acc[i] = first ? v : geo_acc[i] + v;
 }
 
@@ -530,11 +533,11 @@ __global__ void __launch_bounds__(256) k_group_geo_add(float* __restrict__ grad2
   const int64_t m = (int64_t)cnt->n_visible * 6;
   if (i >= m || cnt->overflow) return;
   const int64_t c = i / 6, k = i - 6 * c;
-  grad2d[(size_t)c * kPartials + k] += geo_acc[i];
+  grad2d[(size_t)c * kPartials + kPartGeo + k] += geo_acc[i];
 }
 
 // a feature group's gradients: sum over the views where the Gaussian is
-// visible of its colour partials f0.. (slots 10 ..), zero elsewhere
+// visible of its colour partials f0.. (slots 4 ..), zero elsewhere
 __global__ void __launch_bounds__(256) k_group_feat_grad(int n_views, int64_t n, uint32_t npad_shift,
                                                          const Counters* __restrict__ cnt,
                                                          const uint32_t* __restrict__ cnt_t,
@@ -550,7 +553,7 @@ __global__ void __launch_bounds__(256) k_group_feat_grad(int n_views, int64_t n,
       const uint64_t rid = ((uint64_t)v << npad_shift) | (uint64_t)g;
       if (cnt_t[rid] != 0) {
         const float* G = grad2d_g + (size_t)cidx[rid] * kPartials;
-        for (int k = 0; k < 16; ++k) acc[k] += G[10 + k];
+        for (int k = 0; k < 16; ++k) acc[k] += G[4 + k];
       }
     }
   for (int k = 0; k < 16; ++k)

@@ -24,13 +24,11 @@
 //
 // Backward.  Each wave restarts from the last contributor of its pixels and
 // walks the list backwards, recovering T before each entry as T / (1 - alpha)
-// and the weighted sum of what lies behind as a single running scalar.  Per
-// entry, the 6 geometric sums (the moments of dL/dm2 over the pixel offsets
-// dx, dy, dx^2, dx dy, dy^2, and dL/dalpha-weighted G for the opacity) are
-// summed over the wave by a butterfly transpose-reduction; the 20 colour /
-// depth / feature partials, sum_p w_p g_p, are collected for batches of 8
-// entries as a (entries x pixels) x (pixels x channels) product on the matrix
-// cores.  Both go to the entry's own (Gaussian, block) slot; a segmented
+// and the weighted sum of what lies behind as a single running scalar.  The
+// sums over the wave's pixels, 6 geometric (the moments 1, dx, dy, dx^2, dx dy,
+// dy^2 of dL/dalpha alpha) and 20 colour / depth / feature partials, sum_p w_p
+// g_p, are products on the matrix cores over batches of 16 entries.  Both go
+// to the entry's own (Gaussian, block) slot; a segmented
 // reduction over each Gaussian's slots then forms its gradient.  No atomics:
 // results are deterministic run to run.
 #include "lgs_internal.h"
@@ -134,34 +132,6 @@ __device__ __forceinline__ GeomRec rec_of_lane(const GeomRec* __restrict__ geom,
   return *(const GeomRec*)((const char*)geom + off);
 }
 
-// Appearance record words of Gaussian g (10 words in BF16 storage, 20 in
-// FP32) and their unpacking into the 20-vector [r, g, b, (z), f0..f15]; slot
-// 3 is filled by the caller with the view's depth.
-template <bool BF16>
-__device__ __forceinline__ void load_app_words(const void* __restrict__ app, uint32_t g, uint32_t w[20]) {
-  // (a 32-bit byte offset: the records stay below 2^32 bytes)
-  const uint32_t* a = (const uint32_t*)((const char*)app + g * (BF16 ? 40u : 80u));
-#pragma unroll
-  for (int k = 0; k < (BF16 ? 10 : 20); ++k) w[k] = a[k];
-}
-
-template <bool BF16>
-__device__ __forceinline__ void y_from_words(const uint32_t u[20], float y[20]) {
-  if (BF16) {
-    y[0] = __uint_as_float(u[0] << 16);
-    y[1] = __uint_as_float(u[0] & 0xffff0000u);
-    y[2] = __uint_as_float(u[1] << 16);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      y[4 + 2 * k] = __uint_as_float(u[2 + k] << 16);
-      y[5 + 2 * k] = __uint_as_float(u[2 + k] & 0xffff0000u);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 20; ++k) y[k] = __uint_as_float(u[k]);
-  }
-}
-
 // Pop one work item for the whole wave.  Every active lane executes the
 // atomic (no lane-dependent branch around it): the first active lane adds 1,
 // the others 0, and the first active lane's return value is broadcast.  A
@@ -191,11 +161,12 @@ __device__ __forceinline__ uint32_t next_item(uint32_t* ctr, const uint32_t* __r
 // memory, their accesses are global ones and not flat ones (which wait on the
 // LDS counter too).
 typedef __attribute__((address_space(1))) float* gfloat_ptr;
+typedef __attribute__((address_space(3))) float* lds_ptr;
+__device__ __forceinline__ float gload(const float* p) { return *(gfloat_ptr)p; }
 __device__ __forceinline__ void gstore(float* p, float x) { *(gfloat_ptr)p = x; }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 // Forward accumulation on the matrix cores.
 //
@@ -481,18 +452,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
   }
 }
 
-// Butterfly transpose-reductions: every lane holds a vector of values and
-// the lanes' vectors are summed value by value, each lane ending with one of
-// the sums.  Each step pairs every lane with a partner, each keeps one half
-// of its values and adds the partner's copy of that half: cross-row steps use
-// the gfx950 permlane swaps (no selects: the swap itself hands each half to
-// the lane that keeps it), in-row steps a bit-select and a DPP read of the
-// partner.
-__device__ __forceinline__ float bsel(bool hi, float a, float b) {   // hi ? b : a
-  const uint32_t m = hi ? 0xffffffffu : 0u;
-  return __uint_as_float((__float_as_uint(a) & ~m) | (__float_as_uint(b) & m));
-}
-
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
@@ -504,22 +463,56 @@ __device__ __forceinline__ int wave_max_i32(int x) {
   return x;
 }
 
-constexpr int kZRow = 72;                  // bf16 per LDS row (64 pixels + pad; 144 B, 16-B aligned)
-// Blend-weight rows of a batch of 8 entries: three exact BF16 terms each.
-constexpr int kWRows = 24;
-// At each flush the batch's partial records are assembled in the weight
-// rows, whose weights the products have consumed by then: record e (36
-// floats: the 32 of a slot + pad) fills the 144 bytes of weight row e.  The
-// geometric sums of the batch's entries wait in a small area of their own.
-constexpr int kRecLds = 36;
-static_assert(kRecLds * 4 == kZRow * 2, "a record fills one weight row");
-constexpr int kGeoStride = 8;              // floats per entry of the geometric staging
-constexpr int kGeoBytes = 8 * kGeoStride * 4;
-// LDS bytes of one backward wave: upstream rows, blend-weight rows,
-// geometric staging
-__host__ __device__ constexpr int bwd_wave_lds_bytes(int up_mode) {
-  return (bwd_upstream_rows(up_mode) + kWRows) * kZRow * 2 + kGeoBytes;
+// Backward compositing.  What bounds it: VALU issue when every SIMD holds
+// several waves (large calls), and the latency of one wave's entry loop when
+// a call has few blocks (a single view has about as many blocks as the chip
+// has wave slots).  So what is a contraction goes to the matrix cores, whose
+// pipe is idle otherwise, and what an entry reads is requested an entry (its
+// geometry) or a group of four entries (their appearance) ahead.
+//   - gy[p] = sum_c g[p][c] y[c], per pixel and entry: for four entries at
+//     once by the 16-block 4 x 4 products (block b: the four lanes 4 b ..
+//     4 b + 3, its columns their pixels, its rows the four entries; the A
+//     block of 4 channels broadcast to all blocks by cbsz / abid).  The
+//     appearance is the A operand as it is loaded: lane 4 q + i brings
+//     channels 4 q .. 4 q + 3 of entry i.  With BF16 appearance and the sign
+//     upstream, v_mfma_f32_4x4x4_16b_bf16 takes 4 channels an instruction
+//     (exact products); else v_mfma_f32_4x4x1_16b_f32 takes one (FP32 fused
+//     multiply-adds).
+//   - the six geometric sums sum_p u[p] {1, X, Y, X^2, X Y, Y^2}, u =
+//     dL/dalpha alpha, over each 4 x 4 quarter of the block, X, Y the pixel's
+//     position from the quarter's centre: (6 x pixels) x (pixels x entries) in
+//     FP32 (v_mfma_f32_16x16x4_f32), once per batch of 16 entries; then each
+//     quarter's sums are moved to the entry's mean in the product's own lanes
+//     and added.  (Quarters, because the move cancels: over the whole block at
+//     once the gradients of small Gaussians were up to twice as far from FP64.)
+//     Some rows of A repeat so that every lane holds what its share needs.
+//   - the 20 colour partials sum_p g[p][c] w[p]: (channels x pixels) x (pixels
+//     x entries) on BF16 terms whose sums are exact, once per batch; a lane
+//     then holds four consecutive channels of one entry and stores them as
+//     they are.
+// The vector and the matrix pipe of a SIMD hardly overlap here (their busy
+// cycles add up to nearly all of the kernel's), so a product is worth its place
+// only where it takes fewer cycles than the vector instructions it replaces.
+// Per visited entry 56 vector instructions (88 with the sums by lane exchanges
+// and dot products and a batch of 8), 3 of them products, and 30 scalar ones.
+// 500k Gaussians, 8 views, BF16, fused L1: 1366 -> 1060 us; 300k, 640 x 480,
+// FP32: 242 -> 172 us; 2k, 128 x 96: 49 -> 31 us (there the records in flight
+// an entry ahead and a block's planes requested at once count).  Batches of 8
+// took 1190 us; five waves per SIMD in place of four changed nothing.
+constexpr int kBatch = 16;                 // entries per batch
+constexpr int kZRow = 72;                  // bf16 per upstream row (64 pixels + pad; 144 B, 16-B aligned)
+constexpr int kWRow = 68;                  // floats per weight / u row (64 pixels + pad; 272 B, 16-B aligned)
+constexpr int kBatchBytes = 2 * kBatch * kWRow * 4;
+// LDS bytes of one backward wave: the batch's weight rows and u rows (FP32),
+// and the upstream rows of channels 16-19 (BF16, hi, and lo with a given
+// upstream).  The block's other upstream rows (hi 0-15, then lo) pass through
+// the batch's rows on their way into registers.
+__host__ __device__ constexpr int bwd_wave_lds(int up_mode) {
+  return kBatchBytes + (up_mode == UP_EXPLICIT ? 8 : 4) * kZRow * 2;
 }
+static_assert(32 * kZRow * 2 <= kBatchBytes, "the upstream rows fit");
+// ... and of the work-group: a quarter's basis, [6][16 pixels] FP32
+constexpr int kBasisBytes = 6 * 16 * 4;
 // FP32 -> BF16 bits, round to nearest even (finite inputs)
 __device__ __forceinline__ unsigned short bf16_rne(float x) {
   const uint32_t u = __float_as_uint(x);
@@ -527,38 +520,14 @@ __device__ __forceinline__ unsigned short bf16_rne(float x) {
 }
 __device__ __forceinline__ float bf16_to_f(unsigned short h) { return __uint_as_float((uint32_t)h << 16); }
 
-// Transpose-reduction of 6 values over the whole wave: on exit lane l holds
-// the wave sum of value red6_index(l).  Partners: l ^ 32 (permlane32 swap:
-// lanes below 32 keep values 0..2, the others 3..5), l ^ 16 (permlane16
-// swap: values 0 / 1 split by row parity, value 2 summed in every row), l ^ 8
-// (row_ror:8: bit 3 chooses between the two), then 7 - (l & 7), l ^ 2, l ^ 1.
-__device__ __forceinline__ int red6_index(int l) { return 3 * (l >> 5) + ((l & 8) ? 2 : (l >> 4) & 1); }
-__device__ __forceinline__ float transpose_reduce6(const float v[6], int lane) {
-  float a[3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[3 + i]), false, false);
-    a[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  auto r01 = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[0]), __float_as_uint(a[1]), false, false);
-  const float b = __uint_as_float(r01[0]) + __uint_as_float(r01[1]);
-  auto r22 = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[2]), __float_as_uint(a[2]), false, false);
-  const float b2 = __uint_as_float(r22[0]) + __uint_as_float(r22[1]);
-  const bool h8 = (lane & 8) != 0;
-  float c = bsel(h8, b, b2) + dpp<0x128>(bsel(h8, b2, b));
-  c = c + dpp<0x141>(c);
-  c = c + dpp<0x4E>(c);
-  return c + dpp<0xB1>(c);
-}
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ int amdgcn_writelane(int val, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
-// Waves per SIMD: what the LDS of each upstream form allows (six for the
-// fused L1 gradient, 80 VGPRs, measured fastest; five with the colour
-// gradient's extra rows; four with a given upstream's hi + lo rows), so that
-// the VGPR budget is no tighter than the occupancy LDS permits.
-constexpr int bwd_waves_per_eu(int up_mode) { return up_mode == UP_L1 ? 6 : (up_mode == UP_RGB ? 5 : 4); }
+// Four waves per SIMD (128 VGPRs; what the LDS allows too).
 template <bool BF16, int UPM, bool CNT>
-__global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(bwd_waves_per_eu(UPM), bwd_waves_per_eu(UPM)))) k_raster_bwd(
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) k_raster_bwd(
     Settings st, const ViewDesc* __restrict__ views, const ViewImages* __restrict__ upstream,
     const ViewImages* __restrict__ fwd_out, const ViewImages* __restrict__ targets,
     const float* __restrict__ loss_w, const uint2* __restrict__ ranges,
@@ -569,23 +538,33 @@ __global__ void __launch_bounds__(256)
     const float* __restrict__ T_state, const uint32_t* __restrict__ slot_base,
     float* __restrict__ partials, uint8_t* __restrict__ mask) {
   const int lane = threadIdx.x & 63;
-  extern __shared__ unsigned short lds_z[];
+  extern __shared__ float lds_z[];
   // upstream per channel: the sign of the L1 residual (formed here from the
   // forward's images and the targets; exact in BF16, the per-channel scale is
   // applied after the product) or a given FP32 value (split hi + lo)
   constexpr bool kSignRGB = UPM == UP_L1;
   constexpr bool kSignDF = UPM != UP_EXPLICIT;
-  // this wave's LDS rows (BF16, 64 pixels + pad each): the block's upstream
-  // per channel, hi (20) and lo (for the given channels: 20, or the 3 colour
-  // channels), and the blend weights of up to 8 batched entries in three
-  // exact terms (rows 0-7, 8-15, 16-23); then the geometric staging
-  constexpr int kGRows = bwd_upstream_rows(UPM);
-  unsigned short* lz = lds_z + (threadIdx.x >> 6) * (bwd_wave_lds_bytes(UPM) / 2);
-  unsigned short* wz = lz + kGRows * kZRow;
-  float* recs = (float*)wz;                         // records, at flush time
-  float* geo = (float*)(wz + kWRows * kZRow);       // 8 entries x kGeoStride floats
+  // gy's feature part (and RGB with the sign upstream) on BF16 products
+  constexpr bool kDotGy = BF16 && kSignDF;
+  float* tab = lds_z;                                // [6][16] basis, the same from every wave
+  float* ws = lds_z + kBasisBytes / 4 + (threadIdx.x >> 6) * (bwd_wave_lds(UPM) / 4);   // weight rows
+  float* us = ws + kBatch * kWRow;                                                      // u rows
+  lds_ptr wl = (lds_ptr)(ws + lane);                 // this lane's place in a row
+  asm volatile("" : "+v"(wl));   // (one addition of a scalar per entry)
+  unsigned short* wz = (unsigned short*)ws;          // upstream rows, before the first batch
+  unsigned short* gz = wz + kBatchBytes / 2;         // upstream rows of channels 16-19 (hi, lo)
   const int grp = lane >> 4, col = lane & 15;
   if (cnt->overflow) return;
+  if (lane < 16) {
+    const float X = (float)(lane & 3) - 1.5f, Y = (float)(lane >> 2) - 1.5f;
+    const float b[6] = {1.f, X, Y, X * X, X * Y, Y * Y};
+#pragma unroll
+    for (int m = 0; m < 6; ++m) tab[m * 16 + lane] = b[m];
+  }
+  // appearance of a group of four entries: lane 4 q + i loads channels 4 q ..
+  // 4 q + 3 of entry i (q < 5; the lanes past them repeat the last channels)
+  const __amdgpu_buffer_rsrc_t app_b = app_buffer(app);
+  const uint32_t yoff = (uint32_t)min(lane >> 2, 4) * (BF16 ? 8u : 16u), yent = 8u * ((uint32_t)lane & 3u);
   // this wave's work (CNT: the profiling variant), added to the 64-bit
   // counters once at the end (a wave's own count stays far below 2^32)
   uint32_t n_eval = 0, n_con = 0, n_ent = 0, n_wr = 0;
@@ -606,57 +585,69 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int c = 0; c < 20; ++c) g[c] = 0.f;
     if (inside) {
-      last = last_idx[(size_t)V->pix_off + p];
-      Tfin = T_state[(size_t)V->pix_off + p];
+      // every plane requested before any value is used (planes past nfeat read
+      // the first feature plane, which is there, and drop it): a load under a
+      // test of its own would be waited for alone, one round trip per channel
+      float a[20], b[20];
+      auto feat_at = [&](const float* f, int c) { return gload(f + (c < st.nfeat ? c : 0) * HW + p); };
       if (kSignDF) {
         const ViewImages Y = fwd_out[v], Yt = targets[v];
-        const float s_rgb = loss_w[0] / (3.f * (float)HW), s_d = loss_w[1] / (float)HW;
-        const float s_f = loss_w[2] / (16.f * (float)HW);
-        if (kSignRGB) {
+        const float* __restrict__ Urgb = kSignRGB ? nullptr : upstream[v].rgb;
 #pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const float d = Y.rgb[c * HW + p] - Yt.rgb[c * HW + p];
-            g[c] = d > 0.f ? s_rgb : (d < 0.f ? -s_rgb : 0.f);
-          }
-        } else {
-          const float* __restrict__ Urgb = upstream[v].rgb;
-#pragma unroll
-          for (int c = 0; c < 3; ++c) g[c] = Urgb[c * HW + p];
+        for (int c = 0; c < 3; ++c) {
+          a[c] = kSignRGB ? gload(Y.rgb + c * HW + p) : gload(Urgb + c * HW + p);
+          b[c] = kSignRGB ? gload(Yt.rgb + c * HW + p) : 0.f;
         }
-        {
-          const float d = Y.depth[p] - Yt.depth[p];
-          g[3] = d > 0.f ? s_d : (d < 0.f ? -s_d : 0.f);
-        }
+        a[3] = gload(Y.depth + p);
+        b[3] = gload(Yt.depth + p);
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-          const float d = c < st.nfeat ? Y.feat[c * HW + p] - Yt.feat[c * HW + p] : 0.f;
-          g[4 + c] = d > 0.f ? s_f : (d < 0.f ? -s_f : 0.f);
+          a[4 + c] = feat_at(Y.feat, c);
+          b[4 + c] = feat_at(Yt.feat, c);
         }
       } else {
         const ViewImages U = upstream[v];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) g[c] = U.rgb[c * HW + p];
-        g[3] = U.depth[p];
+        for (int c = 0; c < 3; ++c) a[c] = gload(U.rgb + c * HW + p);
+        a[3] = gload(U.depth + p);
 #pragma unroll
-        for (int c = 0; c < 16; ++c) g[4 + c] = c < st.nfeat ? U.feat[c * HW + p] : 0.f;
-        if (U.T) gT = U.T[p];
+        for (int c = 0; c < 16; ++c) a[4 + c] = feat_at(U.feat, c);
+        if (U.T) gT = gload(U.T + p);
+      }
+      last = last_idx[(size_t)V->pix_off + p];
+      Tfin = T_state[(size_t)V->pix_off + p];
+      asm volatile("" ::: "memory");
+      if (kSignDF) {
+        const float s_rgb = loss_w[0] / (3.f * (float)HW), s_d = loss_w[1] / (float)HW;
+        const float s_f = loss_w[2] / (16.f * (float)HW);
+#pragma unroll
+        for (int c = 0; c < 20; ++c) {
+          const float sc = c < 3 ? s_rgb : (c == 3 ? s_d : s_f), d = a[c] - b[c];
+          g[c] = c < 3 && !kSignRGB ? a[c] : (d > 0.f ? sc : (d < 0.f ? -sc : 0.f));
+          if (c >= 4 && c - 4 >= st.nfeat) g[c] = 0.f;
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < 20; ++c) g[c] = c < 4 || c - 4 < st.nfeat ? a[c] : 0.f;
       }
     }
     // every lane holds the same maximum; readfirstlane makes that visible to
     // the compiler, so the entry loop below stays on the scalar unit
     const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i32(last));
-    if (kmax < 0) continue;
     const uint32_t tile = (uint32_t)V->tile_off + (by >> st.tile_shift) * (uint32_t)V->tiles_x +
                           (bx >> st.tile_shift);
     const uint32_t kbeg = ranges[tile].x;
+    if (kmax < (int)kbeg) continue;
+    const float pxb = kPixBias + (float)px, pyb = kPixBias + (float)py;
     const float gTT = gT * Tfin;
     float Tc = Tfin, sB = 0.f;
     // upstream rows: for the fused L1 gradient the sign (exact in BF16; the
     // per-channel scale is applied to the MFMA result), else hi + lo BF16.
     // The colour partials of a batch of entries, dY[e][c] = sum_p w[p][e] g[p][c],
     // are a (entries x pixels) x (pixels x channels) product: v_mfma_f32_16x16x32_bf16
-    // on the two-term splits (hi.hi + lo.hi, + hi.lo for a general upstream),
-    // FP32 accumulation.
+    // on the exact terms of w (and hi + lo of a general upstream), FP32
+    // accumulation.  The rows are written once per block and read back
+    // transposed as the products' B operands, which stay in registers.
     float gscale[3] = {1.f, 1.f, 1.f};
     if (kSignDF) {
       const float HWf = (float)HW;
@@ -664,110 +655,172 @@ __global__ void __launch_bounds__(256)
       gscale[1] = loss_w[1] / HWf;
       gscale[2] = loss_w[2] / (16.f * HWf);
     }
+    asm volatile("" ::: "memory");   // (the last block's record reads come before)
 #pragma unroll
     for (int c = 0; c < 20; ++c) {
+      unsigned short* row = c < 16 ? wz + c * kZRow : gz + (c - 16) * kZRow;
       if (c < 3 ? kSignRGB : kSignDF) {
         const float sgn = g[c] > 0.f ? 1.f : (g[c] < 0.f ? -1.f : 0.f);
-        lz[c * kZRow + lane] = bf16_rne(sgn);
+        row[lane] = bf16_rne(sgn);
       } else {
         const unsigned short hi = bf16_rne(g[c]);
-        lz[c * kZRow + lane] = hi;
-        lz[(20 + c) * kZRow + lane] = bf16_rne(g[c] - bf16_to_f(hi));
+        row[lane] = hi;
+        row[(c < 16 ? 16 : 4) * kZRow + lane] = bf16_rne(g[c] - bf16_to_f(hi));
       }
     }
-    // Feature part of gy = sum_c g[c] y[c] with BF16 appearance and the sign
-    // upstream: s_f sum_f sign_f y_f, the sum by packed BF16 dot products of
-    // the appearance words (two features each, used as they are stored) with
-    // the signs packed the same way; every product is exact.
-    constexpr bool kDotGy = BF16 && kSignDF;
-    uint32_t sg2[8];
+    asm volatile("" ::: "memory");
+    bf16x8_t bh0[2], bl0[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int off = 32 * ks + 8 * grp;
+      bh0[ks] = *(const bf16x8_t*)(wz + col * kZRow + off);
+      if (UPM == UP_EXPLICIT) {
+        bl0[ks] = *(const bf16x8_t*)(wz + (16 + col) * kZRow + off);
+      } else if (UPM == UP_RGB) {   // lo rows exist for the three colour channels only
+        bl0[ks] = *(const bf16x8_t*)(wz + (16 + (col < 3 ? col : 0)) * kZRow + off);
+        if (col >= 3) bl0[ks] = (bf16x8_t){};
+      }
+    }
+    asm volatile("" ::: "memory");
+    // B operands of gy with the sign upstream and BF16 appearance: the signs
+    // of channels 4 k .. 4 k + 3 (slot 3, the depth, apart)
+    s16x4_t sg[5];
     if (kDotGy) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float a = g[4 + 2 * k], b = g[5 + 2 * k];
-        const uint32_t lo = a > 0.f ? 0x3f80u : (a < 0.f ? 0xbf80u : 0u);
-        const uint32_t hi = b > 0.f ? 0x3f80u : (b < 0.f ? 0xbf80u : 0u);
-        sg2[k] = lo | (hi << 16);
-      }
+      for (int k = 0; k < 5; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float a = g[4 * k + i];
+          sg[k][i] = k == 0 && i == 3 ? (short)0 : (a > 0.f ? (short)0x3f80 : (a < 0.f ? (short)0xbf80 : (short)0));
+        }
     }
     int nb = 0;
-    uint32_t slotv = 0;   // lane e: the slot of the batch's entry e
-    // Write the batch's nb partial records: the colour partials, sum_p w_p
-    // g_p, come from the matrix cores; the three weight terms go through
-    // K-stacked products (each term against the same upstream rows), so
-    // with a sign upstream every product is exact and only the FP32
-    // accumulation rounds.  Then the records are assembled in the consumed
-    // weight rows (colour partials and the staged geometric sums), lanes
-    // store 16-byte quarters of them (seven quarters, 112 bytes, of each
-    // 128-byte slot; 8 lanes per record) and the first lane of each record
-    // sets the slot's mask byte.
+    uint32_t ridv = 0;   // lane e: the record id of the batch's entry e
+    // Write the batch's nb partial records: the colour partials, sum_p g_p
+    // w_p (each weight term against the same upstream, so with a sign upstream
+    // every product is exact and only the FP32 accumulation rounds), and the
+    // moments of u.  Lane (grp, col) gets channels 4 grp .. 4 grp + 3 of entry
+    // col, channels 16 .. 19 in group 0, and the moments 1, X, Y, X^2 in group
+    // 1; 1, X, Y, X Y in group 2; 1, Y, Y, Y^2 in group 3.
     auto flush = [&]() {
-      f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
-      const int er = col & 7;
-      const int ch1 = col < 4 ? 16 + col : 16;
+      // (its lane constants are worked out here: the registers that they would
+      // hold across the entry loop are short)
+      int fl = lane;
+      asm volatile("" : "+v"(fl));
+      const int grp = fl >> 4, col = fl & 15;
+      // the entries' geometry and slot bases again (used after the products)
+      const uint32_t re = (uint32_t)__builtin_amdgcn_ds_bpermute(col * 4, (int)ridv);
+      const GeomRec* __restrict__ ge = geom + re;
+      const float emx = ge->mx, emy = ge->my;
+      const uint32_t ebb = ge->bbox, esb = slot_base[re];
+      asm volatile("" ::: "memory");
+      f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f}, m[4];
+      {
+        // K index: pixel (s, grp) of the quarter; the basis row that this
+        // lane's row of A repeats (rows 0-3 are not used)
+        const int trow = (int)(((col < 8 ? 0x32100000u : 0x52204210u) >> (4 * (col & 7))) & 15u);
+        const f32x4 ta = *(const f32x4*)(tab + trow * 16 + 4 * grp);
+        const float* ur = us + col * kWRow + 8 * grp;
+        f32x4 ub[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {   // quarter h: columns 4 (h & 1) .., rows 4 (h >> 1) .. of the block
+          ub[h] = *(const f32x4*)(ur + 32 * (h >> 1) + 4 * (h & 1));
+          m[h] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int h = 0; h < 4; ++h) m[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(ta[s], ub[h][s], m[h], 0, 0, 0);
+      }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         const int off = 32 * ks + 8 * grp;
-        bf16x8_t aw[3];   // output rows 8..15 repeat rows 0..7
+        // w = hi + mid + lo exactly: each term keeps the top 8 significant bits
+        // of what is left (truncation), so each is a BF16 value: the high
+        // halves of two pixels' words are packed by one byte permutation
+        uint32_t tw[3][4];
+        {
+#pragma clang fp contract(off)
+          const f32x4 w0 = *(const f32x4*)(ws + col * kWRow + off), w1 = *(const f32x4*)(ws + col * kWRow + off + 4);
 #pragma unroll
-        for (int t = 0; t < 3; ++t) aw[t] = *(const bf16x8_t*)(wz + (8 * t + er) * kZRow + off);
-        const bf16x8_t bh0 = *(const bf16x8_t*)(lz + col * kZRow + off);
-        bf16x8_t bh1 = *(const bf16x8_t*)(lz + ch1 * kZRow + off);
-        if (col >= 4) bh1 = (bf16x8_t){};
+          for (int e = 0; e < 4; ++e) {
+            uint32_t t3[2][3];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const float w = e < 2 ? w0[2 * e + i] : w1[2 * e - 4 + i];
+              const float r1 = w - __uint_as_float(__float_as_uint(w) & 0xffff0000u);
+              const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+              t3[i][0] = __float_as_uint(w);
+              t3[i][1] = __float_as_uint(r1);
+              t3[i][2] = __float_as_uint(r2);
+            }
+#pragma unroll
+            for (int t = 0; t < 3; ++t) tw[t][e] = __builtin_amdgcn_perm(t3[1][t], t3[0][t], 0x07060302u);
+          }
+        }
+        bf16x8_t aw[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+          aw[t] = __builtin_bit_cast(bf16x8_t, make_uint4(tw[t][0], tw[t][1], tw[t][2], tw[t][3]));
+        // (rows 4-15 of the second product repeat rows 0-3 and are not used)
+        const bf16x8_t bh1 = *(const bf16x8_t*)(gz + (col & 3) * kZRow + off);
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
-          c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[t], bh0, c0, 0, 0, 0);
-          c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[t], bh1, c1, 0, 0, 0);
+          c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh0[ks], aw[t], c0, 0, 0, 0);
+          c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh1, aw[t], c1, 0, 0, 0);
         }
         if (UPM == UP_EXPLICIT) {
           // the given upstream's lo term (relative 2^-8 of hi) against the two
           // leading weight terms: the dropped products are below 2^-24
-          const bf16x8_t bl0 = *(const bf16x8_t*)(lz + (20 + col) * kZRow + off);
-          bf16x8_t bl1 = *(const bf16x8_t*)(lz + (20 + ch1) * kZRow + off);
-          if (col >= 4) bl1 = (bf16x8_t){};
+          const bf16x8_t bl1 = *(const bf16x8_t*)(gz + (4 + (col & 3)) * kZRow + off);
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
-            c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[t], bl0, c0, 0, 0, 0);
-            c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[t], bl1, c1, 0, 0, 0);
+            c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl0[ks], aw[t], c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl1, aw[t], c1, 0, 0, 0);
           }
         } else if (UPM == UP_RGB) {
-          // lo rows exist for the three colour channels only
-          bf16x8_t bl0 = *(const bf16x8_t*)(lz + (20 + (col < 3 ? col : 0)) * kZRow + off);
-          if (col >= 3) bl0 = (bf16x8_t){};
 #pragma unroll
-          for (int t = 0; t < 2; ++t) c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[t], bl0, c0, 0, 0, 0);
+          for (int t = 0; t < 2; ++t) c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl0[ks], aw[t], c0, 0, 0, 0);
         }
       }
-      // every read of the weight rows above precedes the record writes below
-      // (LDS operations of a wave run in order; this keeps the compiler from
-      // moving the differently typed accesses across each other)
+      // (the reads above precede the next batch's writes: the LDS operations
+      // of a wave run in order; this keeps the compiler's order too)
       asm volatile("" ::: "memory");
-      const float s0 = col < 3 ? gscale[0] : (col == 3 ? gscale[1] : gscale[2]);
-      const float s1 = gscale[2];
-      if (grp < 2) {   // output rows 8..15 repeat rows 0..7
+      const uint32_t ebx = ebb & 255u, eby = (ebb >> 16) & 255u;
+      const uint32_t sl = esb + (by - eby) * (((ebb >> 8) & 255u) - ebx + 1u) + (bx - ebx);
+      // dx = X + xq, dy = Y + yq in quarter h; groups 1 and 3 move their second
+      // moment (X^2 along x, Y^2 along y) by the same steps, group 2 X Y
+      const float x0 = ((float)(8 * ((int)bx - (int)ebx)) - emx) + 1.5f;
+      const float y0 = ((float)(8 * ((int)by - (int)eby)) - emy) + 1.5f;
+      float g0 = 0.f, g1 = 0.f, g2 = 0.f, g3 = 0.f, gxy = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float* rec = recs + (4 * grp + i) * kRecLds;
-          rec[6 + col] = c0[i] * s0;
-          if (col < 4) rec[22 + col] = c1[i] * s1;
+      for (int h = 0; h < 4; ++h) {
+        const float xq = (h & 1) ? x0 + 4.f : x0, yq = (h >> 1) ? y0 + 4.f : y0;
+        const float pq = grp == 3 ? yq : xq;
+        const float f1 = __builtin_fmaf(pq, m[h][0], m[h][1]), f2 = __builtin_fmaf(yq, m[h][0], m[h][2]);
+        g0 += m[h][0];
+        g1 += f1;
+        g2 += f2;
+        g3 += __builtin_fmaf(pq, m[h][1] + f1, m[h][3]);
+        gxy += __builtin_fmaf(xq, f2, __builtin_fmaf(yq, m[h][1], m[h][3]));
+      }
+      const float s0 = grp == 0 ? gscale[0] : gscale[2], s3 = grp == 0 ? gscale[1] : gscale[2];
+      float* rec = partials + (size_t)sl * kSlotFloats;
+      if (col < nb) {
+        *(float4*)(rec + 4 * grp) = make_float4(c0[0] * s0, c0[1] * s0, c0[2] * s0, c0[3] * s3);
+        if (grp < 2) {
+          float4 v4;
+          v4.x = grp == 0 ? c1[0] * gscale[2] : g1;   // Sx
+          v4.y = grp == 0 ? c1[1] * gscale[2] : g2;   // Sy
+          v4.z = grp == 0 ? c1[2] * gscale[2] : g3;   // Sxx
+          v4.w = grp == 0 ? c1[3] * gscale[2] : g0;   // S0
+          *(float4*)(rec + 16 + 4 * grp) = v4;
+        } else {
+          rec[22 + grp] = grp == 2 ? gxy : g3;        // Sxy, Syy
         }
+        if (grp == 0) mask[sl] = 1;
       }
-      if (lane < 48) {   // the geometric sums of the batch's entries
-        const int e = lane / 6, k = lane - 6 * e;
-        recs[e * kRecLds + k] = geo[e * kGeoStride + k];
-      }
-      const int er4 = lane >> 3, q4 = lane & 7;
-      const float4 v4 = *(const float4*)(recs + er4 * kRecLds + 4 * q4);
-      const uint32_t sl = (uint32_t)__builtin_amdgcn_ds_bpermute(er4 * 4, (int)slotv);
-      // quarters 0..6 hold the kPartials values; the eighth is padding that
-      // the reduction never reads, so it is not written
-      static_assert(kPartials <= 28, "the partials fit in seven 16-byte quarters");
-      if (er4 < nb && q4 < 7) {
-        *(float4*)(partials + (size_t)sl * kSlotFloats + 4 * q4) = v4;
-        if (q4 == 0) mask[sl] = 1;
-      }
-      // the record reads above precede the next batch's weight writes
-      asm volatile("" ::: "memory");
+      static_assert(kPartGeo == 20 && kPartials == 26, "the record's layout");
       nb = 0;
     };
     // the list entries of the next chunk are requested a chunk ahead
@@ -785,103 +838,140 @@ __global__ void __launch_bounds__(256)
       }
       if (kl - 64 >= (int)kbeg) rid_n = vals[kl - 64];
       uint64_t hm = __builtin_amdgcn_ballot_w64(hit);
-      while (hm) {
-        const uint32_t j = (uint32_t)__builtin_ctzll(hm);
-        hm &= hm - 1ull;
-        const int k = top - (int)j;
-        const uint32_t rid = __builtin_amdgcn_readlane(rid_l, j);
-        // the entry's three records are requested together, before the
-        // evaluation, so their latencies overlap (the appearance and the slot
-        // base are not needed when no lane contributes, but loading them
-        // anyway costs less than a second round trip when one does)
-        const GeomRec gr = *(const GeomRec*)((const char*)geom + (rid << 5));
-        uint32_t yw[BF16 ? 10 : 20];
-        load_app_words<BF16>(app, rid & npad_mask, yw);
-        const uint32_t sbase = *(const uint32_t*)((const char*)slot_base + (rid << 2));
-        // the compiler would sink the appearance and slot-base loads below the
-        // no-contribution exit, a second round trip after the evaluation's;
-        // using every loaded word here, before the geometry's first use,
-        // keeps the three requests and their one wait together
-        asm volatile("" ::"s"(sbase));
+      if (hm == 0ull) continue;
+      // The chunk's entries in groups of four.  take: the next group's lanes
+      // (63 past the last) and its appearance, requested while the group
+      // before it is worked on.
+      uint32_t jn[4];
+      u32x4_t yn;
+      auto take = [&]() {
+        uint32_t jp = 0;
 #pragma unroll
-        for (int k = 0; k < (BF16 ? 10 : 20); ++k) asm volatile("" ::"s"(yw[k]));
+        for (int i = 0; i < 4; ++i) {
+          jn[i] = first_lane(hm);
+          hm = without_lane(hm, jn[i]);
+          jp |= (jn[i] & 63u) << (8 * i + 2);
+        }
+        const uint32_t ge = (uint32_t)__builtin_amdgcn_ds_bpermute((int)__builtin_amdgcn_ubfe(jp, yent, 8),
+                                                                   (int)rid_l) & npad_mask;
+        if (BF16) {
+          const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(app_b, (ge * 5u << 3) + yoff, 0, 0);
+          yn[0] = t[0];
+          yn[1] = t[1];
+        } else {
+          yn = __builtin_amdgcn_raw_buffer_load_b128(app_b, (ge * 5u << 4) + yoff, 0, 0);
+        }
+        asm volatile("" ::: "memory");   // the request stays here
+      };
+      // an entry's record id and geometry, requested one entry ahead into the
+      // other of two register sets (a copy would wait for the load)
+      auto request = [&](uint32_t j, uint32_t& rid, GeomRec& gr) {
+        rid = __builtin_amdgcn_readlane(rid_l, j);
+        gr = *(const GeomRec*)((const char*)geom + (rid << 5));
+        asm volatile("" ::: "memory");
+      };
+      // the geometry has arrived (scalar loads return in any order, so this
+      // waits for all: the next request comes after it)
+      auto arrived = [&](const GeomRec& gr) {
+        asm volatile("" ::"s"(gr.mx), "s"(gr.my), "s"(gr.qa), "s"(gr.qb2), "s"(gr.qc), "s"(gr.o), "s"(gr.z),
+                     "s"(gr.bbox));
+      };
+      auto work = [&](uint32_t j, uint32_t rid, const GeomRec& gr, float gyf, float gyc) {
+        const int k = top - (int)j;
         const uint64_t lm = __builtin_amdgcn_ballot_w64(k <= last);   // lanes this entry can reach
         if (CNT) {
           n_eval += (uint32_t)__popcll(lm);
           ++n_ent;
         }
-        const int bx0 = (int)(gr.bbox & 255u), by0 = (int)((gr.bbox >> 16) & 255u);
-        const float dx = (float)(px - 8 * bx0) - gr.mx;
-        const float dy = (float)(py - 8 * by0) - gr.my;
+        const float dx = (pxb - block_px_bias(gr.bbox & 255u)) - gr.mx;
+        const float dy = (pyb - block_px_bias((gr.bbox >> 16) & 255u)) - gr.my;
         const Eval e = eval_entry(dx, dy, gr.qa, gr.qb2, gr.qc, gr.o, st.cutoff2, st.alpha_max, st.alpha_min);
         // (k <= last) && e.pass, as a mask of single-comparison ballots and
         // back as a lane predicate (no VALU spent on the conversion)
         const uint64_t cmask = lm & __builtin_amdgcn_ballot_w64(e.m2 <= st.cutoff2) &
                                __builtin_amdgcn_ballot_w64(e.alpha >= st.alpha_min);
-        if (cmask == 0ull) continue;
+        if (cmask == 0ull) return;
         const bool con = __builtin_amdgcn_inverse_ballot_w64(cmask);
         if (CNT) {
           n_con += (uint32_t)__popcll(cmask);
           ++n_wr;
         }
-        float y[20];
-        y_from_words<BF16>(yw, y);
-        y[3] = gr.z;
-        float vv[6];
-        {
-          const float rinv = __builtin_amdgcn_rcpf(1.f - e.alpha);
-          const float Tp = Tc * rinv;
-          const float w = e.alpha * Tp;
-          float gy = 0.f;
-          if (kDotGy) {
-            float fs = 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-              fs = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, yw[2 + k]),
-                                                   __builtin_bit_cast(bf16x2_t, sg2[k]), fs, false);
-            gy = gscale[2] * fs;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) gy = __builtin_fmaf(g[c], y[c], gy);
+        // a lane the entry does not reach: alpha 0, so T stays as it is (the
+        // reciprocal of 1 is 1) and its weight is 0
+        const float al = con ? e.alpha : 0.f;
+        const float rinv = __builtin_amdgcn_rcpf(1.f - al);
+        const float Tp = Tc * rinv;
+        const float w = al * Tp;
+        const float gy = kDotGy ? __builtin_fmaf(g[3], gr.z, __builtin_fmaf(gscale[2], gyf, kSignRGB ? gscale[0] * gyc : gyc))
+                                : __builtin_fmaf(g[3], gr.z, gyf);
+        const float dal = Tp * gy - (UPM == UP_EXPLICIT ? sB + gTT : sB) * rinv;   // gT = 0 otherwise
+        sB = con ? __builtin_fmaf(w, gy, sB) : sB;
+        Tc = Tp;
+        // dL/dm2 per pixel is -1/2 u; the slot keeps the moments of u over the
+        // pixel offsets (the factor -1/2 and the conic's entries are per
+        // Gaussian, so they are applied once to the summed moments in the
+        // projection backward), and their zeroth, from which the opacity's
+        // gradient follows (below the clamp alpha is o G)
+        const bool free_al = __builtin_amdgcn_inverse_ballot_w64(cmask & ~__builtin_amdgcn_ballot_w64(e.araw > st.alpha_max));
+        const float u = free_al ? dal * al : 0.f;
+        const lds_ptr row = wl + nb * kWRow;
+        row[0] = w;
+        row[kBatch * kWRow] = u;
+        ridv = (uint32_t)amdgcn_writelane((int)rid, nb, (int)ridv);
+        if (++nb == kBatch) flush();
+      };
+      int left = __builtin_popcountll(hm);
+      uint32_t r0, r1;
+      GeomRec g0, g1;
+      take();
+      request(jn[0], r0, g0);
+      for (;;) {
+        // gy of the group's four entries: entry i in register i
+        f32x4 gf = {0.f, 0.f, 0.f, 0.f}, gc = {0.f, 0.f, 0.f, 0.f};
+        if (kDotGy) {
+          const s16x4_t ya = __builtin_bit_cast(s16x4_t, (u32x2_t){yn[0], yn[1]});
+          gf = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ya, sg[1], gf, 4, 1, 0);
+          gf = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ya, sg[2], gf, 4, 2, 0);
+          gf = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ya, sg[3], gf, 4, 3, 0);
+          gf = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ya, sg[4], gf, 4, 4, 0);
+          if (kSignRGB) {
+            gc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ya, sg[0], gc, 4, 0, 0);
           } else {
-#pragma unroll
-            for (int c = 0; c < 20; ++c) gy = __builtin_fmaf(g[c], y[c], gy);
+            gc = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(yn[0] << 16), g[0], gc, 4, 0, 0);
+            gc = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(yn[0] & 0xffff0000u), g[1], gc, 4, 0, 0);
+            gc = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(yn[1] << 16), g[2], gc, 4, 0, 0);
           }
-          const float dal = Tp * gy - (UPM == UP_EXPLICIT ? sB + gTT : sB) * rinv;   // gT = 0 otherwise
-          const float wc = con ? w : 0.f;
-          sB = con ? __builtin_fmaf(w, gy, sB) : sB;
-          Tc = con ? Tp : Tc;
-          const float dgeo = (con && !(e.araw > st.alpha_max)) ? dal : 0.f;
-          // dL/dm2 per pixel is -1/2 dgeo alpha; the slot keeps the moments
-          // of dgeo alpha over the pixel offsets (the factor -1/2 and the
-          // conic's entries are per Gaussian, so they are applied once to
-          // the summed moments in the projection backward)
-          const float dm2 = dgeo * e.alpha;
-          const float mxd = dm2 * dx, myd = dm2 * dy;
-          vv[0] = mxd;
-          vv[1] = myd;
-          vv[2] = mxd * dx;
-          vv[3] = mxd * dy;
-          vv[4] = myd * dy;
-          vv[5] = dgeo * e.G;
-          // wc = hi + mid + lo exactly: each term keeps the top 8 significant
-          // bits of what is left (truncation), so each is a BF16 value
-          const float whi = __uint_as_float(__float_as_uint(wc) & 0xffff0000u);
-          const float r1 = wc - whi;
-          const float wmid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-          const float wlo = r1 - wmid;
-          wz[nb * kZRow + lane] = (unsigned short)(__float_as_uint(whi) >> 16);
-          wz[(8 + nb) * kZRow + lane] = (unsigned short)(__float_as_uint(wmid) >> 16);
-          wz[(16 + nb) * kZRow + lane] = (unsigned short)(__float_as_uint(wlo) >> 16);
+        } else {
+          float y4[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            y4[i] = __uint_as_float(!BF16 ? yn[i] : (i & 1) ? yn[i >> 1] & 0xffff0000u : yn[i >> 1] << 16);
+#define LGS_GY(Q, I) gf = __builtin_amdgcn_mfma_f32_4x4x1f32(y4[I], g[4 * Q + I], gf, 4, Q, 0);
+#define LGS_GY4(Q) LGS_GY(Q, 0) LGS_GY(Q, 1) LGS_GY(Q, 2) LGS_GY(Q, 3)
+          LGS_GY(0, 0) LGS_GY(0, 1) LGS_GY(0, 2)
+          LGS_GY4(1) LGS_GY4(2) LGS_GY4(3) LGS_GY4(4)
+#undef LGS_GY4
+#undef LGS_GY
         }
-        const uint32_t bb = gr.bbox;
-        const uint32_t bw = ((bb >> 8) & 255u) - (bb & 255u) + 1u;
-        const uint32_t slot = sbase + (by - (uint32_t)by0) * bw + (bx - (uint32_t)bx0);
-        const float s6 = transpose_reduce6(vv, lane);
-        // one lane per value: 0, 8, 16, 32, 40, 48 (24 and 56 repeat 8 and 40)
-        if ((lane & 7) == 0 && (lane & 24) != 24) geo[nb * kGeoStride + red6_index(lane)] = s6;
-        slotv = lane == nb ? slot : slotv;   // lane nb: this entry's slot
-        ++nb;
-        if (nb == 8) flush();
+        const uint32_t j0 = jn[0], j1 = jn[1], j2 = jn[2], j3 = jn[3];
+        take();
+        arrived(g0);
+        request(j1, r1, g1);
+        work(j0, r0, g0, gf[0], gc[0]);
+        if (left == 1) break;
+        arrived(g1);
+        request(j2, r0, g0);
+        work(j1, r1, g1, gf[1], gc[1]);
+        if (left == 2) break;
+        arrived(g0);
+        request(j3, r1, g1);
+        work(j2, r0, g0, gf[2], gc[2]);
+        if (left == 3) break;
+        arrived(g1);
+        request(jn[0], r0, g0);
+        work(j3, r1, g1, gf[3], gc[3]);
+        left -= 4;
+        if (left == 0) break;
       }
     }
     if (nb > 0) flush();
@@ -893,8 +983,6 @@ __global__ void __launch_bounds__(256)
     atomicAdd(&cnt->bwd_written, (unsigned long long)n_wr);
   }
 }
-
-
 
 // Per-Gaussian sum of the backward's partials.  Visible (view, Gaussian) c
 // owns the slot range [slot_off[c], slot_off[c + 1]) (the last one ends at
@@ -1056,7 +1144,7 @@ static void launch_bwd_t(const Settings& st, const ViewDesc* views, const ViewIm
                          Counters* cnt, int waves_per_group, const int32_t* last_idx, const float* T_state,
                          const uint32_t* slot_base, float* partials, uint8_t* mask, hipStream_t s) {
   const int threads = 64 * waves_per_group;
-  const size_t lds = (size_t)waves_per_group * bwd_wave_lds_bytes(UPM);
+  const size_t lds = kBasisBytes + (size_t)waves_per_group * bwd_wave_lds(UPM);
   int dev = 0, cus = 256;
   hipGetDevice(&dev);
   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
