@@ -188,9 +188,6 @@ size_t radix_temp_bytes(int64_t n_max);
 void radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                     const uint32_t* n_dev, int64_t n_max, int begin_bit, int end_bit,
                     void* temp, hipStream_t s, bool* result_in_alt);
-void radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                    const uint32_t* n_dev, int64_t n_max, int begin_bit, int end_bit,
-                    void* temp, hipStream_t s, bool* result_in_alt);
 
 // work queue ordering (blocks by descending tile-list length): each queue's
 // tiles re-sorted by the length of their list (counting sort on coarse
@@ -274,20 +271,33 @@ void launch_decoder(const DecArgs& a, int target_bf16, float* part, int grid, hi
 // side tau_dist) and the geometric criteria
 struct PruneArgs {
   const float *means, *logits, *log_scales;   // [3][n], [n], [3][n]
-  const void* feat;                           // [16][n], FP32 or BF16
-  int32_t feat_bf16, k;                       // k <= prune_k_max()
-  int64_t n, n_valid;                         // Gaussians; those with a grid cell (sorted first)
+  const void* feat;                           // [planes][n], FP32 or BF16
+  int32_t feat_bf16, planes, k;               // planes: 8 or 16; k <= prune_k_max()
+  uint32_t buckets;                           // prune_buckets(n)
+  int64_t n;
   double tau2, inv_cell, tau_sim;             // tau_dist^2, 1 / tau_dist, tau_sim
   double logit_min, log_scale_max;            // log(o / (1 - o)) of min_opacity, log(max_scale)
+  float tau2_above;                           // above any FP32 |p_i - p_j|^2 whose FP64 value is below tau2
+};
+struct PruneCounters {
+  unsigned long long counts[3];   // redundant, geometric, pruned
+  uint32_t n_heavy;               // Gaussians with more than k neighbours within tau_dist
+  uint32_t range_err;             // a finite mean lies outside the grid's range
+};
+struct PruneWork {
+  void* rec;                      // n x prune_rec_bytes
+  float4* pos;                    // n
+  uint32_t *count, *start;        // buckets, buckets + 1
+  uint32_t* list;                 // n
+  uint8_t *geo, *sem;             // n each
+  void* temp;                     // scan_temp_bytes(buckets)
+  PruneCounters* pc;
 };
 int prune_k_max();
-size_t prune_temp_bytes(int64_t n);
-void launch_prune_keys(const PruneArgs& a, uint64_t* keys, uint32_t* vals, uint8_t* geo, uint32_t* range_err,
-                       hipStream_t s);
-void launch_prune_count_valid(const uint64_t* keys, int64_t n, int64_t* n_valid, hipStream_t s);
-void launch_prune_knn(const PruneArgs& a, const uint64_t* keys, const uint32_t* vals, uint8_t* sem, hipStream_t s);
-void launch_prune_final(int64_t n, const uint8_t* sem, const uint8_t* geo, uint8_t* mask,
-                        unsigned long long* counts, hipStream_t s);
+size_t prune_rec_bytes(int bf16);
+uint32_t prune_buckets(int64_t n);
+// the whole pass (n > 0); leaves the mask alone when w.pc->range_err
+void launch_prune(const PruneArgs& a, const PruneWork& w, uint8_t* mask, hipStream_t s);
 
 // feature groups beyond the first: appearance records (RGB 0, the group's
 // features), the geometric partials of a group's backward added to the

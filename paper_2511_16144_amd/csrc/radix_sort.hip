@@ -255,10 +255,4 @@ void radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t
   sort_impl<uint32_t>(keys, vals, keys_alt, vals_alt, n_dev, n_max, begin_bit, end_bit, temp, s, in_alt);
 }
 
-void radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                    const uint32_t* n_dev, int64_t n_max, int begin_bit, int end_bit, void* temp,
-                    hipStream_t s, bool* in_alt) {
-  sort_impl<uint64_t>(keys, vals, keys_alt, vals_alt, n_dev, n_max, begin_bit, end_bit, temp, s, in_alt);
-}
-
 }  // namespace lgs

@@ -59,6 +59,8 @@ struct lgs_context {
   // lgs_decoder_l1 workspace: per-work-group partial sums
   float* dec_part = nullptr;
   int64_t dec_part_cap = 0;
+  // pinned staging of lgs_prune's readback
+  lgs::PruneCounters* prune_host = nullptr;
   // device address of this GPU's copy of the fixed scratch array used by
   // lgs_decoder_l1_noalloc
   float* scratch = nullptr;
@@ -920,6 +922,7 @@ void lgs_context_destroy(lgs_context* ctx) {
   if (ctx->loss_part) hipFree(ctx->loss_part);
   if (ctx->loss_copied) hipEventDestroy(ctx->loss_copied);
   if (ctx->dec_part) hipFree(ctx->dec_part);
+  if (ctx->prune_host) hipHostFree(ctx->prune_host);
   delete ctx;
 }
 
@@ -1267,58 +1270,50 @@ lgs_status lgs_prune(lgs_context* ctx, const lgs_gaussians* g, const lgs_prune_p
   auto release = [&]() {
     for (void* p : held) pool_free(ctx, p, SharedEvent());   // the call has synchronised
   };
-  uint64_t* keys = (uint64_t*)take(8 * n);
-  uint64_t* keys_b = (uint64_t*)take(8 * n);
-  uint32_t* vals = (uint32_t*)take(4 * n);
-  uint32_t* vals_b = (uint32_t*)take(4 * n);
-  uint8_t* geo = (uint8_t*)take(n);
-  uint8_t* sem = (uint8_t*)take(n);
-  void* temp = take(prune_temp_bytes(n));
-  // small device words: range flag (u32), pad, valid count (i64), counts (3 x u64)
-  unsigned char* misc = (unsigned char*)take(64);
-  if (!keys || !keys_b || !vals || !vals_b || !geo || !sem || !temp || !misc) {
+  const int bf16 = g->appearance_dtype == LGS_BF16;
+  const uint32_t buckets = prune_buckets(n);
+  PruneWork w;
+  w.rec = take(prune_rec_bytes(bf16) * n);
+  w.pos = (float4*)take(sizeof(float4) * n);
+  w.count = (uint32_t*)take(4 * (size_t)buckets);
+  w.start = (uint32_t*)take(4 * ((size_t)buckets + 1));
+  w.list = (uint32_t*)take(4 * n);
+  w.geo = (uint8_t*)take(n);
+  w.sem = (uint8_t*)take(n);
+  w.temp = take(scan_temp_bytes(buckets));
+  w.pc = (PruneCounters*)take(sizeof(PruneCounters));
+  if (held.size() != 9) {
     release();
     return fail(ctx, LGS_ERR_HIP, "device allocation failed (pruning)");
   }
-  uint32_t* range_err = (uint32_t*)misc;
-  int64_t* n_valid_d = (int64_t*)(misc + 8);
-  unsigned long long* counts_d = (unsigned long long*)(misc + 16);
   PruneArgs a;
   a.means = g->means; a.logits = g->opacity_logits; a.log_scales = g->log_scales; a.feat = g->feat;
-  a.feat_bf16 = g->appearance_dtype == LGS_BF16;
+  a.feat_bf16 = bf16;
+  a.planes = g->feat_dim == 8 ? 8 : 16;
   a.k = prm->k;
+  a.buckets = buckets;
   a.n = n;
-  a.n_valid = 0;
   const double tau = (double)prm->tau_dist;
   a.tau2 = tau * tau;
+  // FP32: the differences and the three squares' sum round by less than 2^-20
+  // of the result, or by a few of the least denormals
+  a.tau2_above = a.tau2 < 1e38 ? (float)(a.tau2 * (1.0 + 1.0 / (1 << 20)) + 1e-37) : INFINITY;
   a.inv_cell = 1.0 / tau;
   a.tau_sim = (double)prm->tau_sim;
   a.logit_min = log((double)prm->min_opacity / (1.0 - (double)prm->min_opacity));
   a.log_scale_max = log((double)prm->max_scale);
   auto run = [&]() -> lgs_status {
-    HIP_TRY(ctx, hipMemsetAsync(misc, 0, 64, stream));
-    HIP_TRY(ctx, hipMemsetAsync(sem, 0, n, stream));
-    launch_prune_keys(a, keys, vals, geo, range_err, stream);
-    bool alt = false;
-    radix_sort_u64(keys, vals, keys_b, vals_b, nullptr, n, 0, 64, temp, stream, &alt);
-    const uint64_t* sk = alt ? keys_b : keys;
-    const uint32_t* sv = alt ? vals_b : vals;
-    launch_prune_count_valid(sk, n, n_valid_d, stream);
+    if (!ctx->prune_host)
+      HIP_TRY(ctx, hipHostMalloc((void**)&ctx->prune_host, sizeof(PruneCounters), hipHostMallocDefault));
+    launch_prune(a, w, mask, stream);
     HIP_TRY(ctx, hipGetLastError());
-    int64_t hv[2] = {0, 0};
-    HIP_TRY(ctx, hipMemcpyAsync(hv, misc, 16, hipMemcpyDeviceToHost, stream));
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->prune_host, w.pc, sizeof(PruneCounters), hipMemcpyDeviceToHost, stream));
     HIP_TRY(ctx, hipStreamSynchronize(stream));
-    if ((uint32_t)hv[0] != 0u)
+    const PruneCounters hc = *ctx->prune_host;
+    if (hc.range_err)
       return fail(ctx, LGS_ERR_UNSUPPORTED, "a mean lies more than 2^20 cells of tau_dist from the origin");
-    a.n_valid = hv[1];
-    launch_prune_knn(a, sk, sv, sem, stream);
-    launch_prune_final(n, sem, geo, mask, counts_d, stream);
-    HIP_TRY(ctx, hipGetLastError());
-    unsigned long long hc[3] = {0, 0, 0};
-    HIP_TRY(ctx, hipMemcpyAsync(hc, counts_d, sizeof hc, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(ctx, hipStreamSynchronize(stream));
     if (counts)
-      for (int i = 0; i < 3; ++i) counts[i] = (int64_t)hc[i];
+      for (int i = 0; i < 3; ++i) counts[i] = (int64_t)hc.counts[i];
     return LGS_OK;
   };
   rc = run();
