@@ -160,6 +160,21 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(const uint32_t* __re
     }
     run += v[k];
   }
+  if (cp.big) {   // one atomic per wave that holds such items
+    uint32_t nbig = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) nbig += v[k] > cp.big_min ? 1u : 0u;
+    if (__builtin_amdgcn_ballot_w64(nbig != 0u) != 0ull) {
+      const int lane = threadIdx.x & 63;
+      const uint32_t inc = wave_incl_scan(nbig, lane);
+      uint32_t at = 0;
+      if (lane == 63) at = atomicAdd(cp.n_big, inc);
+      at = (uint32_t)__shfl((int)at, 63) + inc - nbig;
+#pragma unroll
+      for (int k = 0; k < kScanItems; ++k)
+        if (v[k] > cp.big_min) cp.big[at++] = (uint32_t)item(k);
+    }
+  }
   if (base + kScanTile >= n && threadIdx.x == 0) *total = boff + btot;   // the last block
 }
 

@@ -13,6 +13,7 @@ constexpr int kMaxSide = 2048;          // 8-bit block coordinates in records
 constexpr int kChannels = 20;           // RGB 3 + depth 1 + feature 16
 constexpr int kPartials = 26;           // y 20, then the geometric sums Sx, Sy, Sxx, S0, Sxy, Syy
 constexpr int kPartGeo = 20;            // the first of the geometric sums
+constexpr uint32_t kLongSlots = 512;   // a longer slot range is summed by a whole work-group
 constexpr int kSlotFloats = 32;         // a backward slot record: the kPartials floats padded to 128 bytes
 
 // Per-view constants, shared by every stage (device array of n_views).
@@ -104,7 +105,8 @@ struct __attribute__((aligned(128))) Counters {
   uint32_t overflow;    // set when P exceeds the pair capacity
   uint32_t n_pairs_eff; // n_pairs, or 0 after an overflow
   uint32_t n_slots_eff; // n_slots, or 0 after an overflow
-  uint32_t pad0, pad1;
+  uint32_t n_long;      // visible ids with more than kLongSlots slots
+  uint32_t pad1;
   // work actually done by the compositing kernels (one atomic per wave):
   // (pixel, entry) evaluations and contributions, the list entries a wave
   // visited (its records were loaded), forward and backward, and the
@@ -165,6 +167,10 @@ struct Compact {
   uint32_t* ent = nullptr;
   uint32_t* ent_copy = nullptr;
   uint32_t* keys = nullptr;
+  // value and gather scans: the items i whose value exceeds big_min, in any order
+  uint32_t* big = nullptr;
+  uint32_t* n_big = nullptr;   // their number (added to)
+  uint32_t big_min = 0;
 };
 void launch_scan(int mode, const uint32_t* src, const uint32_t* idx, uint32_t* out,
                  uint32_t* total, const uint32_t* n_dev, int64_t n_max,
@@ -311,7 +317,7 @@ void launch_group_feat_grad(int n_views, int64_t n, uint32_t npad_shift, const C
 
 // gradient reduction and projection backward
 void launch_seg_reduce(const uint32_t* slot_off, const float* partials, uint8_t* mask,
-                       const Counters* cnt, int64_t n_max, float* grad2d, hipStream_t s);
+                       const uint32_t* long_ids, const Counters* cnt, int64_t n_max, float* grad2d, hipStream_t s);
 // workspace of launch_project_bwd for at most n_rid visible (view, Gaussian)
 size_t project_bwd_temp_bytes(int64_t n_rid, int n_views);
 // the projection backward: per visible (view, Gaussian) c the view's chain

@@ -995,12 +995,31 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
 // half walks them lowest first in batches (2 kSegBatch while that many are
 // left, else kSegBatch), each batch's loads requested before the first is
 // added.  A fixed order, so results are deterministic.
+//
+// An id with more than kLongSlots slots (a near Gaussian that covers much of
+// the frame: up to 12750 of them at 1200 x 680) would keep one half busy long
+// after the others have run out.  A work-group takes it, in windows of 64 slots
+// dealt to its four waves in turn: a wave adds its window's records to the sum
+// that it finds in LDS, leaves the sum there for the next wave, and requests
+// its next window's records, which have the three other waves' turns to
+// arrive.  The order of the additions, and so the result, is that of one half.
+// These ids (listed by the scan of the block counts) come first.
+// 1 M Gaussians, 1200 x 680, 15.3 M slots of which 2.56 M are written (0.33 GB,
+// 64 us at the rate of a large copy): 201 -> 115 us; 300k at 640 x 480, 0.68 M
+// written: 36 -> 29; eight views of 640 x 480, 25 slots to an id (1.0 GB,
+// 200 us, which the records' lines bound): 260 -> 257.  The line at 512: 256
+// gives 139 and 26 us for the first two, 1024 gives 118 and 32.  (Adding an
+// eighth of the range per half and then the eight sums is as fast, but another
+// order of the additions moves gradients with much cancellation by 1e-3.)
 constexpr int kSegBatch = 8;
-__global__ void __launch_bounds__(256) k_seg_reduce(const uint32_t* __restrict__ slot_off,
+constexpr int kSegWaves = 4;
+__global__ void __launch_bounds__(256, 8) k_seg_reduce(const uint32_t* __restrict__ slot_off,
                                                     const float* __restrict__ partials,
                                                     uint8_t* __restrict__ mask,
+                                                    const uint32_t* __restrict__ long_ids,
                                                     const Counters* __restrict__ cnt,
                                                     float* __restrict__ grad2d) {
+  __shared__ float sum[32];
   const int lane = threadIdx.x & 63;
   if (cnt->overflow) return;
   const uint32_t nv = cnt->n_visible, ns = cnt->n_slots;
@@ -1014,6 +1033,70 @@ __global__ void __launch_bounds__(256) k_seg_reduce(const uint32_t* __restrict__
   // their words are combined only when the pair comes up, so nothing waits
   // on them early.
   if (nv == 0u) return;
+  const uint32_t n_long = cnt->n_long;
+  for (uint32_t e = blockIdx.x; e < n_long; e += gridDim.x) {
+    const uint32_t c = long_ids[e];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t beg = slot_off[c], end = c + 1u < nv ? slot_off[c + 1u] : ns;
+    const uint32_t n_win = (end - beg + 63u) / 64u;
+    auto byte_of = [&](uint32_t win) { return mask[min(beg + 64u * win + (uint32_t)lane, end - 1u)]; };
+    // record 2 j of the window in the lower half of t[j], 2 j + 1 in the upper
+    constexpr int kPairs = 32;
+    float t[kPairs];
+    uint32_t n_rec = 0u;
+    auto request = [&](uint32_t win, uint32_t m) {
+      const uint32_t sl = beg + 64u * win + (uint32_t)lane;
+      const bool written = sl < end && m != 0u;
+      if (written) mask[sl] = 0;   // cleared for the next backward over these slots
+      uint64_t left = __builtin_amdgcn_ballot_w64(written);
+      n_rec = (uint32_t)__builtin_popcountll(left);
+      const float* rec = partials + (size_t)(beg + 64u * win) * kSlotFloats + hl;
+#pragma unroll
+      for (int q = 0; q < kPairs; q += 8)
+        if (n_rec > 2u * q) {
+#pragma unroll
+          for (int j = q; j < q + 8; ++j) {
+            // past the last record: the window's first slot, dropped below
+            const uint32_t i0 = left ? (uint32_t)__builtin_ctzll(left) : 0u;
+            left &= left - 1ull;
+            const uint32_t i1 = left ? (uint32_t)__builtin_ctzll(left) : 0u;
+            left &= left - 1ull;
+            t[j] = rec[(half ? i1 : i0) * kSlotFloats];
+          }
+        }
+    };
+    uint32_t m = byte_of(wave);
+    const uint32_t m1 = byte_of(wave + kSegWaves);
+    request(wave, m);
+    m = m1;
+    for (uint32_t win = 0; win < n_win; ++win) {
+      if (win % kSegWaves == wave) {
+        float acc = win ? sum[hl] : 0.f;
+#pragma unroll
+        for (int q = 0; q < kPairs; q += 8)
+          if (n_rec > 2u * q) {
+#pragma unroll
+            for (int j = q; j < q + 8; ++j) {
+              // (the upper half's value in the lower half; the upper half's own sum is not used)
+              const uint32_t x = __float_as_uint(t[j]);
+              const float up = __uint_as_float(__builtin_amdgcn_permlane32_swap(x, x, false, false)[1]);
+              acc += 2u * j < n_rec ? t[j] : 0.f;
+              acc += 2u * j + 1u < n_rec ? up : 0.f;
+            }
+          }
+        if (half == 0u) sum[hl] = acc;
+        if (win + 1u == n_win && lane < kPartials) grad2d[(size_t)c * kPartials + lane] = acc;
+      }
+      // the sum has to be there, the requested records not: no wait for them
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (win % kSegWaves == wave) {
+        request(win + kSegWaves, m);
+        m = byte_of(win + 2 * kSegWaves);
+      }
+    }
+  }
   const uint32_t step = 2 * n_waves;
   auto req = [&](uint32_t cc, uint32_t& b, uint32_t& e) {   // raw words of pair member cc
     const uint32_t ci = min(cc, nv - 1u);
@@ -1044,16 +1127,21 @@ __global__ void __launch_bounds__(256) k_seg_reduce(const uint32_t* __restrict__
     // the requests above stay ahead of the summing below (no memory operation
     // moves across this point)
     asm volatile("" ::: "memory");
-    const uint32_t base = b0, len = l0;
+    const bool done = l0 > kLongSlots;   // (summed above)
+    const uint32_t base = b0, len = done ? 0u : l0;
     const uint32_t maxlen = __builtin_amdgcn_readfirstlane(max(len, (uint32_t)__shfl_xor((int)len, 32, 64)));
     // the slot a lane with nothing to add reads: the half's last one read
     // (already in cache), slot 0 before the first (read by every wave)
     uint32_t last = 0u;
     float acc = 0.f;
+    uint32_t mraw = mraw0;
     for (uint32_t o = 0; o < maxlen; o += 32) {
       const uint32_t sl = base + o + hl;
-      // the window's first byte per lane is the one requested a pair ago
-      const bool written = o == 0u ? (hl < len && mraw0 != 0u) : (o + hl < len && mask[sl] != 0);
+      // the first window's bytes were requested a pair ago, the others' a
+      // window ago
+      const bool written = o + hl < len && mraw != 0u;
+      mraw = mask[len > 0u ? base + min(o + 32u + hl, len - 1u) : 0u];   // the next window's
+      asm volatile("" ::: "memory");
       if (written) mask[sl] = 0;   // cleared for the next backward over these slots
       const uint64_t bal = __builtin_amdgcn_ballot_w64(written);
       const uint32_t lo = (uint32_t)bal, hi = (uint32_t)(bal >> 32);
@@ -1082,7 +1170,7 @@ __global__ void __launch_bounds__(256) k_seg_reduce(const uint32_t* __restrict__
       for (; k + 2 * kSegBatch <= nmax; k += 2 * kSegBatch) batch(std::integral_constant<int, 2 * kSegBatch>());
       for (; k < nmax; k += kSegBatch) batch(std::integral_constant<int, kSegBatch>());
     }
-    if (c < nv && hl < (uint32_t)kPartials) grad2d[(size_t)c * kPartials + hl] = acc;
+    if (c < nv && !done && hl < (uint32_t)kPartials) grad2d[(size_t)c * kPartials + hl] = acc;
     b0 = b1;
     l0 = l1;
     mraw0 = mraw1;
@@ -1187,7 +1275,7 @@ void launch_raster_bwd(int up_mode, const Settings& st, const ViewDesc* views, c
 }
 
 void launch_seg_reduce(const uint32_t* slot_off, const float* partials, uint8_t* mask,
-                       const Counters* cnt, int64_t n_max, float* grad2d, hipStream_t s) {
+                       const uint32_t* long_ids, const Counters* cnt, int64_t n_max, float* grad2d, hipStream_t s) {
   if (n_max <= 0) return;
   int dev = 0, cus = 256, occ = 1;
   hipGetDevice(&dev);
@@ -1196,7 +1284,8 @@ void launch_seg_reduce(const uint32_t* slot_off, const float* partials, uint8_t*
   int64_t grid = (int64_t)cus * (occ > 0 ? occ : 1);
   const int64_t need = (n_max + 7) / 8;   // two visible ids per wave
   if (grid > need) grid = need;
-  hipLaunchKernelGGL(k_seg_reduce, dim3((unsigned)grid), dim3(256), 0, s, slot_off, partials, mask, cnt, grad2d);
+  hipLaunchKernelGGL(k_seg_reduce, dim3((unsigned)grid), dim3(256), 0, s, slot_off, partials, mask, long_ids, cnt,
+                     grad2d);
 }
 
 }  // namespace lgs

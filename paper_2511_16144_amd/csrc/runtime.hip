@@ -432,7 +432,7 @@ struct Work {
   GeomRec* geom = nullptr;
   uint32_t *cnt_t = nullptr, *cnt_b = nullptr, *cidx = nullptr, *slot_base = nullptr;
   uint32_t *ent = nullptr, *ent_a = nullptr, *ent_b = nullptr, *srid = nullptr;
-  uint32_t *off_t = nullptr, *slot_off = nullptr;
+  uint32_t *off_t = nullptr, *slot_off = nullptr, *long_ids = nullptr;
   uint32_t *dkey = nullptr, *dk0 = nullptr, *dk1 = nullptr;
   void* app = nullptr;
   Counters* counters = nullptr;
@@ -572,6 +572,7 @@ lgs_status w_alloc_front(Work* W) {
   W->ent_b = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->off_t = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->slot_off = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
+  W->long_ids = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->dkey = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->dk0 = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->dk1 = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
@@ -699,8 +700,12 @@ void enqueue_front(Work* W, const lgs_gaussians* g, hipStream_t s) {
   launch_scan(SCAN_GATHER, W->cnt_t, W->srid, W->off_t, &W->counters->n_pairs, &W->counters->n_visible, n_rid,
               W->scan_tmp, s);
   // slot offsets in visible order, and the same as each record's slot base
+  Compact lc;
+  lc.big = W->long_ids;
+  lc.n_big = &W->counters->n_long;
+  lc.big_min = kLongSlots;
   launch_scan(SCAN_GATHER, W->cnt_b, W->ent, W->slot_off, &W->counters->n_slots, &W->counters->n_visible, n_rid,
-              W->scan_tmp, s, W->slot_base);
+              W->scan_tmp, s, W->slot_base, lc);
   const size_t esz = W->app_bf16 ? 2 : 4;
   for (int gi = 1; gi < W->G; ++gi)
     launch_pack_app_group((const char*)g->feat + esz * (size_t)kFeatGroup * gi * (size_t)W->n,
@@ -773,7 +778,7 @@ void enqueue_backward_raster(Work* W, const lgs_grads* gr, int mode, hipStream_t
   if (W->G > 1) w_mark(W, 5, s);
   for (int gi = 1; gi < W->G; ++gi) {
     launch_group_bwd(W, gi, mode, gi == 1, s);
-    launch_seg_reduce(W->slot_off, W->partials, W->mask, W->counters, W->n_rid, W->grad2d_g, s);
+    launch_seg_reduce(W->slot_off, W->partials, W->mask, W->long_ids, W->counters, W->n_rid, W->grad2d_g, s);
     launch_group_geo_acc(W->grad2d_g, W->counters, W->n_rid, W->geo_acc, gi == 1, s);
     launch_group_feat_grad(V, W->n, (uint32_t)W->npad_shift, W->counters, W->cnt_t, W->cidx, W->grad2d_g,
                            group_nfeat(W->D, gi), gr->feat + (size_t)kFeatGroup * gi * (size_t)W->n, s);
@@ -785,7 +790,7 @@ void enqueue_backward_raster(Work* W, const lgs_grads* gr, int mode, hipStream_t
 void enqueue_backward_reduce(Work* W, const lgs_gaussians* g, const lgs_grads* gr, hipStream_t s) {
   const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D, 0);
   const int V = (int)W->plan.views.size();
-  launch_seg_reduce(W->slot_off, W->partials, W->mask, W->counters, W->n_rid, W->grad2d, s);
+  launch_seg_reduce(W->slot_off, W->partials, W->mask, W->long_ids, W->counters, W->n_rid, W->grad2d, s);
   if (W->G > 1) launch_group_geo_add(W->grad2d, W->counters, W->n_rid, W->geo_acc, s);
   launch_project_bwd(ds, W->d_views, V, g->means, g->log_scales, g->quats, g->opacity_logits, W->n,
                      W->npad_shift, W->n_rid, W->counters, W->cnt_t, W->cidx, W->ent, W->grad2d, gr->means,
