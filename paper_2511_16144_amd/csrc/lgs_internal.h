@@ -189,10 +189,15 @@ void launch_tile_ranges(const uint32_t* keys, const Counters* cnt, int64_t grid_
 // the step's overflow flag and effective counts; also zeroes zero[0 .. n_zero)
 void launch_set_overflow(Counters* cnt, uint64_t cap_pairs, uint64_t cap_slots, uint32_t* zero, int64_t n_zero,
                          hipStream_t s);
-// radix sort (LSD, 8-bit digits, stable)
-size_t radix_temp_bytes(int64_t n_max);
+// Stable LSD radix sort.  n_max bounds the count (read from *n_dev when
+// n_dev != nullptr); up to small_max it is sorted with the fewest launches,
+// which pays while the count itself stays below some 10^5: kSmallPairs where
+// n_max is the count or a capacity near it, kSmallIds where it is all ids of
+// which the visible ones, commonly a tenth, are sorted.
+constexpr int64_t kSmallPairs = 1ll << 17, kSmallIds = 1ll << 19;
+size_t radix_temp_bytes(int64_t n_max, int64_t small_max);
 void radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                    const uint32_t* n_dev, int64_t n_max, int begin_bit, int end_bit,
+                    const uint32_t* n_dev, int64_t n_max, int64_t small_max, int begin_bit, int end_bit,
                     void* temp, hipStream_t s, bool* result_in_alt);
 
 // work queue ordering (blocks by descending tile-list length): each queue's

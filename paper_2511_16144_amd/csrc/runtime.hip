@@ -581,7 +581,7 @@ lgs_status w_alloc_front(Work* W) {
   W->last_idx = (int32_t*)w_alloc(W, 4 * npix, ok);
   W->T_state = (float*)w_alloc(W, 4 * npix, ok);
   W->scan_tmp = w_alloc(W, scan_temp_bytes(n_rid), ok);
-  W->radix_small = w_alloc(W, radix_temp_bytes(n_rid), ok);
+  W->radix_small = w_alloc(W, radix_temp_bytes(n_rid, kSmallIds), ok);
   W->ranges = (uint2*)w_alloc(W, 8 * std::max<int64_t>(W->plan.n_tiles, 1), ok);
   const int64_t ni = std::max<int64_t>(W->plan.n_items, 1);
   W->ii_a = (uint32_t*)w_alloc(W, 4 * ni, ok);
@@ -599,7 +599,7 @@ lgs_status w_alloc_pairs(Work* W, int64_t cap_pairs, int64_t cap_slots) {
   W->v0 = (uint32_t*)w_alloc(W, 4 * pa, ok);
   W->k1 = (uint32_t*)w_alloc(W, 4 * pa, ok);
   W->v1 = (uint32_t*)w_alloc(W, 4 * pa, ok);
-  W->radix_big = w_alloc(W, radix_temp_bytes(pa), ok);
+  W->radix_big = w_alloc(W, radix_temp_bytes(pa, kSmallPairs), ok);
   if (!ok) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (pairs)");
   return LGS_OK;
 }
@@ -694,8 +694,8 @@ void enqueue_front(Work* W, const lgs_gaussians* g, hipStream_t s) {
   launch_scan(SCAN_FLAG_NONZERO, W->cnt_t, nullptr, W->cidx, &W->counters->n_visible, nullptr, n_rid,
               W->scan_tmp, s, nullptr, cp);
   bool alt = false;
-  radix_sort_u32(W->dk0, W->ent_a, W->dk1, W->ent_b, &W->counters->n_visible, n_rid, 0, 32, W->radix_small, s,
-                 &alt);
+  radix_sort_u32(W->dk0, W->ent_a, W->dk1, W->ent_b, &W->counters->n_visible, n_rid, kSmallIds, 0, 32,
+                 W->radix_small, s, &alt);
   W->srid = alt ? W->ent_b : W->ent_a;
   launch_scan(SCAN_GATHER, W->cnt_t, W->srid, W->off_t, &W->counters->n_pairs, &W->counters->n_visible, n_rid,
               W->scan_tmp, s);
@@ -721,8 +721,8 @@ void enqueue_pairs(Work* W, hipStream_t s) {
               P.tile_shift, W->k0, W->v0, s);
   const int tile_bits = std::max<int>(1, (int)ceil_log2((uint64_t)P.n_tiles));
   bool alt = false;
-  radix_sort_u32(W->k0, W->v0, W->k1, W->v1, &W->counters->n_pairs_eff, std::max<int64_t>(W->cap_pairs, 1), 0,
-                 tile_bits, W->radix_big, s, &alt);
+  radix_sort_u32(W->k0, W->v0, W->k1, W->v1, &W->counters->n_pairs_eff, std::max<int64_t>(W->cap_pairs, 1),
+                 kSmallPairs, 0, tile_bits, W->radix_big, s, &alt);
   W->pkeys = alt ? W->k1 : W->k0;
   W->pvals = alt ? W->v1 : W->v0;
   launch_tile_ranges(W->pkeys, W->counters, W->cap_pairs, W->ranges, s);
