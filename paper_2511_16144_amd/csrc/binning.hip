@@ -52,12 +52,22 @@ __device__ __forceinline__ int64_t count_of(const uint32_t* n_dev, int64_t n_max
 // any (unconditional loads at indices clamped to the last item, validity
 // applied afterwards): a load under a bounds test that is used at once
 // costs one memory round trip per item.
+//
+// A launch takes two scans of the same bound (blockIdx.y): the step's two
+// gather scans share their two launches (a launch of any size takes some 4.5 us
+// of a busy queue: 21 -> 15 us for 31k visible of 2^19 ids).
+struct ScanArgs {
+  const uint32_t *src, *idx;
+  const uint32_t* n_dev;
+  uint32_t *out, *total, *bsum, *out_at_idx;
+  Compact cp;
+};
+
 template <int MODE>
-__global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const uint32_t* __restrict__ src,
-                                                              const uint32_t* __restrict__ idx,
-                                                              const uint32_t* n_dev, int64_t n_max,
-                                                              uint32_t* __restrict__ bsum,
-                                                              uint32_t* __restrict__ stash) {
+__global__ void __launch_bounds__(kScanThreads) k_scan_reduce(ScanArgs first, ScanArgs second, int64_t n_max) {
+  const ScanArgs& A = blockIdx.y ? second : first;
+  const uint32_t *__restrict__ src = A.src, *__restrict__ idx = A.idx, *n_dev = A.n_dev;
+  uint32_t *__restrict__ bsum = A.bsum, *__restrict__ stash = A.out;
   __shared__ uint32_t sh[4];
   const int64_t n = count_of(n_dev, n_max);
   const int64_t base = (int64_t)blockIdx.x * kScanTile;
@@ -94,12 +104,11 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const uint32_t* __
 // one work-group scans the block sums in place (exclusive) and writes total
 
 template <int MODE>
-__global__ void __launch_bounds__(kScanThreads) k_scan_down(const uint32_t* __restrict__ src,
-                                                            const uint32_t* __restrict__ idx,
-                                                            const uint32_t* n_dev, int64_t n_max,
-                                                            const uint32_t* __restrict__ bsum,
-                                                            uint32_t* __restrict__ out, uint32_t* __restrict__ total,
-                                                            uint32_t* __restrict__ out_at_idx, Compact cp) {
+__global__ void __launch_bounds__(kScanThreads) k_scan_down(ScanArgs first, ScanArgs second, int64_t n_max) {
+  const ScanArgs& A = blockIdx.y ? second : first;
+  const uint32_t *__restrict__ src = A.src, *__restrict__ idx = A.idx, *n_dev = A.n_dev, *__restrict__ bsum = A.bsum;
+  uint32_t *__restrict__ out = A.out, *__restrict__ total = A.total, *__restrict__ out_at_idx = A.out_at_idx;
+  const Compact& cp = A.cp;
   __shared__ uint32_t sh[4];
   const int64_t n = count_of(n_dev, n_max);
   const int64_t base = (int64_t)blockIdx.x * kScanTile;
@@ -212,16 +221,26 @@ __device__ __forceinline__ int64_t wave_upper_bound_u32(const uint32_t* a, int64
   return lo;
 }
 
+// Also the step's overflow flag and effective counts (block 0), and a range of
+// words zeroed for the stages that follow (nothing here reads any of them).
 __global__ void __launch_bounds__(kEmitThreads) k_emit(
     const GeomRec* __restrict__ geom, const ViewDesc* __restrict__ views,
     const uint32_t* __restrict__ srid, const uint32_t* __restrict__ off_t,
-    const Counters* __restrict__ cnt, int64_t cap_pairs, int npad_shift, int tile_shift,
-    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    Counters* __restrict__ cnt, int64_t cap_pairs, int64_t cap_slots, int npad_shift, int tile_shift,
+    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, uint32_t* __restrict__ zero, int64_t n_zero) {
   __shared__ uint32_t s_off[kEmitTile + 2];
   __shared__ uint32_t s_rid[kEmitTile + 2];
   __shared__ int64_t s_j[2];
   const int64_t M = cnt->n_visible;
   const int64_t P = cnt->n_pairs;
+  for (int64_t i = (int64_t)blockIdx.x * kEmitThreads + threadIdx.x; i < n_zero; i += (int64_t)gridDim.x * kEmitThreads)
+    zero[i] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const bool ov = P > cap_pairs || (int64_t)cnt->n_slots > cap_slots;
+    cnt->overflow = ov ? 1u : 0u;
+    cnt->n_pairs_eff = ov ? 0u : cnt->n_pairs;
+    cnt->n_slots_eff = ov ? 0u : cnt->n_slots;
+  }
   if (P > cap_pairs) return;                 // overflow: nothing valid is written
   const int64_t p0 = (int64_t)blockIdx.x * kEmitTile;
   if (p0 >= P) return;
@@ -266,24 +285,10 @@ __global__ void __launch_bounds__(256) k_fill_u32(uint32_t* __restrict__ p, uint
   if (i < n) p[i] = v;
 }
 
-// two ranges of words zeroed by one launch
-__global__ void __launch_bounds__(256) k_zero2_u32(uint32_t* __restrict__ p, int64_t np, uint32_t* __restrict__ q,
-                                                   int64_t nq) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < np) p[i] = 0u;
-  if (i < nq) q[i] = 0u;
-}
-
-__global__ void __launch_bounds__(256) k_fill_u8(uint8_t* __restrict__ p, uint8_t v,
-                                                 const uint32_t* n_dev, int64_t n_max) {
-  const int64_t n = count_of(n_dev, n_max);
-  const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i4 + 3 < n) {
-    const uint32_t w = (uint32_t)v * 0x01010101u;
-    *(uint32_t*)(p + i4) = w;           // p is 4-byte aligned
-  } else {
-    for (int64_t i = i4; i < n; ++i) p[i] = v;
-  }
+__global__ void __launch_bounds__(256) k_zero(ZeroRanges r) {
+#pragma unroll
+  for (int k = 0; k < ZeroRanges::kMax; ++k)
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < r.n[k]; i += (int64_t)gridDim.x * 256) r.p[k][i] = 0u;
 }
 
 __global__ void __launch_bounds__(256) k_tile_ranges(const uint32_t* __restrict__ keys,
@@ -295,19 +300,6 @@ __global__ void __launch_bounds__(256) k_tile_ranges(const uint32_t* __restrict_
   const uint32_t k = keys[i];
   if (i == 0 || keys[i - 1] != k) ranges[k].x = (uint32_t)i;
   if (i == P - 1 || keys[i + 1] != k) ranges[k].y = (uint32_t)(i + 1);
-}
-
-// The overflow flag and effective counts of the step, and (every thread) a
-// range of words zeroed for the stages that follow.
-__global__ void __launch_bounds__(256) k_set_overflow(Counters* cnt, uint64_t cap_pairs, uint64_t cap_slots,
-                                                      uint32_t* __restrict__ zero, int64_t n_zero) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_zero; i += (int64_t)gridDim.x * 256) zero[i] = 0u;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const bool ov = (uint64_t)cnt->n_pairs > cap_pairs || (uint64_t)cnt->n_slots > cap_slots;
-    cnt->overflow = ov ? 1u : 0u;
-    cnt->n_pairs_eff = ov ? 0u : cnt->n_pairs;
-    cnt->n_slots_eff = ov ? 0u : cnt->n_slots;
-  }
 }
 
 // Work items grouped by queue and, inside a queue, by descending list length
@@ -376,40 +368,40 @@ __global__ void __launch_bounds__(kOrderThreads) k_order_items(const uint2* __re
 
 size_t scan_temp_bytes(int64_t n) {
   const int64_t nb = (n + kScanTile - 1) / kScanTile;
-  return (size_t)(nb > 0 ? nb : 1) * sizeof(uint32_t);
+  return (size_t)(nb > 0 ? nb : 1) * 2 * sizeof(uint32_t);   // (two scans' block sums)
 }
 
 template <int MODE>
-static void launch_scan_t(const uint32_t* src, const uint32_t* idx, uint32_t* out, uint32_t* total,
-                   const uint32_t* n_dev, int64_t n_max, void* temp, hipStream_t s, uint32_t* out_at_idx,
-                   Compact cp) {
+static void launch_scan_t(const ScanArgs& a, const ScanArgs& b, unsigned count, int64_t n_max, hipStream_t s) {
   const int64_t nb = (n_max + kScanTile - 1) / kScanTile;
-  uint32_t* bsum = (uint32_t*)temp;
   if (nb > 0)
-    hipLaunchKernelGGL(k_scan_reduce<MODE>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, src, idx, n_dev, n_max,
-                       bsum, out);
-  hipLaunchKernelGGL(k_scan_down<MODE>, dim3((unsigned)(nb > 0 ? nb : 1)), dim3(kScanThreads), 0, s, src, idx,
-                     n_dev, n_max, (const uint32_t*)bsum, out, total, out_at_idx, cp);
+    hipLaunchKernelGGL(k_scan_reduce<MODE>, dim3((unsigned)nb, count), dim3(kScanThreads), 0, s, a, b, n_max);
+  hipLaunchKernelGGL(k_scan_down<MODE>, dim3((unsigned)(nb > 0 ? nb : 1), count), dim3(kScanThreads), 0, s, a, b,
+                     n_max);
 }
 
-void launch_scan(int mode, const uint32_t* src, const uint32_t* idx, uint32_t* out, uint32_t* total,
-                 const uint32_t* n_dev, int64_t n_max, void* temp, hipStream_t s, uint32_t* out_at_idx,
+void launch_scan(int mode, const uint32_t* src, uint32_t* out, uint32_t* total, int64_t n, void* temp, hipStream_t s,
                  Compact cp) {
-  if (mode == SCAN_FLAG_NONZERO)
-    launch_scan_t<SCAN_FLAG_NONZERO>(src, idx, out, total, n_dev, n_max, temp, s, out_at_idx, cp);
-  else if (mode == SCAN_VALUE)
-    launch_scan_t<SCAN_VALUE>(src, idx, out, total, n_dev, n_max, temp, s, out_at_idx, cp);
-  else
-    launch_scan_t<SCAN_GATHER>(src, idx, out, total, n_dev, n_max, temp, s, out_at_idx, cp);
+  const ScanArgs a{src, nullptr, nullptr, out, total, (uint32_t*)temp, nullptr, cp};
+  if (mode == SCAN_FLAG_NONZERO) launch_scan_t<SCAN_FLAG_NONZERO>(a, a, 1, n, s);
+  else launch_scan_t<SCAN_VALUE>(a, a, 1, n, s);
+}
+
+void launch_gather_scans(const GatherScan& a, const GatherScan& b, const uint32_t* n_dev, int64_t n_max, void* temp,
+                         hipStream_t s) {
+  const size_t nb = (size_t)std::max<int64_t>(1, (n_max + kScanTile - 1) / kScanTile);
+  auto args = [&](const GatherScan& g, uint32_t* bsum) {
+    return ScanArgs{g.src, g.idx, n_dev, g.out, g.total, bsum, g.out_at_idx, g.cp};
+  };
+  launch_scan_t<SCAN_GATHER>(args(a, (uint32_t*)temp), args(b, (uint32_t*)temp + nb), 2, n_max, s);
 }
 
 void launch_emit(const GeomRec* geom, const ViewDesc* views, const uint32_t* srid, const uint32_t* off_t,
-                 const Counters* cnt, int64_t pair_grid_max, int64_t cap_pairs, int npad_shift,
-                 int tile_shift, uint32_t* keys, uint32_t* vals, hipStream_t s) {
-  const int64_t blocks = (pair_grid_max + kEmitTile - 1) / kEmitTile;
-  if (blocks <= 0) return;
+                 Counters* cnt, int64_t cap_pairs, int64_t cap_slots, int npad_shift,
+                 int tile_shift, uint32_t* keys, uint32_t* vals, uint32_t* zero, int64_t n_zero, hipStream_t s) {
+  const int64_t blocks = std::max<int64_t>(1, (cap_pairs + kEmitTile - 1) / kEmitTile);
   hipLaunchKernelGGL(k_emit, dim3((unsigned)blocks), dim3(kEmitThreads), 0, s, geom, views, srid, off_t,
-                     cnt, cap_pairs, npad_shift, tile_shift, keys, vals);
+                     cnt, cap_pairs, cap_slots, npad_shift, tile_shift, keys, vals, zero, n_zero);
 }
 
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) {
@@ -417,16 +409,11 @@ void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, v, n);
 }
 
-void launch_zero2_u32(uint32_t* p, int64_t np, uint32_t* q, int64_t nq, hipStream_t s) {
-  const int64_t n = std::max(np, nq);
+void launch_zero(const ZeroRanges& r, hipStream_t s) {
+  int64_t n = 0;
+  for (int k = 0; k < ZeroRanges::kMax; ++k) n = std::max(n, r.n[k]);
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_zero2_u32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, np, q, nq);
-}
-
-void launch_fill_u8(uint8_t* p, uint8_t v, const uint32_t* n_dev, int64_t n_max, hipStream_t s) {
-  if (n_max <= 0) return;
-  const int64_t blocks = (n_max + 1023) / 1024;
-  hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)blocks), dim3(256), 0, s, p, v, n_dev, n_max);
+  hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 8192)), dim3(256), 0, s, r);
 }
 
 void launch_tile_ranges(const uint32_t* keys, const Counters* cnt, int64_t grid_max, uint2* ranges,
@@ -436,12 +423,6 @@ void launch_tile_ranges(const uint32_t* keys, const Counters* cnt, int64_t grid_
                      cnt, ranges);
 }
 
-void launch_set_overflow(Counters* cnt, uint64_t cap_pairs, uint64_t cap_slots, uint32_t* zero, int64_t n_zero,
-                         hipStream_t s) {
-  const int64_t blocks = std::min<int64_t>(std::max<int64_t>((n_zero + 255) / 256, 1), 1024);
-  hipLaunchKernelGGL(k_set_overflow, dim3((unsigned)blocks), dim3(256), 0, s, cnt, cap_pairs, cap_slots, zero,
-                     n_zero);
-}
 
 uint32_t* launch_order_items(const uint2* ranges, const uint32_t* items, const uint32_t* qoff, const TileItems* tiles,
                              const uint32_t* tq, int64_t n_tiles, uint32_t* out, hipStream_t s) {

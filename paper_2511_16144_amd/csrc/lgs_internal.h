@@ -153,14 +153,8 @@ void launch_project(const Settings& st, const ViewDesc* views, int n_views,
 size_t scan_temp_bytes(int64_t n);
 enum ScanInput { SCAN_FLAG_NONZERO = 0, SCAN_VALUE = 1, SCAN_GATHER = 2 };
 // out[i] = exclusive prefix of in(i); total written to *total.
-// in(i) = (src[i] != 0) / src[i] / src[idx[i]] by mode; n read from *n_dev
-// when n_dev != nullptr (n_max bounds the grid), else n_max.
-// out_at_idx (gather scans only, or NULL): each value also written at its
-// source index, out_at_idx[idx[i]] = out[i].  A gather scan also uses out
-// to hold the gathered values between its two passes, so out must not
-// overlap src or idx.
-// Compaction (flag scans only, ent == nullptr for none; not together with
-// out_at_idx): for every flagged item i, with c = out[i]: ent[c] =
+// in(i) = (src[i] != 0) / src[i] / src[idx[i]] by mode.
+// Compaction (flag scans only, ent == nullptr for none): for every flagged item i, with c = out[i]: ent[c] =
 // ent_copy[c] = i and keys[c] = key_src[i].
 struct Compact {
   const uint32_t* key_src = nullptr;
@@ -172,23 +166,36 @@ struct Compact {
   uint32_t* n_big = nullptr;   // their number (added to)
   uint32_t big_min = 0;
 };
-void launch_scan(int mode, const uint32_t* src, const uint32_t* idx, uint32_t* out,
-                 uint32_t* total, const uint32_t* n_dev, int64_t n_max,
-                 void* temp, hipStream_t s, uint32_t* out_at_idx = nullptr, Compact cp = Compact());
+void launch_scan(int mode, const uint32_t* src, uint32_t* out, uint32_t* total, int64_t n, void* temp, hipStream_t s,
+                 Compact cp = Compact());
+// Two gather scans of the same count (*n_dev, at most n_max).  out_at_idx (or
+// NULL): each value also written at its source index, out_at_idx[idx[i]] =
+// out[i].  out also holds the gathered values between the two passes, so it
+// must not overlap src or idx.
+struct GatherScan {
+  const uint32_t *src, *idx;
+  uint32_t *out, *total, *out_at_idx;
+  Compact cp;
+};
+void launch_gather_scans(const GatherScan& a, const GatherScan& b, const uint32_t* n_dev, int64_t n_max, void* temp,
+                         hipStream_t s);
 
 // pair emission (load-balanced over pairs), tile ranges
+// (also sets the step's overflow flag and effective counts and zeroes
+// zero[0 .. n_zero))
 void launch_emit(const GeomRec* geom, const ViewDesc* views, const uint32_t* srid,
-                 const uint32_t* off_t, const Counters* cnt, int64_t pair_grid_max,
-                 int64_t cap_pairs, int npad_shift, int tile_shift,
-                 uint32_t* keys, uint32_t* vals, hipStream_t s);
+                 const uint32_t* off_t, Counters* cnt, int64_t cap_pairs, int64_t cap_slots, int npad_shift,
+                 int tile_shift, uint32_t* keys, uint32_t* vals, uint32_t* zero, int64_t n_zero, hipStream_t s);
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
-void launch_zero2_u32(uint32_t* p, int64_t np, uint32_t* q, int64_t nq, hipStream_t s);
-void launch_fill_u8(uint8_t* p, uint8_t v, const uint32_t* n_dev, int64_t n_max, hipStream_t s);
+// ranges of words zeroed by one launch
+struct ZeroRanges {
+  static constexpr int kMax = 4;
+  uint32_t* p[kMax] = {nullptr, nullptr, nullptr, nullptr};
+  int64_t n[kMax] = {0, 0, 0, 0};
+};
+void launch_zero(const ZeroRanges& r, hipStream_t s);
 void launch_tile_ranges(const uint32_t* keys, const Counters* cnt, int64_t grid_max,
                         uint2* ranges, hipStream_t s);
-// the step's overflow flag and effective counts; also zeroes zero[0 .. n_zero)
-void launch_set_overflow(Counters* cnt, uint64_t cap_pairs, uint64_t cap_slots, uint32_t* zero, int64_t n_zero,
-                         hipStream_t s);
 // Stable LSD radix sort.  n_max bounds the count (read from *n_dev when
 // n_dev != nullptr); up to small_max it is sorted with the fewest launches,
 // which pays while the count itself stays below some 10^5: kSmallPairs where

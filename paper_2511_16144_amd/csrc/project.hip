@@ -399,16 +399,47 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
   }
 }
 
+// twist[v][k]: the block partials of view v's c range (the scan of the
+// visibility flags gives its first c), summed in block order by one work-group.
+__device__ __forceinline__ void twist_sum(int idx, const double* __restrict__ part, int64_t nblk_max, int n_views,
+                                          uint32_t npad_shift, const uint32_t* __restrict__ cidx,
+                                          const Counters* __restrict__ cnt, float* __restrict__ twist) {
+  __shared__ double red[256];
+  const int v = idx / 6;   // idx: v * 6 + k
+  double s = 0.0;
+  if (cnt->overflow == 0u) {
+    const int64_t c0 = cidx[(uint64_t)v << npad_shift];
+    const int64_t c1 = v + 1 < n_views ? (int64_t)cidx[(uint64_t)(v + 1) << npad_shift] : (int64_t)cnt->n_visible;
+    if (c1 > c0)
+      for (int64_t b = c0 / 64 + threadIdx.x; b <= (c1 - 1) / 64; b += 256) s += part[(int64_t)idx * nblk_max + b];
+  }
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) twist[idx] = (float)red[0];
+}
+
 // Per Gaussian: the views' contributions summed in view order (a fixed
-// order, so results are deterministic), then the activation's chain rule.
+// order, so results are deterministic), then the activation's chain rule.  Where
+// the pose twist is wanted (twist), the first 6 n_views work-groups take one
+// component of a view's each.
 __global__ void __launch_bounds__(256) k_project_bwd(
     Settings st, int n_views, const float* __restrict__ means, const float* __restrict__ log_scales,
     const float* __restrict__ quats, const float* __restrict__ logits, int64_t n,
     uint32_t npad_shift, const Counters* __restrict__ cnt, const uint32_t* __restrict__ cnt_t,
     const uint32_t* __restrict__ cidx, const float* __restrict__ grad2d, const float* __restrict__ contrib,
     float* __restrict__ g_means, float* __restrict__ g_ls, float* __restrict__ g_q, float* __restrict__ g_logit,
-    float* __restrict__ g_rgb, float* __restrict__ g_feat) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    float* __restrict__ g_rgb, float* __restrict__ g_feat, const double* __restrict__ twist_part, int64_t nblk_max,
+    float* __restrict__ twist) {
+  const uint32_t n_twist = twist ? 6u * (uint32_t)n_views : 0u;
+  if (blockIdx.x < n_twist) {
+    twist_sum((int)blockIdx.x, twist_part, nblk_max, n_views, npad_shift, cidx, cnt, twist);
+    return;
+  }
+  const int64_t g = (int64_t)(blockIdx.x - n_twist) * blockDim.x + threadIdx.x;
   const bool active = g < n;
   double p[3] = {0, 0, 0}, ls[3] = {0, 0, 0}, q[4] = {1, 0, 0, 0}, logit = 0.0;
   if (active) {
@@ -560,34 +591,6 @@ __global__ void __launch_bounds__(256) k_group_feat_grad(int n_views, int64_t n,
     if (k < nfeat) g_feat_g[k * n + g] = acc[k];
 }
 
-// twist[v][k] = sum over the projection-backward waves of their partial sums
-// (stored [v][k][wave]); one workgroup per (view, component), fixed
-// summation order.
-// twist[v][k]: the block partials of view v's c range (the scan of the
-// visibility flags gives its first c), summed in block order.
-__global__ void __launch_bounds__(256) k_twist_final(const double* __restrict__ part, int64_t nblk_max,
-                                                    int n_views, uint32_t npad_shift,
-                                                    const uint32_t* __restrict__ cidx,
-                                                    const Counters* __restrict__ cnt, float* __restrict__ twist) {
-  __shared__ double red[256];
-  const int idx = blockIdx.x;   // v * 6 + k
-  const int v = idx / 6;
-  double s = 0.0;
-  if (cnt->overflow == 0u) {
-    const int64_t c0 = cidx[(uint64_t)v << npad_shift];
-    const int64_t c1 = v + 1 < n_views ? (int64_t)cidx[(uint64_t)(v + 1) << npad_shift] : (int64_t)cnt->n_visible;
-    if (c1 > c0)
-      for (int64_t b = c0 / 64 + threadIdx.x; b <= (c1 - 1) / 64; b += 256) s += part[(int64_t)idx * nblk_max + b];
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) twist[idx] = (float)red[0];
-}
-
 }  // namespace
 
 void launch_project(const Settings& st, const ViewDesc* views, int n_views, const float* means,
@@ -657,14 +660,11 @@ void launch_project_bwd(const Settings& st, const ViewDesc* views, int n_views, 
   if (grid > need) grid = need;
   hipLaunchKernelGGL(k_project_bwd_view, dim3((unsigned)grid), dim3(256), 0, s, st, views, means, log_scales,
                      quats, logits, n, npad_shift, cnt, ent, grad2d, contrib, tpart, nblk);
-  const int blocks = (int)((n + 255) / 256);
+  const int64_t blocks = (n + 255) / 256 + (twist ? 6 * n_views : 0);
   if (blocks > 0)
-    hipLaunchKernelGGL(k_project_bwd, dim3(blocks), dim3(256), 0, s, st, n_views, means, log_scales, quats,
+    hipLaunchKernelGGL(k_project_bwd, dim3((unsigned)blocks), dim3(256), 0, s, st, n_views, means, log_scales, quats,
                        logits, n, npad_shift, cnt, cnt_t, cidx, grad2d, (const float*)contrib, g_means, g_ls,
-                       g_q, g_logit, g_rgb, g_feat);
-  if (twist)
-    hipLaunchKernelGGL(k_twist_final, dim3(n_views * 6), dim3(256), 0, s, (const double*)tpart, nblk, n_views,
-                       npad_shift, cidx, cnt, twist);
+                       g_q, g_logit, g_rgb, g_feat, (const double*)tpart, nblk, twist);
 }
 
 }  // namespace lgs

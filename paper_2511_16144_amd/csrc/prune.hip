@@ -409,10 +409,15 @@ unsigned blocks(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 template <bool BF16>
 void launch_t(const PruneArgs& a, const PruneWork& w, hipStream_t s) {
   Rec<BF16>* rec = (Rec<BF16>*)w.rec;
-  launch_zero2_u32(w.count, a.buckets, (uint32_t*)w.pc, sizeof(PruneCounters) / 4, s);
+  ZeroRanges z;
+  z.p[0] = w.count;
+  z.n[0] = a.buckets;
+  z.p[1] = (uint32_t*)w.pc;
+  z.n[1] = sizeof(PruneCounters) / 4;
+  launch_zero(z, s);
   hipLaunchKernelGGL(k_prune_pack<BF16>, dim3(blocks(a.n, 256)), dim3(256), 0, s, a, rec, w.geo, w.sem, w.count,
                      w.list, w.pc);
-  launch_scan(SCAN_VALUE, w.count, nullptr, w.start, w.start + a.buckets, nullptr, a.buckets, w.temp, s);
+  launch_scan(SCAN_VALUE, w.count, w.start, w.start + a.buckets, a.buckets, w.temp, s);
   hipLaunchKernelGGL(k_prune_fill, dim3(blocks(a.n, 256)), dim3(256), 0, s, a, (const uint32_t*)w.start,
                      (const uint32_t*)w.list, w.pos);
   // from here on w.list holds the Gaussians with more than k neighbours

@@ -446,6 +446,7 @@ struct Work {
   const uint32_t* items = nullptr;
   float* partials = nullptr;
   uint8_t* mask = nullptr;
+  int64_t mask_words = 0;     // still to be zeroed
   float* grad2d = nullptr;
   void* ttmp = nullptr;
   bool bwd_alloc = false;
@@ -617,8 +618,9 @@ lgs_status w_alloc_bwd(Work* W) {
     W->geo_acc = (float*)w_alloc(W, sizeof(float) * 6 * std::max<int64_t>(W->n_rid, 1), ok);
   }
   if (!ok) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (backward)");
-  // the slot mask starts at zero; every reduction leaves it at zero again
-  launch_fill_u8(W->mask, 0, nullptr, S + 8, W->stream);
+  // the slot mask starts at zero (the first backward clears it, together with
+  // its counters); every reduction leaves it at zero again
+  W->mask_words = (S + 8 + 3) / 4;
   W->bwd_alloc = true;
   return LGS_OK;
 }
@@ -691,21 +693,19 @@ void enqueue_front(Work* W, const lgs_gaussians* g, hipStream_t s) {
   cp.ent = W->ent;
   cp.ent_copy = W->ent_a;
   cp.keys = W->dk0;
-  launch_scan(SCAN_FLAG_NONZERO, W->cnt_t, nullptr, W->cidx, &W->counters->n_visible, nullptr, n_rid,
-              W->scan_tmp, s, nullptr, cp);
+  launch_scan(SCAN_FLAG_NONZERO, W->cnt_t, W->cidx, &W->counters->n_visible, n_rid, W->scan_tmp, s, cp);
   bool alt = false;
   radix_sort_u32(W->dk0, W->ent_a, W->dk1, W->ent_b, &W->counters->n_visible, n_rid, kSmallIds, 0, 32,
                  W->radix_small, s, &alt);
   W->srid = alt ? W->ent_b : W->ent_a;
-  launch_scan(SCAN_GATHER, W->cnt_t, W->srid, W->off_t, &W->counters->n_pairs, &W->counters->n_visible, n_rid,
-              W->scan_tmp, s);
-  // slot offsets in visible order, and the same as each record's slot base
-  Compact lc;
-  lc.big = W->long_ids;
-  lc.n_big = &W->counters->n_long;
-  lc.big_min = kLongSlots;
-  launch_scan(SCAN_GATHER, W->cnt_b, W->ent, W->slot_off, &W->counters->n_slots, &W->counters->n_visible, n_rid,
-              W->scan_tmp, s, W->slot_base, lc);
+  // pair offsets in depth order; slot offsets in visible order, and the same
+  // as each record's slot base
+  const GatherScan pairs{W->cnt_t, W->srid, W->off_t, &W->counters->n_pairs, nullptr, Compact()};
+  GatherScan slots{W->cnt_b, W->ent, W->slot_off, &W->counters->n_slots, W->slot_base, Compact()};
+  slots.cp.big = W->long_ids;
+  slots.cp.n_big = &W->counters->n_long;
+  slots.cp.big_min = kLongSlots;
+  launch_gather_scans(pairs, slots, &W->counters->n_visible, n_rid, W->scan_tmp, s);
   const size_t esz = W->app_bf16 ? 2 : 4;
   for (int gi = 1; gi < W->G; ++gi)
     launch_pack_app_group((const char*)g->feat + esz * (size_t)kFeatGroup * gi * (size_t)W->n,
@@ -715,10 +715,8 @@ void enqueue_front(Work* W, const lgs_gaussians* g, hipStream_t s) {
 // emission, tile sort, tile ranges, work order (capacity-bounded)
 void enqueue_pairs(Work* W, hipStream_t s) {
   const Plan& P = W->plan;
-  launch_set_overflow(W->counters, (uint64_t)W->cap_pairs, (uint64_t)W->cap_slots, (uint32_t*)W->ranges,
-                      2 * P.n_tiles, s);
-  launch_emit(W->geom, W->d_views, W->srid, W->off_t, W->counters, W->cap_pairs, W->cap_pairs, W->npad_shift,
-              P.tile_shift, W->k0, W->v0, s);
+  launch_emit(W->geom, W->d_views, W->srid, W->off_t, W->counters, W->cap_pairs, W->cap_slots, W->npad_shift,
+              P.tile_shift, W->k0, W->v0, (uint32_t*)W->ranges, 2 * P.n_tiles, s);
   const int tile_bits = std::max<int>(1, (int)ceil_log2((uint64_t)P.n_tiles));
   bool alt = false;
   radix_sort_u32(W->k0, W->v0, W->k1, W->v1, &W->counters->n_pairs_eff, std::max<int64_t>(W->cap_pairs, 1),
@@ -751,15 +749,24 @@ void enqueue_raster_fwd(Work* W, hipStream_t s) {
 // Backward compositing of one feature group; upstream by mode (UpMode):
 // d_up; dL1/dY from (d_fo, d_tgt, d_lossw); or colour channels from d_up and
 // depth + features from the L1 residual.
-// The slot mask needs no clearing here: it is zeroed when the backward's
-// buffers are acquired, and the reduction clears each byte it reads.  The
-// first group's launch also zeroes the backward's work counts.
+// The slot mask is cleared by the first backward over it; from then on the
+// reduction clears each byte it reads.  The first group's launch also zeroes
+// the backward's work counts.
 void launch_group_bwd(Work* W, int gi, int mode, bool first, hipStream_t s) {
   const int V = (int)W->plan.views.size();
   const bool sign = mode != UP_EXPLICIT;
   const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D, gi);
-  launch_zero2_u32(W->counters->work_qb, kQueues * kLineWords, (uint32_t*)&W->counters->bwd_evals, first ? 8 : 0,
-                   s);   // bwd_evals, _contrib, _entries, _written
+  ZeroRanges z;
+  z.p[0] = W->counters->work_qb;
+  z.n[0] = kQueues * kLineWords;
+  if (first) {
+    z.p[1] = (uint32_t*)&W->counters->bwd_evals;   // bwd_evals, _contrib, _entries, _written
+    z.n[1] = 8;
+    z.p[2] = (uint32_t*)W->mask;
+    z.n[2] = W->mask_words;
+    W->mask_words = 0;
+  }
+  launch_zero(z, s);
   if (gi == 0 && W->G == 1) w_mark(W, 5, s);   // one group: the stage is the kernel alone
   launch_raster_bwd(mode, ds, W->d_views, W->d_up + (size_t)gi * V, sign ? W->d_fo + (size_t)gi * V : nullptr,
                     sign ? W->d_tgt + (size_t)gi * V : nullptr, sign ? W->d_lossw + 4 * gi : nullptr, W->ranges,
@@ -1387,6 +1394,9 @@ lgs_status lgs_graph_create(lgs_context* ctx, const lgs_settings* st, const lgs_
   if ((rc = w_alloc_front(W)) != LGS_OK) return bail(rc);
   if ((rc = w_alloc_pairs(W, capP, capS)) != LGS_OK) return bail(rc);
   if ((rc = w_alloc_bwd(W)) != LGS_OK) return bail(rc);
+  // (cleared now: the captured step must not clear it on each launch)
+  launch_fill_u32((uint32_t*)W->mask, 0u, W->mask_words, stream);
+  W->mask_words = 0;
   if ((rc = w_upload(W, out, stream)) != LGS_OK) return bail(rc);
   {
     const std::vector<ViewImages> ho = group_tables(W, out, TAB_FO), ht = group_tables(W, targets, TAB_TGT);
