@@ -113,13 +113,14 @@ struct __attribute__((aligned(128))) Counters {
   // backward's partial records written
   unsigned long long fwd_evals, fwd_contrib, fwd_entries;
   unsigned long long bwd_evals, bwd_contrib, bwd_entries, bwd_written;
-  uint32_t pad2[42];   // the queue counters below start on a 128-byte line
-  // persistent-kernel work counters, queue q at word q * kLineWords, each on
-  // its own line so that the queues' atomics do not serialise on one address
-  uint32_t work_q[kQueues * kLineWords];    // forward
-  uint32_t work_qb[kQueues * kLineWords];   // backward
+  uint32_t pad2[10];
 };
-static_assert(offsetof(Counters, work_q) % 128 == 0, "queue counters must start on a 128-byte line");
+static_assert(sizeof(Counters) % 128 == 0, "whole lines");
+
+// Work counters of one feature group's compositing, queue q at word
+// q * kLineWords, each on its own line so that the queues' atomics do not
+// serialise on one address
+constexpr int kQueueWords = kQueues * kLineWords;
 
 // Queue of the items of binning tile t (global tile index) in the raster
 // and list-length orders (settings.order 0 and 1): neighbouring tiles go to
@@ -222,22 +223,30 @@ uint32_t* launch_order_items(const uint2* ranges, const uint32_t* items, const u
                              const uint32_t* tq, int64_t n_tiles, uint32_t* out, hipStream_t s);
 
 // compositing
-void launch_raster_fwd(const Settings& st, const ViewDesc* views, const ViewImages* out,
+// Feature groups in one launch (blockIdx.y = j): group (first + j) mod total;
+// its image tables start n_views after the group's before it, its appearance
+// app_stride bytes, its work counters kQueueWords words; the backward's partial
+// records and marks of j start j * slots records and mask_stride bytes in.
+struct Groups {
+  int32_t first = 0, count = 1, total = 1, n_views = 0;
+  int64_t app_stride = 0, slots = 0, mask_stride = 0;
+};
+void launch_raster_fwd(const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* out,
                        const uint2* ranges, const uint32_t* vals, const GeomRec* geom,
                        const void* app, int app_bf16, uint32_t npad_mask,
                        const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt,
-                       int waves_per_group, int32_t* last_idx, float* T_state, int n_contrib,
+                       uint32_t* work_q, int waves_per_group, int32_t* last_idx, float* T_state, int n_contrib,
                        hipStream_t s);   // n_contrib: some view's out table asks for contributor counts
 // Upstream of the backward compositing kernel: dL/dY given per channel
 // (upstream), the L1 loss gradient formed from the forward's images and the
 // targets (loss_w), or the colour channels given and depth + features from
 // the L1 residual (the D-SSIM loss, whose colour gradient a kernel writes).
 enum UpMode { UP_EXPLICIT = 0, UP_L1 = 1, UP_RGB = 2 };
-void launch_raster_bwd(int up_mode, const Settings& st, const ViewDesc* views, const ViewImages* upstream,
+void launch_raster_bwd(int up_mode, const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* upstream,
                        const ViewImages* fwd_out, const ViewImages* targets, const float* loss_w,
                        const uint2* ranges, const uint32_t* vals, const GeomRec* geom,
                        const void* app, int app_bf16, uint32_t npad_mask,
-                       const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt,
+                       const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt, uint32_t* work_q,
                        int waves_per_group, const int32_t* last_idx, const float* T_state,
                        const uint32_t* slot_base, float* partials, uint8_t* mask, hipStream_t s);
 
@@ -317,19 +326,30 @@ uint32_t prune_buckets(int64_t n);
 // the whole pass (n > 0); leaves the mask alone when w.pc->range_err
 void launch_prune(const PruneArgs& a, const PruneWork& w, uint8_t* mask, hipStream_t s);
 
-// feature groups beyond the first: appearance records (RGB 0, the group's
-// features), the geometric partials of a group's backward added to the
-// first group's, and a group's feature gradients summed over views
-void launch_pack_app_group(const void* feat_g, int nfeat, int app_bf16, int64_t n, void* app, hipStream_t s);
-void launch_group_geo_acc(const float* grad2d_g, const Counters* cnt, int64_t n_max, float* geo_acc, int first,
-                          hipStream_t s);
-void launch_group_geo_add(float* grad2d, const Counters* cnt, int64_t n_max, const float* geo_acc, hipStream_t s);
-void launch_group_feat_grad(int n_views, int64_t n, uint32_t npad_shift, const Counters* cnt, const uint32_t* cnt_t,
-                            const uint32_t* cidx, const float* grad2d_g, int nfeat, float* g_feat_g, hipStream_t s);
+// feature groups beyond the first (feat: the first group's planes): appearance
+// records (RGB 0, the group's features), app_stride bytes from one to the next
+void launch_pack_app_groups(const void* feat, int app_bf16, int64_t n, int n_groups, void* app, int64_t app_stride,
+                            hipStream_t s);
+// geo_acc[c][0 .. 5] (= | +=) the geometric sums of `count` groups' reductions,
+// one after the other (stride floats apart)
+void launch_group_geo_acc(const float* grad2d, int64_t stride, int count, const Counters* cnt, int64_t n_max,
+                          float* geo_acc, int first, hipStream_t s);
+// the feature gradients of those of the groups that are not the first
+void launch_group_feat_grad(const Groups& gr, int64_t n, uint32_t npad_shift, const Counters* cnt,
+                            const uint32_t* cnt_t, const uint32_t* cidx, const float* grad2d, int64_t stride,
+                            float* g_feat, hipStream_t s);
 
 // gradient reduction and projection backward
-void launch_seg_reduce(const uint32_t* slot_off, const float* partials, uint8_t* mask,
-                       const uint32_t* long_ids, const Counters* cnt, int64_t n_max, float* grad2d, hipStream_t s);
+void launch_seg_reduce(const Groups& gr, const uint32_t* slot_off, const float* partials, uint8_t* mask,
+                       const uint32_t* long_ids, const Counters* cnt, int64_t n_max, float* grad2d, int64_t stride,
+                       hipStream_t s);
+// Geometric sums of the feature groups besides the first, added to its own:
+// those summed before (or NULL), then n reductions, stride floats apart.
+struct GroupGeo {
+  const float *acc = nullptr, *grad2d = nullptr;
+  int64_t stride = 0;
+  int32_t n = 0;
+};
 // workspace of launch_project_bwd for at most n_rid visible (view, Gaussian)
 size_t project_bwd_temp_bytes(int64_t n_rid, int n_views);
 // the projection backward: per visible (view, Gaussian) c the view's chain
@@ -338,7 +358,7 @@ size_t project_bwd_temp_bytes(int64_t n_rid, int n_views);
 void launch_project_bwd(const Settings& st, const ViewDesc* views, int n_views, const float* means,
                         const float* log_scales, const float* quats, const float* logits, int64_t n,
                         uint32_t npad_shift, int64_t n_rid, const Counters* cnt, const uint32_t* cnt_t,
-                        const uint32_t* cidx, const uint32_t* ent, const float* grad2d, float* g_means,
+                        const uint32_t* cidx, const uint32_t* ent, const GroupGeo& geo, const float* grad2d, float* g_means,
                         float* g_ls, float* g_q, float* g_logit, float* g_rgb, float* g_feat, float* twist,
                         void* temp, hipStream_t s);
 

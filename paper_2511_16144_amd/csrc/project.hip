@@ -273,7 +273,7 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
     Settings st, const ViewDesc* __restrict__ views, const float* __restrict__ means,
     const float* __restrict__ log_scales, const float* __restrict__ quats, const float* __restrict__ logits,
     int64_t n, uint32_t npad_shift, const Counters* __restrict__ cnt, const uint32_t* __restrict__ ent,
-    const float* __restrict__ grad2d, float* __restrict__ contrib, double* __restrict__ twist_part,
+    GroupGeo geo, const float* __restrict__ grad2d, float* __restrict__ contrib, double* __restrict__ twist_part,
     int64_t nblk_max) {
   if (cnt->overflow) return;
   const int lane = threadIdx.x & 63;
@@ -300,7 +300,19 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
       double gp[3] = {0, 0, 0}, gM[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, glogit = 0.0;
       const ViewDesc V = views[v];
       const float* Y = grad2d + (size_t)ci * kPartials;
-      const float* G = Y + kPartGeo;
+      float G[6];
+      for (int k = 0; k < 6; ++k) G[k] = Y[kPartGeo + k];
+      if (geo.acc || geo.n > 0) {
+        // the other feature groups' sums, added up in order, then to the first's
+        for (int k = 0; k < 6; ++k) {
+          float t = geo.acc ? geo.acc[ci * 6 + k] : 0.f;
+          for (int j = 0; j < geo.n; ++j) {
+            const float x = geo.grad2d[j * geo.stride + ci * kPartials + kPartGeo + k];
+            t = !geo.acc && j == 0 ? x : t + x;
+          }
+          G[k] += t;
+        }
+      }
       Screen S;
       to_screen(V, p, P, (double)st.eps2d, S);
       const double z = S.xc[2], iz = 1.0 / z;
@@ -516,21 +528,24 @@ __global__ void __launch_bounds__(256) k_project_bwd(
     if (k < st.nfeat) g_feat[k * n + g] = gy[4 + k];
 }
 
-// Appearance records of a feature group beyond the first: RGB 0, slot 3
-// unused, the group's nfeat feature planes starting at feat_g (the rest 0).
+// Appearance records of the feature groups beyond the first: RGB 0, slot 3
+// unused, the group's 16 feature planes.
 template <bool BF16>
-__global__ void __launch_bounds__(256) k_pack_app_group(const void* __restrict__ feat_g, int nfeat, int64_t n,
-                                                        void* __restrict__ app) {
+__global__ void __launch_bounds__(256) k_pack_app_groups(const void* __restrict__ feat, int64_t n,
+                                                         void* __restrict__ app0, int64_t app_stride) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= n) return;
+  const int gi = (int)blockIdx.y + 1;
+  void* app = (char*)app0 + gi * app_stride;
+  const void* feat_g = (const char*)feat + (int64_t)gi * kFeatGroup * n * (BF16 ? 2 : 4);
   if (BF16) {
     const uint16_t* f = (const uint16_t*)feat_g;
     uint32_t w[10];
     w[0] = 0u;
     w[1] = 0u;
     for (int k = 0; k < 8; ++k) {
-      const uint32_t lo = 2 * k < nfeat ? (uint32_t)f[(2 * k) * n + g] : 0u;
-      const uint32_t hi = 2 * k + 1 < nfeat ? (uint32_t)f[(2 * k + 1) * n + g] : 0u;
+      const uint32_t lo = f[(2 * k) * n + g];
+      const uint32_t hi = f[(2 * k + 1) * n + g];
       w[2 + k] = lo | (hi << 16);
     }
     uint2* d2 = (uint2*)((uint32_t*)app + (size_t)g * 10);
@@ -539,56 +554,53 @@ __global__ void __launch_bounds__(256) k_pack_app_group(const void* __restrict__
     const float* f = (const float*)feat_g;
     float y[20];
     for (int k = 0; k < 4; ++k) y[k] = 0.f;
-    for (int k = 0; k < 16; ++k) y[4 + k] = k < nfeat ? f[k * n + g] : 0.f;
+    for (int k = 0; k < 16; ++k) y[4 + k] = f[k * n + g];
     float4* dst = (float4*)((float*)app + (size_t)g * 20);
     for (int k = 0; k < 5; ++k) dst[k] = make_float4(y[4 * k], y[4 * k + 1], y[4 * k + 2], y[4 * k + 3]);
   }
 }
 
-// geo_acc[c][0..5] (=|+=) the geometric sums (moments, opacity) of
-// a feature group's backward, per visible (view, Gaussian)
-__global__ void __launch_bounds__(256) k_group_geo_acc(const float* __restrict__ grad2d_g,
+// geo_acc[c][0 .. 5] (= | +=) the geometric sums (moments, opacity) of feature
+// groups' backwards, per visible (view, Gaussian), one group after the other
+__global__ void __launch_bounds__(256) k_group_geo_acc(const float* __restrict__ grad2d, int64_t stride, int count,
                                                        const Counters* __restrict__ cnt,
                                                        float* __restrict__ geo_acc, int first) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t m = (int64_t)cnt->n_visible * 6;
   if (i >= m || cnt->overflow) return;
   const int64_t c = i / 6, k = i - 6 * c;
-  const float v = grad2d_g[(size_t)c * kPartials + kPartGeo + k];
-  geo_acc[i] = first ? v : geo_acc[i] + v;
-}
-
-__global__ void __launch_bounds__(256) k_group_geo_add(float* __restrict__ grad2d, const Counters* __restrict__ cnt,
-                                                       const float* __restrict__ geo_acc) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t m = (int64_t)cnt->n_visible * 6;
-  if (i >= m || cnt->overflow) return;
-  const int64_t c = i / 6, k = i - 6 * c;
-  grad2d[(size_t)c * kPartials + kPartGeo + k] += geo_acc[i];
+  float t = first ? 0.f : geo_acc[i];
+  for (int j = 0; j < count; ++j) {
+    const float v = grad2d[j * stride + c * kPartials + kPartGeo + k];
+    t = first && j == 0 ? v : t + v;
+  }
+  geo_acc[i] = t;
 }
 
 // a feature group's gradients: sum over the views where the Gaussian is
 // visible of its colour partials f0.. (slots 4 ..), zero elsewhere
-__global__ void __launch_bounds__(256) k_group_feat_grad(int n_views, int64_t n, uint32_t npad_shift,
+__global__ void __launch_bounds__(256) k_group_feat_grad(Groups gr, int64_t n, uint32_t npad_shift,
                                                          const Counters* __restrict__ cnt,
                                                          const uint32_t* __restrict__ cnt_t,
                                                          const uint32_t* __restrict__ cidx,
-                                                         const float* __restrict__ grad2d_g, int nfeat,
-                                                         float* __restrict__ g_feat_g) {
+                                                         const float* __restrict__ grad2d, int64_t stride,
+                                                         float* __restrict__ g_feat) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= n) return;
+  const int gi = (gr.first + (int)blockIdx.y) % gr.total;
+  const float* grad2d_g = grad2d + blockIdx.y * stride;
+  float* g_feat_g = g_feat + (int64_t)gi * kFeatGroup * n;
   float acc[16];
   for (int k = 0; k < 16; ++k) acc[k] = 0.f;
   if (cnt->overflow == 0u)
-    for (int v = 0; v < n_views; ++v) {
+    for (int v = 0; v < gr.n_views; ++v) {
       const uint64_t rid = ((uint64_t)v << npad_shift) | (uint64_t)g;
       if (cnt_t[rid] != 0) {
         const float* G = grad2d_g + (size_t)cidx[rid] * kPartials;
         for (int k = 0; k < 16; ++k) acc[k] += G[4 + k];
       }
     }
-  for (int k = 0; k < 16; ++k)
-    if (k < nfeat) g_feat_g[k * n + g] = acc[k];
+  for (int k = 0; k < 16; ++k) g_feat_g[k * n + g] = acc[k];
 }
 
 }  // namespace
@@ -608,31 +620,29 @@ void launch_project(const Settings& st, const ViewDesc* views, int n_views, cons
                        log_scales, quats, logits, rgb, feat, n, npad_shift, geom, cnt_t, cnt_b, dkey, app, cnt);
 }
 
-void launch_pack_app_group(const void* feat_g, int nfeat, int app_bf16, int64_t n, void* app, hipStream_t s) {
-  if (n <= 0) return;
-  const int blocks = (int)((n + 255) / 256);
-  if (app_bf16) hipLaunchKernelGGL(k_pack_app_group<true>, dim3(blocks), dim3(256), 0, s, feat_g, nfeat, n, app);
-  else hipLaunchKernelGGL(k_pack_app_group<false>, dim3(blocks), dim3(256), 0, s, feat_g, nfeat, n, app);
+void launch_pack_app_groups(const void* feat, int app_bf16, int64_t n, int n_groups, void* app, int64_t app_stride,
+                            hipStream_t s) {
+  if (n <= 0 || n_groups <= 1) return;
+  const dim3 grid((unsigned)((n + 255) / 256), (unsigned)(n_groups - 1));
+  if (app_bf16) hipLaunchKernelGGL(k_pack_app_groups<true>, grid, dim3(256), 0, s, feat, n, app, app_stride);
+  else hipLaunchKernelGGL(k_pack_app_groups<false>, grid, dim3(256), 0, s, feat, n, app, app_stride);
 }
 
-void launch_group_geo_acc(const float* grad2d_g, const Counters* cnt, int64_t n_max, float* geo_acc, int first,
-                          hipStream_t s) {
+void launch_group_geo_acc(const float* grad2d, int64_t stride, int count, const Counters* cnt, int64_t n_max,
+                          float* geo_acc, int first, hipStream_t s) {
   if (n_max <= 0) return;
-  hipLaunchKernelGGL(k_group_geo_acc, dim3((unsigned)((6 * n_max + 255) / 256)), dim3(256), 0, s, grad2d_g, cnt,
-                     geo_acc, first);
+  hipLaunchKernelGGL(k_group_geo_acc, dim3((unsigned)((6 * n_max + 255) / 256)), dim3(256), 0, s, grad2d, stride,
+                     count, cnt, geo_acc, first);
 }
 
-void launch_group_geo_add(float* grad2d, const Counters* cnt, int64_t n_max, const float* geo_acc, hipStream_t s) {
-  if (n_max <= 0) return;
-  hipLaunchKernelGGL(k_group_geo_add, dim3((unsigned)((6 * n_max + 255) / 256)), dim3(256), 0, s, grad2d, cnt,
-                     geo_acc);
-}
-
-void launch_group_feat_grad(int n_views, int64_t n, uint32_t npad_shift, const Counters* cnt, const uint32_t* cnt_t,
-                            const uint32_t* cidx, const float* grad2d_g, int nfeat, float* g_feat_g, hipStream_t s) {
-  if (n <= 0) return;
-  hipLaunchKernelGGL(k_group_feat_grad, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n_views, n, npad_shift,
-                     cnt, cnt_t, cidx, grad2d_g, nfeat, g_feat_g);
+void launch_group_feat_grad(const Groups& gr, int64_t n, uint32_t npad_shift, const Counters* cnt,
+                            const uint32_t* cnt_t, const uint32_t* cidx, const float* grad2d, int64_t stride,
+                            float* g_feat, hipStream_t s) {
+  // (the first group comes last in its launch, and has its own place)
+  const int count = gr.first + gr.count > gr.total || gr.first == 0 ? gr.count - 1 : gr.count;
+  if (n <= 0 || count <= 0) return;
+  hipLaunchKernelGGL(k_group_feat_grad, dim3((unsigned)((n + 255) / 256), (unsigned)count), dim3(256), 0, s, gr, n,
+                     npad_shift, cnt, cnt_t, cidx, grad2d, stride, g_feat);
 }
 
 // per-view contributions (16 floats per visible c) and the twist's block
@@ -645,7 +655,8 @@ size_t project_bwd_temp_bytes(int64_t n_rid, int n_views) {
 void launch_project_bwd(const Settings& st, const ViewDesc* views, int n_views, const float* means,
                         const float* log_scales, const float* quats, const float* logits, int64_t n,
                         uint32_t npad_shift, int64_t n_rid, const Counters* cnt, const uint32_t* cnt_t,
-                        const uint32_t* cidx, const uint32_t* ent, const float* grad2d, float* g_means,
+                        const uint32_t* cidx, const uint32_t* ent, const GroupGeo& geo, const float* grad2d,
+                        float* g_means,
                         float* g_ls, float* g_q, float* g_logit, float* g_rgb, float* g_feat, float* twist,
                         void* temp, hipStream_t s) {
   const int64_t nblk = (std::max<int64_t>(n_rid, 1) + 63) / 64;
@@ -659,7 +670,7 @@ void launch_project_bwd(const Settings& st, const ViewDesc* views, int n_views, 
   const int64_t need = (nblk + 3) / 4;   // four waves (blocks of 64 c) per work-group
   if (grid > need) grid = need;
   hipLaunchKernelGGL(k_project_bwd_view, dim3((unsigned)grid), dim3(256), 0, s, st, views, means, log_scales,
-                     quats, logits, n, npad_shift, cnt, ent, grad2d, contrib, tpart, nblk);
+                     quats, logits, n, npad_shift, cnt, ent, geo, grad2d, contrib, tpart, nblk);
   const int64_t blocks = (n + 255) / 256 + (twist ? 6 * n_views : 0);
   if (blocks > 0)
     hipLaunchKernelGGL(k_project_bwd, dim3((unsigned)blocks), dim3(256), 0, s, st, n_views, means, log_scales, quats,

@@ -238,13 +238,19 @@ __device__ __forceinline__ float block_px_bias(uint32_t b0) { return __uint_as_f
 // without them the entry loop keeps no count.
 template <bool BF16, bool CNT, bool NC>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 7 : 8, BF16 ? 7 : 8))) k_raster_fwd(
-    Settings st, const ViewDesc* __restrict__ views, const ViewImages* __restrict__ out,
+    Settings st, Groups gr, const ViewDesc* __restrict__ views, const ViewImages* __restrict__ out,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const GeomRec* __restrict__ geom, const void* __restrict__ app, uint32_t npad_mask,
     const uint32_t* __restrict__ items, const uint32_t* __restrict__ qoff, uint32_t n_items,
-    Counters* __restrict__ cnt, int32_t* __restrict__ last_idx, float* __restrict__ T_state) {
+    Counters* __restrict__ cnt, uint32_t* __restrict__ work_q, int32_t* __restrict__ last_idx,
+    float* __restrict__ T_state) {
   const int lane = threadIdx.x & 63;
   if (cnt->overflow) return;
+  if (gr.total > 1) {   // (groups of one pixel write the same last entry and T)
+    out += (size_t)blockIdx.y * gr.n_views;
+    app = (const char*)app + blockIdx.y * gr.app_stride;
+    work_q += blockIdx.y * kQueueWords;
+  }
   extern __shared__ float lds_f[];
   float* ws = lds_f + (threadIdx.x >> 6) * (kFwdWaveLds / 4);
   unsigned short* ys = (unsigned short*)(ws + kFwdW);
@@ -269,7 +275,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
   uint32_t n_eval = 0, n_con = 0, n_ent = 0;
   const uint32_t q = blockIdx.x % (uint32_t)kQueues;
   for (;;) {
-    const uint32_t it = next_item(cnt->work_q, qoff, q, n_items);
+    const uint32_t it = next_item(work_q, qoff, q, n_items);
     if (it >= n_items) break;
     const uint32_t item = items[it];
     const uint32_t bx = item & 255u, by = (item >> 8) & 255u, v = item >> 16;
@@ -528,13 +534,13 @@ __device__ int amdgcn_writelane(int val, int lane, int old) __asm("llvm.amdgcn.w
 // Four waves per SIMD (128 VGPRs; what the LDS allows too).
 template <bool BF16, int UPM, bool CNT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) k_raster_bwd(
-    Settings st, const ViewDesc* __restrict__ views, const ViewImages* __restrict__ upstream,
+    Settings st, Groups gr, const ViewDesc* __restrict__ views, const ViewImages* __restrict__ upstream,
     const ViewImages* __restrict__ fwd_out, const ViewImages* __restrict__ targets,
     const float* __restrict__ loss_w, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const GeomRec* __restrict__ geom,
     const void* __restrict__ app, uint32_t npad_mask, const uint32_t* __restrict__ items,
     const uint32_t* __restrict__ qoff, uint32_t n_items, Counters* __restrict__ cnt,
-    const int32_t* __restrict__ last_idx,
+    uint32_t* __restrict__ work_q, const int32_t* __restrict__ last_idx,
     const float* __restrict__ T_state, const uint32_t* __restrict__ slot_base,
     float* __restrict__ partials, uint8_t* __restrict__ mask) {
   const int lane = threadIdx.x & 63;
@@ -555,6 +561,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
   unsigned short* gz = wz + kBatchBytes / 2;         // upstream rows of channels 16-19 (hi, lo)
   const int grp = lane >> 4, col = lane & 15;
   if (cnt->overflow) return;
+  if (gr.total > 1) {
+    const uint32_t j = blockIdx.y, gi = ((uint32_t)gr.first + j) % (uint32_t)gr.total;
+    const size_t tab_off = (size_t)gi * gr.n_views;
+    if (UPM != UP_L1) upstream += tab_off;
+    if (UPM != UP_EXPLICIT) {
+      fwd_out += tab_off;
+      targets += tab_off;
+      loss_w += 4 * gi;
+    }
+    app = (const char*)app + gi * gr.app_stride;
+    work_q += gi * kQueueWords;
+    partials += j * gr.slots * kSlotFloats;
+    mask += j * gr.mask_stride;
+  }
   if (lane < 16) {
     const float X = (float)(lane & 3) - 1.5f, Y = (float)(lane >> 2) - 1.5f;
     const float b[6] = {1.f, X, Y, X * X, X * Y, Y * Y};
@@ -570,7 +590,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
   uint32_t n_eval = 0, n_con = 0, n_ent = 0, n_wr = 0;
   const uint32_t q = blockIdx.x % (uint32_t)kQueues;
   for (;;) {
-    const uint32_t it = next_item(cnt->work_qb, qoff, q, n_items);
+    const uint32_t it = next_item(work_q, qoff, q, n_items);
     if (it >= n_items) break;
     const uint32_t item = items[it];
     const uint32_t bx = item & 255u, by = (item >> 8) & 255u, v = item >> 16;
@@ -1013,12 +1033,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
 // order of the additions moves gradients with much cancellation by 1e-3.)
 constexpr int kSegBatch = 8;
 constexpr int kSegWaves = 4;
-__global__ void __launch_bounds__(256, 8) k_seg_reduce(const uint32_t* __restrict__ slot_off,
+__global__ void __launch_bounds__(256, 8) k_seg_reduce(Groups gr, const uint32_t* __restrict__ slot_off,
                                                     const float* __restrict__ partials,
                                                     uint8_t* __restrict__ mask,
                                                     const uint32_t* __restrict__ long_ids,
                                                     const Counters* __restrict__ cnt,
-                                                    float* __restrict__ grad2d) {
+                                                    float* __restrict__ grad2d, int64_t stride) {
+  partials += blockIdx.y * gr.slots * kSlotFloats;
+  mask += blockIdx.y * gr.mask_stride;
+  grad2d += blockIdx.y * stride;
   __shared__ float sum[32];
   const int lane = threadIdx.x & 63;
   if (cnt->overflow) return;
@@ -1182,10 +1205,10 @@ __global__ void __launch_bounds__(256, 8) k_seg_reduce(const uint32_t* __restric
 }  // namespace
 
 template <bool BF16, bool CNT, bool NC>
-static void launch_fwd_t(const Settings& st, const ViewDesc* views, const ViewImages* out, const uint2* ranges,
+static void launch_fwd_t(const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* out, const uint2* ranges,
                          const uint32_t* vals, const GeomRec* geom, const void* app, uint32_t npad_mask,
                          const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt,
-                         int waves_per_group, int32_t* last_idx, float* T_state, hipStream_t s) {
+                         uint32_t* work_q, int waves_per_group, int32_t* last_idx, float* T_state, hipStream_t s) {
   const int threads = 64 * waves_per_group;
   int dev = 0, cus = 256;
   hipGetDevice(&dev);
@@ -1197,19 +1220,20 @@ static void launch_fwd_t(const Settings& st, const ViewDesc* views, const ViewIm
   const int64_t need = (n_items + waves_per_group - 1) / waves_per_group;
   if (grid > need) grid = need;
   if (grid < kQueues) grid = kQueues;   // every queue needs a workgroup (index mod kQueues) to drain it
-  hipLaunchKernelGGL((k_raster_fwd<BF16, CNT, NC>), dim3((unsigned)grid), dim3(threads), lds, s, st, views, out,
-                     ranges, vals, geom, app, npad_mask, items, qoff, (uint32_t)n_items, cnt, last_idx, T_state);
+  hipLaunchKernelGGL((k_raster_fwd<BF16, CNT, NC>), dim3((unsigned)grid, gr.count), dim3(threads), lds, s, st, gr, views, out,
+                     ranges, vals, geom, app, npad_mask, items, qoff, (uint32_t)n_items, cnt, work_q, last_idx,
+                     T_state);
 }
 
-void launch_raster_fwd(const Settings& st, const ViewDesc* views, const ViewImages* out, const uint2* ranges,
+void launch_raster_fwd(const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* out, const uint2* ranges,
                        const uint32_t* vals, const GeomRec* geom, const void* app, int app_bf16,
                        uint32_t npad_mask, const uint32_t* items, const uint32_t* qoff, int64_t n_items,
-                       Counters* cnt, int waves_per_group, int32_t* last_idx, float* T_state, int n_contrib,
+                       Counters* cnt, uint32_t* work_q, int waves_per_group, int32_t* last_idx, float* T_state, int n_contrib,
                        hipStream_t s) {
   if (n_items <= 0) return;
 #define LGS_FWD(B, K, N)                                                                                     \
-  launch_fwd_t<B, K, N>(st, views, out, ranges, vals, geom, app, npad_mask, items, qoff, n_items, cnt,       \
-                        waves_per_group, last_idx, T_state, s)
+  launch_fwd_t<B, K, N>(st, gr, views, out, ranges, vals, geom, app, npad_mask, items, qoff, n_items, cnt,   \
+                        work_q, waves_per_group, last_idx, T_state, s)
 #define LGS_FWD_N(B, K)        \
   if (n_contrib) LGS_FWD(B, K, true); \
   else LGS_FWD(B, K, false)
@@ -1225,11 +1249,11 @@ void launch_raster_fwd(const Settings& st, const ViewDesc* views, const ViewImag
 }
 
 template <bool BF16, int UPM, bool CNT>
-static void launch_bwd_t(const Settings& st, const ViewDesc* views, const ViewImages* upstream,
+static void launch_bwd_t(const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* upstream,
                          const ViewImages* fwd_out, const ViewImages* targets, const float* loss_w,
                          const uint2* ranges, const uint32_t* vals, const GeomRec* geom, const void* app,
                          uint32_t npad_mask, const uint32_t* items, const uint32_t* qoff, int64_t n_items,
-                         Counters* cnt, int waves_per_group, const int32_t* last_idx, const float* T_state,
+                         Counters* cnt, uint32_t* work_q, int waves_per_group, const int32_t* last_idx, const float* T_state,
                          const uint32_t* slot_base, float* partials, uint8_t* mask, hipStream_t s) {
   const int threads = 64 * waves_per_group;
   const size_t lds = kBasisBytes + (size_t)waves_per_group * bwd_wave_lds(UPM);
@@ -1242,25 +1266,25 @@ static void launch_bwd_t(const Settings& st, const ViewDesc* views, const ViewIm
   const int64_t need = (n_items + waves_per_group - 1) / waves_per_group;
   if (grid > need) grid = need;
   if (grid < kQueues) grid = kQueues;   // every queue needs a workgroup (index mod kQueues) to drain it
-  hipLaunchKernelGGL((k_raster_bwd<BF16, UPM, CNT>), dim3((unsigned)grid), dim3(threads), lds, s, st, views,
+  hipLaunchKernelGGL((k_raster_bwd<BF16, UPM, CNT>), dim3((unsigned)grid, gr.count), dim3(threads), lds, s, st, gr, views,
                      upstream, fwd_out, targets, loss_w, ranges, vals, geom, app, npad_mask, items, qoff,
-                     (uint32_t)n_items, cnt, last_idx, T_state, slot_base, partials, mask);
+                     (uint32_t)n_items, cnt, work_q, last_idx, T_state, slot_base, partials, mask);
 }
 
-void launch_raster_bwd(int up_mode, const Settings& st, const ViewDesc* views, const ViewImages* upstream,
+void launch_raster_bwd(int up_mode, const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* upstream,
                        const ViewImages* fwd_out, const ViewImages* targets, const float* loss_w,
                        const uint2* ranges, const uint32_t* vals, const GeomRec* geom, const void* app,
                        int app_bf16, uint32_t npad_mask, const uint32_t* items, const uint32_t* qoff,
-                       int64_t n_items, Counters* cnt, int waves_per_group, const int32_t* last_idx,
+                       int64_t n_items, Counters* cnt, uint32_t* work_q, int waves_per_group, const int32_t* last_idx,
                        const float* T_state, const uint32_t* slot_base, float* partials, uint8_t* mask,
                        hipStream_t s) {
   if (n_items <= 0) return;
 #define LGS_BWD(B, M)                                                                                     \
-  (st.count ? launch_bwd_t<B, M, true>(st, views, upstream, fwd_out, targets, loss_w, ranges, vals, geom, app,  \
-                                       npad_mask, items, qoff, n_items, cnt, waves_per_group, last_idx,      \
+  (st.count ? launch_bwd_t<B, M, true>(st, gr, views, upstream, fwd_out, targets, loss_w, ranges, vals, geom, app,  \
+                                       npad_mask, items, qoff, n_items, cnt, work_q, waves_per_group, last_idx,      \
                                        T_state, slot_base, partials, mask, s)                                 \
-            : launch_bwd_t<B, M, false>(st, views, upstream, fwd_out, targets, loss_w, ranges, vals, geom,  \
-                                        app, npad_mask, items, qoff, n_items, cnt, waves_per_group, last_idx, \
+            : launch_bwd_t<B, M, false>(st, gr, views, upstream, fwd_out, targets, loss_w, ranges, vals, geom,  \
+                                        app, npad_mask, items, qoff, n_items, cnt, work_q, waves_per_group, last_idx, \
                                         T_state, slot_base, partials, mask, s))
   if (app_bf16) {
     if (up_mode == UP_L1) LGS_BWD(true, UP_L1);
@@ -1274,8 +1298,9 @@ void launch_raster_bwd(int up_mode, const Settings& st, const ViewDesc* views, c
 #undef LGS_BWD
 }
 
-void launch_seg_reduce(const uint32_t* slot_off, const float* partials, uint8_t* mask,
-                       const uint32_t* long_ids, const Counters* cnt, int64_t n_max, float* grad2d, hipStream_t s) {
+void launch_seg_reduce(const Groups& gr, const uint32_t* slot_off, const float* partials, uint8_t* mask,
+                       const uint32_t* long_ids, const Counters* cnt, int64_t n_max, float* grad2d, int64_t stride,
+                       hipStream_t s) {
   if (n_max <= 0) return;
   int dev = 0, cus = 256, occ = 1;
   hipGetDevice(&dev);
@@ -1284,8 +1309,8 @@ void launch_seg_reduce(const uint32_t* slot_off, const float* partials, uint8_t*
   int64_t grid = (int64_t)cus * (occ > 0 ? occ : 1);
   const int64_t need = (n_max + 7) / 8;   // two visible ids per wave
   if (grid > need) grid = need;
-  hipLaunchKernelGGL(k_seg_reduce, dim3((unsigned)grid), dim3(256), 0, s, slot_off, partials, mask, long_ids, cnt,
-                     grad2d);
+  hipLaunchKernelGGL(k_seg_reduce, dim3((unsigned)grid, gr.count), dim3(256), 0, s, gr, slot_off, partials, mask, long_ids, cnt,
+                     grad2d, stride);
 }
 
 }  // namespace lgs

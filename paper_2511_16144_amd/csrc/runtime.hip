@@ -322,15 +322,14 @@ std::vector<uint32_t> make_items(const Plan& P, int tile, bool spatial) {
 
 
 // feature channels of group g when the features have D channels
-int group_nfeat(int D, int g) { return D >= kFeatGroup * (g + 1) ? kFeatGroup : D - kFeatGroup * g; }
-
-Settings dev_settings(const lgs_settings* st, int tile_shift, int D = kFeatGroup, int group = 0) {
+// (a dimension above 16 is a multiple of 16: every group of it is whole)
+Settings dev_settings(const lgs_settings* st, int tile_shift, int D) {
   Settings s;
   s.z_near = st->z_near; s.eps2d = st->eps2d; s.fov_clamp = st->fov_clamp;
   s.alpha_max = st->alpha_max; s.alpha_min = st->alpha_min; s.T_eps = st->T_eps;
   s.cutoff2 = st->cutoff2; s.tile = st->tile; s.tile_shift = tile_shift;
   s.feat_dim = D;
-  s.nfeat = group_nfeat(D, group);
+  s.nfeat = std::min(D, kFeatGroup);
   s.count = (st->profile & LGS_PROFILE_COUNTS) != 0;
   s.log2_alpha_min = log2f(st->alpha_min);
   return s;
@@ -425,10 +424,13 @@ struct Work {
   float* d_lossw = nullptr;
   int want_ncon = 0;                         // some view of the forward's outputs asks for contributor counts
   int D = kFeatGroup, G = 1;                 // feature dimension and groups
-  std::vector<void*> app_g;                  // appearance records of groups 1 ..
   float* scratch_img = nullptr;              // groups 1 ..: their RGB / depth / T outputs (discarded)
   float* zero_img = nullptr;                 // groups 1 ..: zero RGB / depth upstream
-  float *grad2d_g = nullptr, *geo_acc = nullptr;
+  int gb = 1;                                // groups at once in the backward
+  int64_t app_stride = 0;                    // bytes from one group's appearance records to the next
+  int64_t grad2d_stride = 0, mask_stride = 0;
+  float* geo_acc = nullptr;
+  uint32_t *work_q = nullptr, *work_qb = nullptr;   // [group][kQueueWords]
   GeomRec* geom = nullptr;
   uint32_t *cnt_t = nullptr, *cnt_b = nullptr, *cidx = nullptr, *slot_base = nullptr;
   uint32_t *ent = nullptr, *ent_a = nullptr, *ent_b = nullptr, *srid = nullptr;
@@ -441,6 +443,7 @@ struct Work {
   void *scan_tmp = nullptr, *radix_small = nullptr, *radix_big = nullptr;
   uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr, *pkeys = nullptr, *pvals = nullptr;
   uint2* ranges = nullptr;
+  int64_t range_words = 0;    // to be cleared from there on
   const uint32_t* items_static = nullptr;
   uint32_t* ii_a = nullptr;   // work items in scheduling order
   const uint32_t* items = nullptr;
@@ -556,13 +559,7 @@ lgs_status w_alloc_front(Work* W) {
   W->d_fo = (ViewImages*)w_alloc(W, sizeof(ViewImages) * V * G, ok);
   W->d_tgt = (ViewImages*)w_alloc(W, sizeof(ViewImages) * V * G, ok);
   W->d_lossw = (float*)w_alloc(W, 16 * G, ok);
-  for (int gi = 1; gi < G; ++gi)
-    W->app_g.push_back(w_alloc(W, (size_t)std::max<int64_t>(W->n, 1) * (W->app_bf16 ? 40 : 80), ok));
-  if (G > 1) {
-    W->scratch_img = (float*)w_alloc(W, sizeof(float) * 5 * npix, ok);
-    W->zero_img = (float*)w_alloc(W, sizeof(float) * 4 * npix, ok);
-    if (ok && hipMemsetAsync(W->zero_img, 0, sizeof(float) * 4 * npix, W->stream) != hipSuccess) ok = false;
-  }
+  if (G > 1) W->scratch_img = (float*)w_alloc(W, sizeof(float) * 5 * npix, ok);
   W->geom = (GeomRec*)w_alloc(W, sizeof(GeomRec) * n_rid, ok);
   W->cnt_t = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->cnt_b = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
@@ -577,13 +574,18 @@ lgs_status w_alloc_front(Work* W) {
   W->dkey = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->dk0 = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
   W->dk1 = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->app = w_alloc(W, (size_t)std::max<int64_t>(W->n, 1) * (W->app_bf16 ? 40 : 80), ok);
+  W->app_stride = (std::max<int64_t>(W->n, 1) * (W->app_bf16 ? 40 : 80) + 255) / 256 * 256;
+  W->app = w_alloc(W, (size_t)W->app_stride * G, ok);
   W->counters = (Counters*)w_alloc(W, sizeof(Counters), ok);
   W->last_idx = (int32_t*)w_alloc(W, 4 * npix, ok);
   W->T_state = (float*)w_alloc(W, 4 * npix, ok);
   W->scan_tmp = w_alloc(W, scan_temp_bytes(n_rid), ok);
   W->radix_small = w_alloc(W, radix_temp_bytes(n_rid, kSmallIds), ok);
-  W->ranges = (uint2*)w_alloc(W, 8 * std::max<int64_t>(W->plan.n_tiles, 1), ok);
+  // the tile ranges and the forward's work counters, cleared together
+  W->range_words = (2 * W->plan.n_tiles + kLineWords - 1) / kLineWords * kLineWords + (int64_t)G * kQueueWords;
+  W->ranges = (uint2*)w_alloc(W, 4 * W->range_words, ok);
+  W->work_q = (uint32_t*)W->ranges + (W->range_words - (int64_t)G * kQueueWords);
+  W->work_qb = (uint32_t*)w_alloc(W, 4 * (size_t)G * kQueueWords, ok);
   const int64_t ni = std::max<int64_t>(W->plan.n_items, 1);
   W->ii_a = (uint32_t*)w_alloc(W, 4 * ni, ok);
   W->items_static = get_items(W->ctx, W->plan, W->st.tile, W->st.order == 2);
@@ -605,27 +607,43 @@ lgs_status w_alloc_pairs(Work* W, int64_t cap_pairs, int64_t cap_slots) {
   return LGS_OK;
 }
 
+constexpr int64_t kGroupBytes = 1ll << 31;
+
 lgs_status w_alloc_bwd(Work* W) {
   if (W->bwd_alloc) return LGS_OK;
   bool ok = true;
-  const int64_t S = std::max<int64_t>(W->cap_slots, 1);
-  W->partials = (float*)w_alloc(W, sizeof(float) * kSlotFloats * S, ok);
-  W->mask = (uint8_t*)w_alloc(W, S + 8, ok);
-  W->grad2d = (float*)w_alloc(W, sizeof(float) * kPartials * std::max<int64_t>(W->n_rid, 1), ok);
+  const int64_t S = std::max<int64_t>(W->cap_slots, 1), R = std::max<int64_t>(W->n_rid, 1);
+  // as many feature groups at once as keep their records within 2 GB (a frame
+  // large enough to pass that fills the chip with one)
+  W->gb = (int)std::min<int64_t>(W->G, std::max<int64_t>(1, kGroupBytes / (4 * (S * kSlotFloats + R * kPartials))));
+  W->grad2d_stride = R * kPartials;
+  W->mask_stride = (S + 8 + 255) / 256 * 256;
+  W->partials = (float*)w_alloc(W, sizeof(float) * kSlotFloats * S * W->gb, ok);
+  W->mask = (uint8_t*)w_alloc(W, W->mask_stride * W->gb, ok);
+  W->grad2d = (float*)w_alloc(W, sizeof(float) * W->grad2d_stride * W->gb, ok);
   W->ttmp = w_alloc(W, project_bwd_temp_bytes(W->n_rid, (int)W->plan.views.size()), ok);
-  if (W->G > 1) {
-    W->grad2d_g = (float*)w_alloc(W, sizeof(float) * kPartials * std::max<int64_t>(W->n_rid, 1), ok);
-    W->geo_acc = (float*)w_alloc(W, sizeof(float) * 6 * std::max<int64_t>(W->n_rid, 1), ok);
-  }
+  if (W->gb < W->G) W->geo_acc = (float*)w_alloc(W, sizeof(float) * 6 * R, ok);
   if (!ok) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (backward)");
   // the slot mask starts at zero (the first backward clears it, together with
   // its counters); every reduction leaves it at zero again
-  W->mask_words = (S + 8 + 3) / 4;
+  W->mask_words = W->mask_stride * W->gb / 4;
   W->bwd_alloc = true;
   return LGS_OK;
 }
 
 int64_t view_plane(const Work* W, int v) { return (int64_t)W->plan.views[v].W * W->plan.views[v].H; }
+
+// zero RGB / depth upstream of the groups beyond the first, where a backward
+// is given its upstream
+lgs_status w_zero_img(Work* W) {
+  if (W->G == 1 || W->zero_img) return LGS_OK;
+  bool ok = true;
+  const size_t n = 4 * (size_t)std::max<int64_t>(W->plan.n_pix, 1);
+  W->zero_img = (float*)w_alloc(W, sizeof(float) * n, ok);
+  if (!ok) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (backward)");
+  launch_fill_u32((uint32_t*)W->zero_img, 0u, (int64_t)n, W->stream);
+  return LGS_OK;
+}
 
 // Per-group tables, [group][view], from the callers' images: group g reads or
 // writes feature planes 16 g ... of each view's feature image.
@@ -681,7 +699,7 @@ lgs_status w_upload(Work* W, const lgs_images* out, hipStream_t stream) {
 
 // projection .. slot bases: everything up to the pair / slot counts
 void enqueue_front(Work* W, const lgs_gaussians* g, hipStream_t s) {
-  const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D, 0);
+  const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D);
   const int V = (int)W->plan.views.size();
   const int64_t n_rid = W->n_rid;
   launch_project(ds, W->d_views, V, g->means, g->log_scales, g->quats, g->opacity_logits, g->rgb, g->feat,
@@ -706,17 +724,14 @@ void enqueue_front(Work* W, const lgs_gaussians* g, hipStream_t s) {
   slots.cp.n_big = &W->counters->n_long;
   slots.cp.big_min = kLongSlots;
   launch_gather_scans(pairs, slots, &W->counters->n_visible, n_rid, W->scan_tmp, s);
-  const size_t esz = W->app_bf16 ? 2 : 4;
-  for (int gi = 1; gi < W->G; ++gi)
-    launch_pack_app_group((const char*)g->feat + esz * (size_t)kFeatGroup * gi * (size_t)W->n,
-                          group_nfeat(W->D, gi), W->app_bf16, W->n, W->app_g[gi - 1], s);
+  launch_pack_app_groups(g->feat, W->app_bf16, W->n, W->G, W->app, W->app_stride, s);
 }
 
 // emission, tile sort, tile ranges, work order (capacity-bounded)
 void enqueue_pairs(Work* W, hipStream_t s) {
   const Plan& P = W->plan;
   launch_emit(W->geom, W->d_views, W->srid, W->off_t, W->counters, W->cap_pairs, W->cap_slots, W->npad_shift,
-              P.tile_shift, W->k0, W->v0, (uint32_t*)W->ranges, 2 * P.n_tiles, s);
+              P.tile_shift, W->k0, W->v0, (uint32_t*)W->ranges, W->range_words, s);
   const int tile_bits = std::max<int>(1, (int)ceil_log2((uint64_t)P.n_tiles));
   bool alt = false;
   radix_sort_u32(W->k0, W->v0, W->k1, W->v1, &W->counters->n_pairs_eff, std::max<int64_t>(W->cap_pairs, 1),
@@ -732,75 +747,93 @@ void enqueue_pairs(Work* W, hipStream_t s) {
     W->items = W->items_static;
 }
 
-// group 0 (RGB, depth, features 0..15), then each further feature group
-// over the same lists (its RGB / depth / T outputs go to scratch)
+Groups groups_of(const Work* W) {
+  Groups gr;
+  gr.count = gr.total = W->G;
+  gr.n_views = (int)W->plan.views.size();
+  gr.app_stride = W->app_stride;
+  gr.slots = std::max<int64_t>(W->cap_slots, 1);
+  gr.mask_stride = W->mask_stride;
+  return gr;
+}
+
+// every feature group over the same lists, at once: group 0 (RGB, depth,
+// features 0..15) and the further ones (their RGB / depth / T outputs go to
+// scratch).  A small frame has fewer blocks than the chip has wave slots: four
+// groups of 320 x 240 took 4 x 58 us one after the other, 84 at once, and their
+// backwards 4 x 73 and 139.
 void enqueue_raster_fwd(Work* W, hipStream_t s) {
-  const int V = (int)W->plan.views.size();
-  for (int gi = 0; gi < W->G; ++gi) {
-    const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D, gi);
-    if (gi > 0) launch_fill_u32(W->counters->work_q, 0u, kQueues * kLineWords, s);
-    launch_raster_fwd(ds, W->d_views, W->d_out + (size_t)gi * V, W->ranges, W->pvals, W->geom,
-                      gi == 0 ? W->app : W->app_g[gi - 1], W->app_bf16, (uint32_t)((1ull << W->npad_shift) - 1),
-                      W->items, W->items_static + W->plan.n_items, W->plan.n_items, W->counters, W->st.chunk,
-                      W->last_idx, W->T_state, gi == 0 && W->want_ncon, s);
-  }
-}
-
-// Backward compositing of one feature group; upstream by mode (UpMode):
-// d_up; dL1/dY from (d_fo, d_tgt, d_lossw); or colour channels from d_up and
-// depth + features from the L1 residual.
-// The slot mask is cleared by the first backward over it; from then on the
-// reduction clears each byte it reads.  The first group's launch also zeroes
-// the backward's work counts.
-void launch_group_bwd(Work* W, int gi, int mode, bool first, hipStream_t s) {
-  const int V = (int)W->plan.views.size();
-  const bool sign = mode != UP_EXPLICIT;
-  const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D, gi);
-  ZeroRanges z;
-  z.p[0] = W->counters->work_qb;
-  z.n[0] = kQueues * kLineWords;
-  if (first) {
-    z.p[1] = (uint32_t*)&W->counters->bwd_evals;   // bwd_evals, _contrib, _entries, _written
-    z.n[1] = 8;
-    z.p[2] = (uint32_t*)W->mask;
-    z.n[2] = W->mask_words;
-    W->mask_words = 0;
-  }
-  launch_zero(z, s);
-  if (gi == 0 && W->G == 1) w_mark(W, 5, s);   // one group: the stage is the kernel alone
-  launch_raster_bwd(mode, ds, W->d_views, W->d_up + (size_t)gi * V, sign ? W->d_fo + (size_t)gi * V : nullptr,
-                    sign ? W->d_tgt + (size_t)gi * V : nullptr, sign ? W->d_lossw + 4 * gi : nullptr, W->ranges,
-                    W->pvals, W->geom, gi == 0 ? W->app : W->app_g[gi - 1], W->app_bf16,
+  const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D);
+  launch_raster_fwd(ds, groups_of(W), W->d_views, W->d_out, W->ranges, W->pvals, W->geom, W->app, W->app_bf16,
                     (uint32_t)((1ull << W->npad_shift) - 1), W->items, W->items_static + W->plan.n_items,
-                    W->plan.n_items, W->counters, W->st.chunk,
-                    W->last_idx, W->T_state, W->slot_base, W->partials, W->mask, s);
+                    W->plan.n_items, W->counters, W->work_q, W->st.chunk, W->last_idx, W->T_state, W->want_ncon, s);
 }
 
-// Feature groups 1 .. first (each: compositing backward, per-Gaussian
-// reduction, its geometric partials accumulated, its feature gradients
-// written), then group 0's compositing backward; its reduction and the
-// projection backward follow in enqueue_backward_reduce.
-void enqueue_backward_raster(Work* W, const lgs_grads* gr, int mode, hipStream_t s) {
-  const int V = (int)W->plan.views.size();
+// Backward compositing: the feature groups in the order 1 .., 0, W->gb at a
+// time; upstream by mode (UpMode): d_up; dL1/dY from (d_fo, d_tgt, d_lossw); or
+// colour channels from d_up and depth + features from the L1 residual.  Each
+// batch of groups but the last is reduced per Gaussian, its feature gradients
+// written and its geometric sums accumulated here; the last one's reduction and
+// the projection backward follow in enqueue_backward_reduce.
+// The slot mask is cleared by the first backward over it; from then on the
+// reduction clears each byte it reads.
+Groups backward_groups(const Work* W, int at) {
+  Groups gr = groups_of(W);
+  gr.first = (1 + at) % W->G;
+  gr.count = std::min(W->gb, W->G - at);
+  return gr;
+}
+
+void enqueue_group_reduce(Work* W, const Groups& gr, const lgs_grads* out, hipStream_t s) {
+  launch_seg_reduce(gr, W->slot_off, W->partials, W->mask, W->long_ids, W->counters, W->n_rid, W->grad2d,
+                    W->grad2d_stride, s);
+  if (W->G > 1)
+    launch_group_feat_grad(gr, W->n, (uint32_t)W->npad_shift, W->counters, W->cnt_t, W->cidx, W->grad2d,
+                           W->grad2d_stride, out->feat, s);
+}
+
+void enqueue_backward_raster(Work* W, const lgs_grads* out, int mode, hipStream_t s) {
+  const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D);
+  const bool sign = mode != UP_EXPLICIT;
   if (W->G > 1) w_mark(W, 5, s);
-  for (int gi = 1; gi < W->G; ++gi) {
-    launch_group_bwd(W, gi, mode, gi == 1, s);
-    launch_seg_reduce(W->slot_off, W->partials, W->mask, W->long_ids, W->counters, W->n_rid, W->grad2d_g, s);
-    launch_group_geo_acc(W->grad2d_g, W->counters, W->n_rid, W->geo_acc, gi == 1, s);
-    launch_group_feat_grad(V, W->n, (uint32_t)W->npad_shift, W->counters, W->cnt_t, W->cidx, W->grad2d_g,
-                           group_nfeat(W->D, gi), gr->feat + (size_t)kFeatGroup * gi * (size_t)W->n, s);
+  ZeroRanges z;
+  z.p[0] = W->work_qb;
+  z.n[0] = (int64_t)W->G * kQueueWords;
+  z.p[1] = (uint32_t*)&W->counters->bwd_evals;   // bwd_evals, _contrib, _entries, _written
+  z.n[1] = 8;
+  z.p[2] = (uint32_t*)W->mask;
+  z.n[2] = W->mask_words;
+  W->mask_words = 0;
+  launch_zero(z, s);
+  if (W->G == 1) w_mark(W, 5, s);   // one group: the stage is the kernel alone
+  for (int at = 0; at < W->G; at += W->gb) {
+    const Groups gr = backward_groups(W, at);
+    launch_raster_bwd(mode, ds, gr, W->d_views, W->d_up, sign ? W->d_fo : nullptr, sign ? W->d_tgt : nullptr,
+                      sign ? W->d_lossw : nullptr, W->ranges, W->pvals, W->geom, W->app, W->app_bf16,
+                      (uint32_t)((1ull << W->npad_shift) - 1), W->items, W->items_static + W->plan.n_items,
+                      W->plan.n_items, W->counters, W->work_qb, W->st.chunk, W->last_idx, W->T_state, W->slot_base,
+                      W->partials, W->mask, s);
+    if (at + gr.count == W->G) break;
+    enqueue_group_reduce(W, gr, out, s);
+    launch_group_geo_acc(W->grad2d, W->grad2d_stride, gr.count, W->counters, W->n_rid, W->geo_acc, at == 0, s);
   }
-  launch_group_bwd(W, 0, mode, W->G == 1, s);
   w_mark(W, 6, s);
 }
 
 void enqueue_backward_reduce(Work* W, const lgs_gaussians* g, const lgs_grads* gr, hipStream_t s) {
-  const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D, 0);
+  const Settings ds = dev_settings(&W->st, W->plan.tile_shift, W->D);
   const int V = (int)W->plan.views.size();
-  launch_seg_reduce(W->slot_off, W->partials, W->mask, W->long_ids, W->counters, W->n_rid, W->grad2d, s);
-  if (W->G > 1) launch_group_geo_add(W->grad2d, W->counters, W->n_rid, W->geo_acc, s);
+  const int last = (W->G - 1) / W->gb * W->gb;
+  const Groups lg = backward_groups(W, last);
+  enqueue_group_reduce(W, lg, gr, s);
+  GroupGeo geo;   // group 0 is the batch's last
+  geo.acc = last > 0 ? W->geo_acc : nullptr;
+  geo.grad2d = W->grad2d;
+  geo.stride = W->grad2d_stride;
+  geo.n = lg.count - 1;
   launch_project_bwd(ds, W->d_views, V, g->means, g->log_scales, g->quats, g->opacity_logits, W->n,
-                     W->npad_shift, W->n_rid, W->counters, W->cnt_t, W->cidx, W->ent, W->grad2d, gr->means,
+                     W->npad_shift, W->n_rid, W->counters, W->cnt_t, W->cidx, W->ent, geo,
+                     W->grad2d + (lg.count - 1) * W->grad2d_stride, gr->means,
                      gr->log_scales, gr->quats, gr->opacity_logits, gr->rgb, gr->feat, gr->twist, W->ttmp, s);
   w_mark(W, 7, s);
 }
@@ -1032,6 +1065,7 @@ lgs_status lgs_backward(lgs_context* ctx, const lgs_fwd_state* Sc, const lgs_gau
   (void)hipGetLastError();   // launch checks below see only this call's errors
   W->stream = stream;
   if ((rc = w_alloc_bwd(W)) != LGS_OK) return rc;
+  if ((rc = w_zero_img(W)) != LGS_OK) return rc;
   const std::vector<ViewImages> hup = group_tables(W, grad_out, TAB_UP);
   HIP_TRY(ctx, upload_table(W, W->d_up, hup.data(), hup.size(), stream));
   enqueue_backward(W, g, grads, UP_EXPLICIT, stream);
@@ -1418,6 +1452,7 @@ lgs_status lgs_graph_create(lgs_context* ctx, const lgs_settings* st, const lgs_
       float* base = W->up_buf + 3 * (int64_t)W->plan.views[v].pix_off;
       gi[v] = lgs_images{base, nullptr, nullptr, nullptr, nullptr};
     }
+    if ((rc = w_zero_img(W)) != LGS_OK) return bail(rc);
     const std::vector<ViewImages> hu = group_tables(W, gi.data(), TAB_UP_RGB);
     std::vector<LossView> lv(n_views);
     int64_t n_df = 0;
