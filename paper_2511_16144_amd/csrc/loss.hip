@@ -15,13 +15,20 @@
 // (G the same window; it is symmetric, so correlation and convolution agree
 // and the zero-padded window is its own adjoint).  One work-group computes a
 // 32 x 32 output tile of one colour channel: it stages X and Y over the tile
-// plus two window radii in LDS, forms the five window sums with a horizontal
+// plus two window radii in LDS, forms four window sums (X, Y, XY, and X^2 + Y^2,
+// which the variances enter only together) with a horizontal
 // then a vertical pass (each thread slides along a row or a column, keeping
 // its inputs in registers), evaluates S and the three coefficient maps over
 // the tile plus one radius, filters those the same way, and writes the
-// gradient of the channel.  The depth and feature L1 terms are a separate
-// streaming kernel (16-byte accesses, several loads in flight per thread, no
-// LDS), so that neither kernel's resources limit the other's occupancy.
+// gradient of the channel.  The depth and feature L1 terms are a streaming pass
+// (16-byte accesses, several loads in flight per thread, no LDS).
+// What bounds them: the colour part its vector FP32 instructions (280 fused
+// multiply-adds per pixel and channel; without packed forms the chip issues
+// 39 T a second, 52 us for eight views of 640 x 480), the streaming part memory
+// (0.50 GB, 98 us at the rate of a large copy, of which the last-level cache
+// takes some: 60 us).  Colour: 98 -> 86 us with the tile's words requested
+// before the first is stored, -> 74 with four sums in place of five; both in
+// one launch of mixed work-groups: 135 -> 100 us, as their bounds differ.
 // Per-work-group sums of |I - I*|, S, |D - D*| and |F - F*| go to partial
 // arrays; a third kernel adds them per view in a fixed order (FP64), so the
 // loss values are deterministic.
@@ -41,11 +48,11 @@ constexpr int kPC = kLT + 1;
 constexpr int kLossThreads = 256;
 // One LDS region, reused stage by stage (a barrier between a stage's last
 // read of one array and the first write of the next): X, Y (2 x 52 x 53);
-// the five horizontal sums (5 x 52 x 43); the coefficient maps (3 x 42 x 43)
-// followed by their horizontal sums (3 x 42 x 33).  44.7 KB: three
+// the four horizontal sums (4 x 52 x 43); the coefficient maps (3 x 42 x 43)
+// followed by their horizontal sums (3 x 42 x 33).  38.3 KB: four
 // work-groups per CU.
 constexpr int kMax2(int a, int b) { return a > b ? a : b; }
-constexpr int kLdsFloats = kMax2(kMax2(2 * kLA * kPA, 5 * kLA * kPB), 3 * kLB * kPB + 3 * kLB * kPC);
+constexpr int kLdsFloats = kMax2(kMax2(2 * kLA * kPA, 4 * kLA * kPB), 3 * kLB * kPB + 3 * kLB * kPC);
 
 static_assert(kLT * kLT == 1024, "tile pixel index uses 10 bits");
 static_assert(kLossDfPixels == 256 * 8, "depth/feature kernel: 8 pixels per thread");
@@ -69,11 +76,10 @@ __device__ __forceinline__ void block_sum2(float& a, float& b, float* red) {
   b = (red[1] + red[3]) + (red[5] + red[7]);
 }
 
-__global__ __launch_bounds__(kLossThreads) void k_loss_rgb(const LossView* __restrict__ views, LossConsts k,
-                                                           float2* __restrict__ partials) {
-  __shared__ float lds[kLdsFloats];
-  __shared__ float red[8];
-  const int b = blockIdx.x, t = threadIdx.x;
+// colour: work-group b's tile and channel
+__device__ __forceinline__ void loss_rgb(const LossView* __restrict__ views, const LossConsts& k, int b, float* lds,
+                                         float* red, float2* __restrict__ partials) {
+  const int t = threadIdx.x;
   int v = 0;
   while (v + 1 < k.n_views && views[v + 1].blk_off <= b) ++v;
   const LossView V = views[v];
@@ -100,76 +106,87 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_rgb(const LossView* __res
       // (A) X, Y over the tile plus 2 radii (zeros outside the image)
       float* sx = lds;
       float* sy = lds + kLA * kPA;
-      for (int e = t; e < kLA * kLA; e += kLossThreads) {
-        const int r = e / kLA, q = e - r * kLA;
+      // every word requested before the first is stored (unconditional loads at
+      // clamped positions)
+      constexpr int kStage = (kLA * kLA + kLossThreads - 1) / kLossThreads;
+      float xa[kStage], ya[kStage];
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) {
+        const int e = t + u * kLossThreads, r = e / kLA, q = e - r * kLA;
+        const int gy = min(max(y0 - 2 * kLR + r, 0), H - 1), gx = min(max(x0 - 2 * kLR + q, 0), W - 1);
+        const size_t o = (size_t)gy * W + gx;
+        xa[u] = X[o];
+        ya[u] = Y[o];
+      }
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) {
+        const int e = t + u * kLossThreads, r = e / kLA, q = e - r * kLA;
         const int gy = y0 - 2 * kLR + r, gx = x0 - 2 * kLR + q;
-        float a = 0.f, c = 0.f;
-        if (gy >= 0 && gy < H && gx >= 0 && gx < W) {
-          const size_t o = (size_t)gy * W + gx;
-          a = X[o];
-          c = Y[o];
+        const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
+        if (e < kLA * kLA) {
+          sx[r * kPA + q] = in ? xa[u] : 0.f;
+          sy[r * kPA + q] = in ? ya[u] : 0.f;
         }
-        sx[r * kPA + q] = a;
-        sy[r * kPA + q] = c;
       }
       __syncthreads();
-      // (B) horizontal window sums of X, Y, X^2, Y^2, XY: 52 rows x 42
+      // (B) horizontal window sums of X, Y, X^2 + Y^2, XY: 52 rows x 42
       // statistics columns; thread = (row, segment of 11 columns), walking
-      // its 21 inputs once (the three products per input, then 5 FMAs per
+      // its 21 inputs once (the products per input, then 4 FMAs per
       // tap); results stay in registers until every thread has read X, Y
-      float hb[11][5];
+      float hb[11][4];
       const int rb = t % kLA, segb = t / kLA;
       const int jb0 = min(segb * 11, kLB - 11);   // the last segment overlaps
       if (t < 4 * kLA) {
 #pragma unroll
         for (int o = 0; o < 11; ++o)
 #pragma unroll
-          for (int q = 0; q < 5; ++q) hb[o][q] = 0.f;
+          for (int q = 0; q < 4; ++q) hb[o][q] = 0.f;
 #pragma unroll
         for (int m = 0; m < 21; ++m) {
           const float a = sx[rb * kPA + jb0 + m], c = sy[rb * kPA + jb0 + m];
-          const float pv[5] = {a, c, a * a, c * c, a * c};
+          const float pv[4] = {a, c, fmaf(a, a, c * c), a * c};
 #pragma unroll
           for (int o = 0; o < 11; ++o) {
             const int tap = m - o;
             if (tap >= 0 && tap < kLTaps) {
 #pragma unroll
-              for (int q = 0; q < 5; ++q) hb[o][q] = fmaf(k.w[tap], pv[q], hb[o][q]);
+              for (int q = 0; q < 4; ++q) hb[o][q] = fmaf(k.w[tap], pv[q], hb[o][q]);
             }
           }
         }
       }
       __syncthreads();   // X, Y are dead: the sums take their place
-      float* h5 = lds;
+      float* hs = lds;
       if (t < 4 * kLA) {
 #pragma unroll
         for (int o = 0; o < 11; ++o)
 #pragma unroll
-          for (int q = 0; q < 5; ++q) h5[(q * kLA + rb) * kPB + jb0 + o] = hb[o][q];
+          for (int q = 0; q < 4; ++q) hs[(q * kLA + rb) * kPB + jb0 + o] = hb[o][q];
       }
       __syncthreads();
       // (C) vertical sums -> local statistics over the 42 x 42 statistics
       // region; SSIM and its three coefficient maps (zero outside the image),
       // written over the sums once every thread has read them
-      float st5[7][5];
+      float st[7][4];
       const int jc = t % kLB, segc = t / kLB;
       const int ic0 = segc * 7;
       if (t < 6 * kLB) {
 #pragma unroll
         for (int o = 0; o < 7; ++o)
 #pragma unroll
-          for (int q = 0; q < 5; ++q) st5[o][q] = 0.f;
+          for (int q = 0; q < 4; ++q) st[o][q] = 0.f;
 #pragma unroll
         for (int ii = 0; ii < 17; ++ii) {
-          float val[5];
+          float val[4];
 #pragma unroll
-          for (int q = 0; q < 5; ++q) val[q] = h5[(q * kLA + ic0 + ii) * kPB + jc];
+          for (int q = 0; q < 4; ++q) val[q] = hs[(q * kLA + ic0 + ii) * kPB + jc];
 #pragma unroll
           for (int o = 0; o < 7; ++o) {
             const int tap = ii - o;
             if (tap >= 0 && tap < kLTaps) {
 #pragma unroll
-              for (int q = 0; q < 5; ++q) st5[o][q] = fmaf(k.w[tap], val[q], st5[o][q]);
+              for (int q = 0; q < 4; ++q) st[o][q] = fmaf(k.w[tap], val[q], st[o][q]);
             }
           }
         }
@@ -184,10 +201,10 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_rgb(const LossView* __res
           const int i = ic0 + o, gy = y0 - kLR + i;
           float ca = 0.f, cb = 0.f, cc = 0.f;
           if (gy >= 0 && gy < H && gx >= 0 && gx < W) {
-            const float mx = st5[o][0], my = st5[o][1];
-            const float vx = st5[o][2] - mx * mx, vy = st5[o][3] - my * my, cxy = st5[o][4] - mx * my;
+            const float mx = st[o][0], my = st[o][1];
+            const float vxy = st[o][2] - fmaf(mx, mx, my * my), cxy = st[o][3] - mx * my;   // var x + var y, cov
             const float A1 = 2.f * mx * my + k.c1, A2 = 2.f * cxy + k.c2;
-            const float B1 = mx * mx + my * my + k.c1, B2 = vx + vy + k.c2;
+            const float B1 = mx * mx + my * my + k.c1, B2 = vxy + k.c2;
             // B1 >= C1 and B2 >= C2 (up to rounding of the variances): normal
             // positive numbers, for which the hardware reciprocal is within 1 ulp
             const float rB1 = __builtin_amdgcn_rcpf(B1), rB2 = __builtin_amdgcn_rcpf(B2), iB = rB1 * rB2;
@@ -275,10 +292,9 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_rgb(const LossView* __res
 // and loads four channels ahead before it computes and stores them.
 constexpr int kDfGroup = 4;
 
-__global__ __launch_bounds__(256) void k_loss_df(const LossView* __restrict__ views, int n_views,
-                                                 float2* __restrict__ partials) {
-  __shared__ float red[8];
-  const int b = blockIdx.x, t = threadIdx.x;
+__device__ __forceinline__ void loss_df(const LossView* __restrict__ views, int n_views, int b, float* red,
+                                        float2* __restrict__ partials) {
+  const int t = threadIdx.x;
   int v = 0;
   while (v + 1 < n_views && views[v + 1].df_off <= b) ++v;
   const LossView V = views[v];
@@ -360,6 +376,28 @@ __global__ __launch_bounds__(256) void k_loss_df(const LossView* __restrict__ vi
   if (t == 0) partials[b] = make_float2(acc0, acc1);
 }
 
+__global__ __launch_bounds__(kLossThreads) void k_loss_rgb(const LossView* __restrict__ views, LossConsts k,
+                                                           float2* __restrict__ partials) {
+  __shared__ float lds[kLdsFloats];
+  __shared__ float red[8];
+  loss_rgb(views, k, (int)blockIdx.x, lds, red, partials);
+}
+
+// Both, in one launch: the colour work-groups are bound by their vector
+// instructions and the depth / feature ones by memory, so the two are mixed
+// evenly over the grid (df work-group i is the first whose share of nd reaches
+// i + 1).
+__global__ __launch_bounds__(kLossThreads) void k_loss(const LossView* __restrict__ views, LossConsts k, uint32_t nb,
+                                                       uint32_t nd, float2* __restrict__ part_rgb,
+                                                       float2* __restrict__ part_df) {
+  __shared__ float lds[kLdsFloats];
+  __shared__ float red[8];
+  const uint64_t b = blockIdx.x, n = nb + nd;
+  const uint32_t before = (uint32_t)(b * nd / n);   // df work-groups before this one
+  if ((uint32_t)((b + 1) * nd / n) > before) loss_df(views, k.n_views, (int)before, red, part_df);
+  else loss_rgb(views, k, (int)(b - before), lds, red, part_rgb);
+}
+
 // Per view: the four loss terms from the work-groups' partial sums, added in
 // a fixed order in FP64.
 __global__ __launch_bounds__(256) void k_loss_terms(const LossView* __restrict__ views, int ssim,
@@ -413,9 +451,11 @@ void launch_loss_rgb(const LossView* views, const LossConsts& k, int64_t n_block
     hipLaunchKernelGGL(k_loss_rgb, dim3((unsigned)n_blocks), dim3(kLossThreads), 0, s, views, k, partials);
 }
 
-void launch_loss_df(const LossView* views, int n_views, int64_t n_blocks, float2* partials, hipStream_t s) {
-  if (n_blocks > 0)
-    hipLaunchKernelGGL(k_loss_df, dim3((unsigned)n_blocks), dim3(256), 0, s, views, n_views, partials);
+void launch_loss(const LossView* views, const LossConsts& k, int64_t n_rgb, int64_t n_df, float2* part_rgb,
+                 float2* part_df, hipStream_t s) {
+  if (n_rgb + n_df > 0)
+    hipLaunchKernelGGL(k_loss, dim3((unsigned)(n_rgb + n_df)), dim3(kLossThreads), 0, s, views, k, (uint32_t)n_rgb,
+                       (uint32_t)n_df, part_rgb, part_df);
 }
 
 void launch_loss_terms(const LossView* views, int n_views, int ssim, const float2* part_rgb,
