@@ -221,8 +221,11 @@ def gaussians_c(means, log_scales, quats, logits, rgb, feat) -> lgs_gaussians:
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    # the current device's current stream, as torch.cuda.current_stream()
+    # gives it (whose stream object takes 10 us to make)
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 class Context:

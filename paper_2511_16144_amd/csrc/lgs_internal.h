@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <atomic>
+
 namespace lgs {
 
 // Pixel blocks are 8x8: one wave64 renders one block, one pixel per lane.
@@ -97,6 +99,29 @@ struct Settings {
 constexpr int kQueues = 8;
 
 constexpr int kLineWords = 32;   // one 128-byte line per queue counter
+
+// Work-groups of a kernel that the current device holds at once: asked of the
+// runtime once per device and work-group size (one slot of the kernel's own
+// table each; the answer never changes).
+struct Residency {
+  static constexpr int kDevices = 16, kSizes = 5;   // 64 << size threads
+  std::atomic<int> groups[kDevices][kSizes] = {};
+};
+template <class F>
+int64_t resident_groups(Residency& known, F kernel, int threads, size_t lds) {
+  int dev = 0, size = 0;
+  (void)hipGetDevice(&dev);
+  while ((64 << size) < threads) ++size;
+  const bool keep = dev >= 0 && dev < Residency::kDevices && size < Residency::kSizes && (64 << size) == threads;
+  if (keep)
+    if (const int n = known.groups[dev][size].load(std::memory_order_relaxed)) return n;
+  int cus = 256, occ = 1;
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, lds);
+  const int n = cus * (occ > 0 ? occ : 1);
+  if (keep) known.groups[dev][size].store(n, std::memory_order_relaxed);
+  return n;
+}
 
 struct __attribute__((aligned(128))) Counters {
   uint32_t n_visible;   // M

@@ -662,11 +662,8 @@ void launch_project_bwd(const Settings& st, const ViewDesc* views, int n_views, 
   const int64_t nblk = (std::max<int64_t>(n_rid, 1) + 63) / 64;
   float* contrib = (float*)temp;
   double* tpart = (double*)((char*)temp + (size_t)nblk * 64 * 16 * sizeof(float));
-  int dev = 0, cus = 256, occ = 1;
-  (void)hipGetDevice(&dev);
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_project_bwd_view, 256, 0);
-  int64_t grid = (int64_t)cus * (occ > 0 ? occ : 1);
+  static Residency known;
+  int64_t grid = resident_groups(known, k_project_bwd_view, 256, 0);
   const int64_t need = (nblk + 3) / 4;   // four waves (blocks of 64 c) per work-group
   if (grid > need) grid = need;
   hipLaunchKernelGGL(k_project_bwd_view, dim3((unsigned)grid), dim3(256), 0, s, st, views, means, log_scales,

@@ -1210,13 +1210,9 @@ static void launch_fwd_t(const Settings& st, const Groups& gr, const ViewDesc* v
                          const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt,
                          uint32_t* work_q, int waves_per_group, int32_t* last_idx, float* T_state, hipStream_t s) {
   const int threads = 64 * waves_per_group;
-  int dev = 0, cus = 256;
-  hipGetDevice(&dev);
-  hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  int occ = 1;
   const size_t lds = BF16 ? (size_t)waves_per_group * kFwdWaveLds : 0;
-  hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_raster_fwd<BF16, CNT, NC>, threads, lds);
-  int64_t grid = (int64_t)cus * (occ > 0 ? occ : 1);
+  static Residency known;
+  int64_t grid = resident_groups(known, k_raster_fwd<BF16, CNT, NC>, threads, lds);
   const int64_t need = (n_items + waves_per_group - 1) / waves_per_group;
   if (grid > need) grid = need;
   if (grid < kQueues) grid = kQueues;   // every queue needs a workgroup (index mod kQueues) to drain it
@@ -1257,12 +1253,8 @@ static void launch_bwd_t(const Settings& st, const Groups& gr, const ViewDesc* v
                          const uint32_t* slot_base, float* partials, uint8_t* mask, hipStream_t s) {
   const int threads = 64 * waves_per_group;
   const size_t lds = kBasisBytes + (size_t)waves_per_group * bwd_wave_lds(UPM);
-  int dev = 0, cus = 256;
-  hipGetDevice(&dev);
-  hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  int occ = 1;
-  hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_raster_bwd<BF16, UPM, CNT>, threads, lds);
-  int64_t grid = (int64_t)cus * (occ > 0 ? occ : 1);
+  static Residency known;
+  int64_t grid = resident_groups(known, k_raster_bwd<BF16, UPM, CNT>, threads, lds);
   const int64_t need = (n_items + waves_per_group - 1) / waves_per_group;
   if (grid > need) grid = need;
   if (grid < kQueues) grid = kQueues;   // every queue needs a workgroup (index mod kQueues) to drain it
@@ -1302,11 +1294,8 @@ void launch_seg_reduce(const Groups& gr, const uint32_t* slot_off, const float* 
                        const uint32_t* long_ids, const Counters* cnt, int64_t n_max, float* grad2d, int64_t stride,
                        hipStream_t s) {
   if (n_max <= 0) return;
-  int dev = 0, cus = 256, occ = 1;
-  hipGetDevice(&dev);
-  hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_seg_reduce, 256, 0);
-  int64_t grid = (int64_t)cus * (occ > 0 ? occ : 1);
+  static Residency known;
+  int64_t grid = resident_groups(known, k_seg_reduce, 256, 0);
   const int64_t need = (n_max + 7) / 8;   // two visible ids per wave
   if (grid > need) grid = need;
   hipLaunchKernelGGL(k_seg_reduce, dim3((unsigned)grid, gr.count), dim3(256), 0, s, gr, slot_off, partials, mask, long_ids, cnt,

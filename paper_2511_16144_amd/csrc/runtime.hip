@@ -59,7 +59,8 @@ struct lgs_context {
   // lgs_decoder_l1 workspace: per-work-group partial sums
   float* dec_part = nullptr;
   int64_t dec_part_cap = 0;
-  // pinned staging of lgs_prune's readback
+  // pinned staging of the readbacks: a step's counters, lgs_prune's
+  lgs::Counters* counts_host = nullptr;
   lgs::PruneCounters* prune_host = nullptr;
   // device address of this GPU's copy of the fixed scratch array used by
   // lgs_decoder_l1_noalloc
@@ -496,14 +497,55 @@ void w_release(Work* W) {
     }
 }
 
-// Asynchronous copy of a host table to the device; the host copy is kept
-// with the Work (then with the context until the copy has surely run).
-template <class T>
-hipError_t upload_table(Work* W, void* dst, const T* src, size_t count, hipStream_t s) {
-  if (count == 0) return hipSuccess;
-  W->host_keep.emplace_back((const char*)src, (const char*)(src + count));
+// Buffers of a Work that share one block of the pool, each on a 256-byte line.
+class Carve {
+ public:
+  template <class T>
+  void add(T*& p, size_t bytes) {
+    parts_.push_back({(void*)&p, total_});
+    total_ += (bytes + 255) / 256 * 256;
+  }
+  bool get(Work* W) {
+    bool ok = true;
+    char* base = (char*)w_alloc(W, total_, ok);
+    for (const Part& x : parts_) {
+      char* at = ok ? base + x.off : nullptr;
+      memcpy(x.p, &at, sizeof at);
+    }
+    return ok;
+  }
+
+ private:
+  struct Part {
+    void* p;   // the pointer to set
+    size_t off;
+  };
+  std::vector<Part> parts_;
+  size_t total_ = 0;
+};
+
+// Asynchronous copy of host tables to device buffers that follow one another
+// in one block, as one copy; the host copy is kept with the Work (then with
+// the context until the copy has surely run).
+struct Table {
+  void* dst;
+  const void* src;
+  size_t bytes;
+};
+hipError_t upload_tables(Work* W, std::initializer_list<Table> tables, hipStream_t s) {
+  char* const base = (char*)tables.begin()->dst;
+  const Table& last = *(tables.end() - 1);
+  std::vector<char> host((char*)last.dst + last.bytes - base);
+  for (const Table& t : tables)
+    if (t.bytes) memcpy(host.data() + ((char*)t.dst - base), t.src, t.bytes);
+  if (host.empty()) return hipSuccess;
+  W->host_keep.push_back(std::move(host));
   const std::vector<char>& b = W->host_keep.back();
-  return hipMemcpyAsync(dst, b.data(), b.size(), hipMemcpyHostToDevice, s);
+  return hipMemcpyAsync(base, b.data(), b.size(), hipMemcpyHostToDevice, s);
+}
+template <class T>
+Table table(void* dst, const std::vector<T>& v) {
+  return Table{dst, v.data(), v.size() * sizeof(T)};
 }
 
 void w_mark(Work* W, int i, hipStream_t s) {
@@ -549,61 +591,62 @@ lgs_status w_init(Work* W, lgs_context* ctx, const lgs_settings* st, const lgs_g
 
 // buffers whose size does not depend on the pair count
 lgs_status w_alloc_front(Work* W) {
-  bool ok = true;
+  Carve block;
   const int V = (int)W->plan.views.size();
   const int64_t n_rid = W->n_rid, npix = std::max<int64_t>(W->plan.n_pix, 1);
-  W->d_views = (ViewDesc*)w_alloc(W, sizeof(ViewDesc) * V, ok);
+  // (uploaded together: views and out; fo, tgt and lossw)
+  block.add(W->d_views, sizeof(ViewDesc) * V);
   const int G = W->G;
-  W->d_out = (ViewImages*)w_alloc(W, sizeof(ViewImages) * V * G, ok);
-  W->d_up = (ViewImages*)w_alloc(W, sizeof(ViewImages) * V * G, ok);
-  W->d_fo = (ViewImages*)w_alloc(W, sizeof(ViewImages) * V * G, ok);
-  W->d_tgt = (ViewImages*)w_alloc(W, sizeof(ViewImages) * V * G, ok);
-  W->d_lossw = (float*)w_alloc(W, 16 * G, ok);
-  if (G > 1) W->scratch_img = (float*)w_alloc(W, sizeof(float) * 5 * npix, ok);
-  W->geom = (GeomRec*)w_alloc(W, sizeof(GeomRec) * n_rid, ok);
-  W->cnt_t = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->cnt_b = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->cidx = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->slot_base = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->ent = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->ent_a = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->ent_b = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->off_t = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->slot_off = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->long_ids = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->dkey = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->dk0 = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
-  W->dk1 = (uint32_t*)w_alloc(W, 4 * n_rid, ok);
+  block.add(W->d_out, sizeof(ViewImages) * V * G);
+  block.add(W->d_up, sizeof(ViewImages) * V * G);
+  block.add(W->d_fo, sizeof(ViewImages) * V * G);
+  block.add(W->d_tgt, sizeof(ViewImages) * V * G);
+  block.add(W->d_lossw, 16 * G);
+  if (G > 1) block.add(W->scratch_img, sizeof(float) * 5 * npix);
+  block.add(W->geom, sizeof(GeomRec) * n_rid);
+  block.add(W->cnt_t, 4 * n_rid);
+  block.add(W->cnt_b, 4 * n_rid);
+  block.add(W->cidx, 4 * n_rid);
+  block.add(W->slot_base, 4 * n_rid);
+  block.add(W->ent, 4 * n_rid);
+  block.add(W->ent_a, 4 * n_rid);
+  block.add(W->ent_b, 4 * n_rid);
+  block.add(W->off_t, 4 * n_rid);
+  block.add(W->slot_off, 4 * n_rid);
+  block.add(W->long_ids, 4 * n_rid);
+  block.add(W->dkey, 4 * n_rid);
+  block.add(W->dk0, 4 * n_rid);
+  block.add(W->dk1, 4 * n_rid);
   W->app_stride = (std::max<int64_t>(W->n, 1) * (W->app_bf16 ? 40 : 80) + 255) / 256 * 256;
-  W->app = w_alloc(W, (size_t)W->app_stride * G, ok);
-  W->counters = (Counters*)w_alloc(W, sizeof(Counters), ok);
-  W->last_idx = (int32_t*)w_alloc(W, 4 * npix, ok);
-  W->T_state = (float*)w_alloc(W, 4 * npix, ok);
-  W->scan_tmp = w_alloc(W, scan_temp_bytes(n_rid), ok);
-  W->radix_small = w_alloc(W, radix_temp_bytes(n_rid, kSmallIds), ok);
+  block.add(W->app, (size_t)W->app_stride * G);
+  block.add(W->counters, sizeof(Counters));
+  block.add(W->last_idx, 4 * npix);
+  block.add(W->T_state, 4 * npix);
+  block.add(W->scan_tmp, scan_temp_bytes(n_rid));
+  block.add(W->radix_small, radix_temp_bytes(n_rid, kSmallIds));
   // the tile ranges and the forward's work counters, cleared together
   W->range_words = (2 * W->plan.n_tiles + kLineWords - 1) / kLineWords * kLineWords + (int64_t)G * kQueueWords;
-  W->ranges = (uint2*)w_alloc(W, 4 * W->range_words, ok);
-  W->work_q = (uint32_t*)W->ranges + (W->range_words - (int64_t)G * kQueueWords);
-  W->work_qb = (uint32_t*)w_alloc(W, 4 * (size_t)G * kQueueWords, ok);
+  block.add(W->ranges, 4 * W->range_words);
+  block.add(W->work_qb, 4 * (size_t)G * kQueueWords);
   const int64_t ni = std::max<int64_t>(W->plan.n_items, 1);
-  W->ii_a = (uint32_t*)w_alloc(W, 4 * ni, ok);
+  block.add(W->ii_a, 4 * ni);
   W->items_static = get_items(W->ctx, W->plan, W->st.tile, W->st.order == 2);
-  if (!ok || !W->items_static) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed");
+  if (!block.get(W) || !W->items_static) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed");
+  W->work_q = (uint32_t*)W->ranges + (W->range_words - (int64_t)G * kQueueWords);
   return LGS_OK;
 }
 
 lgs_status w_alloc_pairs(Work* W, int64_t cap_pairs, int64_t cap_slots) {
-  bool ok = true;
+  Carve block;
   W->cap_pairs = cap_pairs;
   W->cap_slots = cap_slots;
   const int64_t pa = std::max<int64_t>(cap_pairs, 1);
-  W->k0 = (uint32_t*)w_alloc(W, 4 * pa, ok);
-  W->v0 = (uint32_t*)w_alloc(W, 4 * pa, ok);
-  W->k1 = (uint32_t*)w_alloc(W, 4 * pa, ok);
-  W->v1 = (uint32_t*)w_alloc(W, 4 * pa, ok);
-  W->radix_big = w_alloc(W, radix_temp_bytes(pa, kSmallPairs), ok);
-  if (!ok) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (pairs)");
+  block.add(W->k0, 4 * pa);
+  block.add(W->v0, 4 * pa);
+  block.add(W->k1, 4 * pa);
+  block.add(W->v1, 4 * pa);
+  block.add(W->radix_big, radix_temp_bytes(pa, kSmallPairs));
+  if (!block.get(W)) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (pairs)");
   return LGS_OK;
 }
 
@@ -611,19 +654,19 @@ constexpr int64_t kGroupBytes = 1ll << 31;
 
 lgs_status w_alloc_bwd(Work* W) {
   if (W->bwd_alloc) return LGS_OK;
-  bool ok = true;
+  Carve block;
   const int64_t S = std::max<int64_t>(W->cap_slots, 1), R = std::max<int64_t>(W->n_rid, 1);
   // as many feature groups at once as keep their records within 2 GB (a frame
   // large enough to pass that fills the chip with one)
   W->gb = (int)std::min<int64_t>(W->G, std::max<int64_t>(1, kGroupBytes / (4 * (S * kSlotFloats + R * kPartials))));
   W->grad2d_stride = R * kPartials;
   W->mask_stride = (S + 8 + 255) / 256 * 256;
-  W->partials = (float*)w_alloc(W, sizeof(float) * kSlotFloats * S * W->gb, ok);
-  W->mask = (uint8_t*)w_alloc(W, W->mask_stride * W->gb, ok);
-  W->grad2d = (float*)w_alloc(W, sizeof(float) * W->grad2d_stride * W->gb, ok);
-  W->ttmp = w_alloc(W, project_bwd_temp_bytes(W->n_rid, (int)W->plan.views.size()), ok);
-  if (W->gb < W->G) W->geo_acc = (float*)w_alloc(W, sizeof(float) * 6 * R, ok);
-  if (!ok) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (backward)");
+  block.add(W->partials, sizeof(float) * kSlotFloats * S * W->gb);
+  block.add(W->mask, W->mask_stride * W->gb);
+  block.add(W->grad2d, sizeof(float) * W->grad2d_stride * W->gb);
+  block.add(W->ttmp, project_bwd_temp_bytes(W->n_rid, (int)W->plan.views.size()));
+  if (W->gb < W->G) block.add(W->geo_acc, sizeof(float) * 6 * R);
+  if (!block.get(W)) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (backward)");
   // the slot mask starts at zero (the first backward clears it, together with
   // its counters); every reduction leaves it at zero again
   W->mask_words = W->mask_stride * W->gb / 4;
@@ -692,8 +735,7 @@ lgs_status w_upload(Work* W, const lgs_images* out, hipStream_t stream) {
   const std::vector<ViewImages> himg = group_tables(W, out, TAB_OUT);
   W->want_ncon = 0;
   for (int v = 0; v < V; ++v) W->want_ncon |= out[v].n_contrib != nullptr;
-  HIP_TRY(W->ctx, upload_table(W, W->d_views, W->plan.views.data(), (size_t)V, stream));
-  HIP_TRY(W->ctx, upload_table(W, W->d_out, himg.data(), himg.size(), stream));
+  HIP_TRY(W->ctx, upload_tables(W, {table(W->d_views, W->plan.views), table(W->d_out, himg)}, stream));
   return LGS_OK;
 }
 
@@ -844,8 +886,12 @@ void enqueue_backward(Work* W, const lgs_gaussians* g, const lgs_grads* gr, int 
 }
 
 lgs_status read_counts(Work* W, hipStream_t s, Counters* hc) {
-  HIP_TRY(W->ctx, hipMemcpyAsync(hc, W->counters, offsetof(Counters, pad2), hipMemcpyDeviceToHost, s));
-  HIP_TRY(W->ctx, hipStreamSynchronize(s));
+  lgs_context* ctx = W->ctx;
+  if (!ctx->counts_host)
+    HIP_TRY(ctx, hipHostMalloc((void**)&ctx->counts_host, sizeof(Counters), hipHostMallocDefault));
+  HIP_TRY(ctx, hipMemcpyAsync(ctx->counts_host, W->counters, offsetof(Counters, pad2), hipMemcpyDeviceToHost, s));
+  HIP_TRY(ctx, hipStreamSynchronize(s));
+  *hc = *ctx->counts_host;
   W->counts.n_visible = hc->n_visible;
   W->counts.n_pairs = hc->n_pairs;
   W->counts.n_slots = hc->n_slots;
@@ -967,6 +1013,7 @@ void lgs_context_destroy(lgs_context* ctx) {
   if (ctx->loss_part) hipFree(ctx->loss_part);
   if (ctx->loss_copied) hipEventDestroy(ctx->loss_copied);
   if (ctx->dec_part) hipFree(ctx->dec_part);
+  if (ctx->counts_host) hipHostFree(ctx->counts_host);
   if (ctx->prune_host) hipHostFree(ctx->prune_host);
   delete ctx;
 }
@@ -1067,7 +1114,7 @@ lgs_status lgs_backward(lgs_context* ctx, const lgs_fwd_state* Sc, const lgs_gau
   if ((rc = w_alloc_bwd(W)) != LGS_OK) return rc;
   if ((rc = w_zero_img(W)) != LGS_OK) return rc;
   const std::vector<ViewImages> hup = group_tables(W, grad_out, TAB_UP);
-  HIP_TRY(ctx, upload_table(W, W->d_up, hup.data(), hup.size(), stream));
+  HIP_TRY(ctx, upload_tables(W, {table(W->d_up, hup)}, stream));
   enqueue_backward(W, g, grads, UP_EXPLICIT, stream);
   HIP_TRY(ctx, hipGetLastError());
   return LGS_OK;
@@ -1097,9 +1144,7 @@ lgs_status lgs_backward_l1(lgs_context* ctx, const lgs_fwd_state* Sc, const lgs_
   if ((rc = w_alloc_bwd(W)) != LGS_OK) return rc;
   const std::vector<ViewImages> ho = group_tables(W, out, TAB_FO), ht = group_tables(W, targets, TAB_TGT);
   const std::vector<float> lw = group_lossw(W, loss_w);
-  HIP_TRY(ctx, upload_table(W, W->d_fo, ho.data(), ho.size(), stream));
-  HIP_TRY(ctx, upload_table(W, W->d_tgt, ht.data(), ht.size(), stream));
-  HIP_TRY(ctx, upload_table(W, W->d_lossw, lw.data(), lw.size(), stream));
+  HIP_TRY(ctx, upload_tables(W, {table(W->d_fo, ho), table(W->d_tgt, ht), table(W->d_lossw, lw)}, stream));
   enqueue_backward(W, g, grads, UP_L1, stream);
   HIP_TRY(ctx, hipGetLastError());
   return LGS_OK;
@@ -1434,9 +1479,7 @@ lgs_status lgs_graph_create(lgs_context* ctx, const lgs_settings* st, const lgs_
   {
     const std::vector<ViewImages> ho = group_tables(W, out, TAB_FO), ht = group_tables(W, targets, TAB_TGT);
     const std::vector<float> lw = group_lossw(W, loss_w);
-    if (upload_table(W, W->d_fo, ho.data(), ho.size(), stream) != hipSuccess ||
-        upload_table(W, W->d_tgt, ht.data(), ht.size(), stream) != hipSuccess ||
-        upload_table(W, W->d_lossw, lw.data(), lw.size(), stream) != hipSuccess)
+    if (upload_tables(W, {table(W->d_fo, ho), table(W->d_tgt, ht), table(W->d_lossw, lw)}, stream) != hipSuccess)
       return bail(fail(ctx, LGS_ERR_HIP, "upload failed"));
   }
   if (ssim_lambda != 0.f) {
@@ -1460,8 +1503,8 @@ lgs_status lgs_graph_create(lgs_context* ctx, const lgs_settings* st, const lgs_
     W->loss_part = (float2*)w_alloc(W, sizeof(float2) * std::max<int64_t>(W->loss_blocks, 1), ok);
     W->loss_k = loss_consts(ssim_lambda, n_views);
     if (!ok) return bail(fail(ctx, LGS_ERR_HIP, "device allocation failed (loss)"));
-    if (upload_table(W, W->loss_tab, lv.data(), lv.size(), stream) != hipSuccess ||
-        upload_table(W, W->d_up, hu.data(), hu.size(), stream) != hipSuccess)
+    if (upload_tables(W, {table(W->loss_tab, lv)}, stream) != hipSuccess ||
+        upload_tables(W, {table(W->d_up, hu)}, stream) != hipSuccess)
       return bail(fail(ctx, LGS_ERR_HIP, "upload failed"));
   }
   if (hipStreamCreateWithFlags(&G->cap_stream, hipStreamNonBlocking) != hipSuccess)
