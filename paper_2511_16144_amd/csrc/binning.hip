@@ -190,6 +190,188 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(ScanArgs first, Scan
 // reduce kernel must sum the same items as the down-sweep: both cover the
 // block's 2048 items, only the assignment to threads differs.
 
+// The lists of a small front end by one work-group of 16 waves, in LDS: ten
+// launches become one.  Thread t owns the ids 4 t .. 4 t + 3 in the scans.  The
+// depth sort is the radix sort's (stable, ranks from match masks, a wave's keys
+// contiguous), with the keys in LDS between four passes of 8 bits (three of 11
+// clear and scan eight times the counters: 21 us in place of 18 for 2000).  What
+// bounds it is one work-group's chain of loads, barriers and LDS accesses.
+// 2000 visible ids: 44 us and nine more launches -> 18 us (a captured step 134 ->
+// 109); 4000: 57 -> 28.  The line: with room for 8192 ids, 8000 take 65 us in
+// place of some 60, and 2000 take 23.
+constexpr int kFrontThreads = 1024, kFrontWaves = kFrontThreads / 64;
+constexpr int kFrontItems = (int)(kSmallFront / kFrontThreads);   // 4
+constexpr int kFrontBits = 8, kFrontPasses = 32 / kFrontBits;
+struct FrontLds {
+  uint32_t key[kSmallFront];
+  uint16_t id[kSmallFront];
+  uint16_t cnt[kFrontWaves][1 << kFrontBits];   // a wave's keys of a digit, then those of the waves before it
+  uint32_t first[1 << kFrontBits];
+  uint32_t sh[2][kFrontWaves];
+};
+static_assert(sizeof(FrontLds) <= 160 * 1024, "the lists fit in LDS");
+
+// exclusive scans of two values per thread over the work-group
+__device__ __forceinline__ uint2 front_scan2(uint32_t x, uint32_t y, uint32_t (*sh)[kFrontWaves], uint2& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t ix = wave_incl_scan(x, lane), iy = wave_incl_scan(y, lane);
+  __syncthreads();
+  if (lane == 63) {
+    sh[0][wave] = ix;
+    sh[1][wave] = iy;
+  }
+  __syncthreads();
+  uint2 pre = make_uint2(0u, 0u);
+  total = make_uint2(0u, 0u);
+#pragma unroll
+  for (int w = 0; w < kFrontWaves; ++w) {
+    const uint32_t a = sh[0][w], b = sh[1][w];
+    if (w < wave) {
+      pre.x += a;
+      pre.y += b;
+    }
+    total.x += a;
+    total.y += b;
+  }
+  return make_uint2(pre.x + ix - x, pre.y + iy - y);
+}
+
+__global__ void __launch_bounds__(kFrontThreads) k_small_front(FrontLists f, uint32_t n, Counters* __restrict__ out) {
+  __shared__ FrontLds S;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  uint32_t ct[kFrontItems], cb[kFrontItems], dk[kFrontItems];
+#pragma unroll
+  for (int k = 0; k < kFrontItems; ++k) {
+    const uint32_t i = min((uint32_t)(kFrontItems * t + k), n - 1u);
+    ct[k] = f.cnt_t[i];
+    cb[k] = f.cnt_b[i];
+    dk[k] = f.dkey[i];
+  }
+  asm volatile("" ::: "memory");
+  uint32_t vis = 0u, slots = 0u;
+#pragma unroll
+  for (int k = 0; k < kFrontItems; ++k) {
+    const bool v = (uint32_t)(kFrontItems * t + k) < n && ct[k] != 0u;
+    vis += v ? 1u : 0u;
+    slots += v ? cb[k] : 0u;
+  }
+  uint2 total;
+  uint2 at = front_scan2(vis, slots, S.sh, total);
+  const uint32_t m = total.x;
+#pragma unroll
+  for (int k = 0; k < kFrontItems; ++k) {
+    const uint32_t i = (uint32_t)(kFrontItems * t + k);
+    if (i >= n) continue;
+    f.cidx[i] = at.x;
+    if (ct[k] == 0u) continue;
+    f.ent[at.x] = i;
+    f.slot_off[at.x] = at.y;
+    f.slot_base[i] = at.y;
+    if (cb[k] > kLongSlots) f.long_ids[atomicAdd(&out->n_long, 1u)] = at.x;
+    S.key[at.x] = dk[k];
+    S.id[at.x] = (uint16_t)i;
+    ++at.x;
+    at.y += cb[k];
+  }
+  // depth sort of the m keys; a wave takes iters rows of 64
+  const int iters = (int)((m + kFrontThreads - 1) / kFrontThreads);
+  const uint32_t base = (uint32_t)(wave * iters * 64 + lane);
+#pragma unroll 1
+  for (int pass = 0; pass < kFrontPasses; ++pass) {
+    const int shift = kFrontBits * pass;
+    constexpr uint32_t mask = (1u << kFrontBits) - 1u;
+    for (int d = t; d < (int)(sizeof(S.cnt) / 16); d += kFrontThreads) ((uint4*)S.cnt)[d] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();   // (the keys are complete, too)
+    uint32_t kk[kFrontItems];
+    uint16_t vv[kFrontItems];
+    uint64_t peers[kFrontItems];
+#pragma unroll
+    for (int it = 0; it < kFrontItems; ++it)
+      if (it < iters) {
+        const uint32_t i = base + 64u * it;
+        const bool ok = i < m;
+        kk[it] = S.key[ok ? i : 0u];
+        vv[it] = S.id[ok ? i : 0u];
+        const uint32_t d = (kk[it] >> shift) & mask;
+        uint64_t p = __builtin_amdgcn_ballot_w64(ok);
+#pragma unroll
+        for (int b = 0; b < kFrontBits; ++b) {
+          const bool bit = (d >> b) & 1u;
+          const uint64_t bal = __builtin_amdgcn_ballot_w64(bit);
+          p &= bit ? bal : ~bal;
+        }
+        peers[it] = p;
+        if (ok && (p & lt) == 0ull) S.cnt[wave][d] += (uint16_t)__popcll(p);
+        __builtin_amdgcn_wave_barrier();
+      }
+    __syncthreads();
+    uint32_t a = 0u, b = 0u;   // digits 2 t, 2 t + 1
+    const bool owner = 2 * t < (1 << kFrontBits);
+    if (owner) {
+#pragma unroll
+      for (int w = 0; w < kFrontWaves; ++w) {
+        uint32_t* q = (uint32_t*)&S.cnt[w][2 * t];
+        const uint32_t c = *q;
+        *q = a | b << 16;
+        a += c & 0xffffu;
+        b += c >> 16;
+      }
+    }
+    uint2 all;
+    const uint2 pre = front_scan2(a + b, 0u, S.sh, all);
+    if (owner) {
+      S.first[2 * t] = pre.x;
+      S.first[2 * t + 1] = pre.x + a;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kFrontItems; ++it)
+      if (it < iters) {
+        const bool ok = base + 64u * it < m;
+        const uint32_t d = (kk[it] >> shift) & mask, rank = (uint32_t)__popcll(peers[it] & lt), c = S.cnt[wave][d];
+        __builtin_amdgcn_wave_barrier();
+        if (ok) {
+          const uint32_t pos = S.first[d] + c + rank;
+          S.key[pos] = kk[it];
+          S.id[pos] = vv[it];
+          if (rank == 0u) S.cnt[wave][d] = (uint16_t)(c + (uint32_t)__popcll(peers[it]));
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    __syncthreads();
+  }
+  // pair offsets in depth order
+  uint32_t id[kFrontItems], np[kFrontItems], pairs = 0u;
+#pragma unroll
+  for (int k = 0; k < kFrontItems; ++k) {
+    const uint32_t j = (uint32_t)(kFrontItems * t + k);
+    id[k] = S.id[j < m ? j : 0u];
+    np[k] = f.cnt_t[m ? id[k] : 0u];
+  }
+#pragma unroll
+  for (int k = 0; k < kFrontItems; ++k) {
+    np[k] = (uint32_t)(kFrontItems * t + k) < m ? np[k] : 0u;
+    pairs += np[k];
+  }
+  uint2 n_pairs;
+  uint32_t run = front_scan2(pairs, 0u, S.sh, n_pairs).x;
+#pragma unroll
+  for (int k = 0; k < kFrontItems; ++k) {
+    const uint32_t j = (uint32_t)(kFrontItems * t + k);
+    if (j < m) {
+      f.srid[j] = id[k];
+      f.off_t[j] = run;
+    }
+    run += np[k];
+  }
+  if (t == 0) {
+    out->n_visible = m;
+    out->n_pairs = n_pairs.x;
+    out->n_slots = total.y;
+  }
+}
+
 constexpr int kEmitThreads = 256;
 constexpr int kEmitPerThread = 4;
 constexpr int kEmitTile = kEmitThreads * kEmitPerThread;   // 1024 pairs per block
@@ -394,6 +576,10 @@ void launch_gather_scans(const GatherScan& a, const GatherScan& b, const uint32_
     return ScanArgs{g.src, g.idx, n_dev, g.out, g.total, bsum, g.out_at_idx, g.cp};
   };
   launch_scan_t<SCAN_GATHER>(args(a, (uint32_t*)temp), args(b, (uint32_t*)temp + nb), 2, n_max, s);
+}
+
+void launch_small_front(const FrontLists& f, int64_t n_rid, Counters* cnt, hipStream_t s) {
+  hipLaunchKernelGGL(k_small_front, dim3(1), dim3(kFrontThreads), 0, s, f, (uint32_t)n_rid, cnt);
 }
 
 void launch_emit(const GeomRec* geom, const ViewDesc* views, const uint32_t* srid, const uint32_t* off_t,

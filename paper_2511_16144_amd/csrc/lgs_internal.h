@@ -233,6 +233,19 @@ void radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t
                     const uint32_t* n_dev, int64_t n_max, int64_t small_max, int begin_bit, int end_bit,
                     void* temp, hipStream_t s, bool* result_in_alt);
 
+// The lists between projection and pair emission, of n_rid <= kSmallFront
+// (view, Gaussian) ids, by one work-group: what the flag scan with compaction,
+// the depth sort and the two gather scans give, with the same contents.
+constexpr int64_t kSmallFront = 4096;
+struct FrontLists {
+  const uint32_t *cnt_t, *cnt_b, *dkey;             // [n_rid]
+  uint32_t *cidx, *ent;                             // prefix of the visibility flags; visible ids, index order
+  uint32_t *srid, *off_t;                           // visible ids, depth order; their pair offsets
+  uint32_t *slot_off, *slot_base;                   // slot offsets, visible order and by id
+  uint32_t* long_ids;                               // visible ids (their place) with more than kLongSlots slots
+};
+void launch_small_front(const FrontLists& f, int64_t n_rid, Counters* cnt, hipStream_t s);
+
 // work queue ordering (blocks by descending tile-list length): each queue's
 // tiles re-sorted by the length of their list (counting sort on coarse
 // length buckets, one work-group per queue), a tile's blocks kept together;

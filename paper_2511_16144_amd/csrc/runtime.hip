@@ -746,26 +746,33 @@ void enqueue_front(Work* W, const lgs_gaussians* g, hipStream_t s) {
   const int64_t n_rid = W->n_rid;
   launch_project(ds, W->d_views, V, g->means, g->log_scales, g->quats, g->opacity_logits, g->rgb, g->feat,
                  W->app_bf16, W->n, W->npad_shift, W->geom, W->cnt_t, W->cnt_b, W->dkey, W->app, W->counters, s);
-  // the visibility scan also compacts: ent (kept, index order), a copy that
-  // the depth sort permutes, and the depth keys in the same order
-  Compact cp;
-  cp.key_src = W->dkey;
-  cp.ent = W->ent;
-  cp.ent_copy = W->ent_a;
-  cp.keys = W->dk0;
-  launch_scan(SCAN_FLAG_NONZERO, W->cnt_t, W->cidx, &W->counters->n_visible, n_rid, W->scan_tmp, s, cp);
-  bool alt = false;
-  radix_sort_u32(W->dk0, W->ent_a, W->dk1, W->ent_b, &W->counters->n_visible, n_rid, kSmallIds, 0, 32,
-                 W->radix_small, s, &alt);
-  W->srid = alt ? W->ent_b : W->ent_a;
-  // pair offsets in depth order; slot offsets in visible order, and the same
-  // as each record's slot base
-  const GatherScan pairs{W->cnt_t, W->srid, W->off_t, &W->counters->n_pairs, nullptr, Compact()};
-  GatherScan slots{W->cnt_b, W->ent, W->slot_off, &W->counters->n_slots, W->slot_base, Compact()};
-  slots.cp.big = W->long_ids;
-  slots.cp.n_big = &W->counters->n_long;
-  slots.cp.big_min = kLongSlots;
-  launch_gather_scans(pairs, slots, &W->counters->n_visible, n_rid, W->scan_tmp, s);
+  if (n_rid <= kSmallFront) {
+    W->srid = W->ent_a;
+    launch_small_front(FrontLists{W->cnt_t, W->cnt_b, W->dkey, W->cidx, W->ent, W->srid, W->off_t, W->slot_off,
+                                  W->slot_base, W->long_ids},
+                       n_rid, W->counters, s);
+  } else {
+    // the visibility scan also compacts: ent (kept, index order), a copy that
+    // the depth sort permutes, and the depth keys in the same order
+    Compact cp;
+    cp.key_src = W->dkey;
+    cp.ent = W->ent;
+    cp.ent_copy = W->ent_a;
+    cp.keys = W->dk0;
+    launch_scan(SCAN_FLAG_NONZERO, W->cnt_t, W->cidx, &W->counters->n_visible, n_rid, W->scan_tmp, s, cp);
+    bool alt = false;
+    radix_sort_u32(W->dk0, W->ent_a, W->dk1, W->ent_b, &W->counters->n_visible, n_rid, kSmallIds, 0, 32,
+                   W->radix_small, s, &alt);
+    W->srid = alt ? W->ent_b : W->ent_a;
+    // pair offsets in depth order; slot offsets in visible order, and the same
+    // as each record's slot base
+    const GatherScan pairs{W->cnt_t, W->srid, W->off_t, &W->counters->n_pairs, nullptr, Compact()};
+    GatherScan slots{W->cnt_b, W->ent, W->slot_off, &W->counters->n_slots, W->slot_base, Compact()};
+    slots.cp.big = W->long_ids;
+    slots.cp.n_big = &W->counters->n_long;
+    slots.cp.big_min = kLongSlots;
+    launch_gather_scans(pairs, slots, &W->counters->n_visible, n_rid, W->scan_tmp, s);
+  }
   launch_pack_app_groups(g->feat, W->app_bf16, W->n, W->G, W->app, W->app_stride, s);
 }
 
