@@ -23,8 +23,25 @@
 // gives lane l 8 consecutive pixels of one channel over the chunk's two
 // column groups, so its targets are one 16-byte load per channel), the
 // signs, its share of dL/dF (summed over the waves through LDS) and its
-// rows of dL/dW and dL/db (kept in registers over all chunks).  A second
+// rows of dL/dW and dL/db (kept in registers over all chunks).  The lane's
+// eight signs of a channel are the dL/dW product's operand as they stand; for
+// dL/dF, which contracts channels, they pass through LDS once (one 16-byte
+// store per channel, read across by the transposing LDS loads).  A second
 // kernel adds the work-groups' partials in a fixed order.
+//
+// What bounds it: the targets, read once (1.57 GB of 8 views of 640 x 480 and
+// 320 x 240, C = 512, BF16, in 277 us at this access pattern without any
+// arithmetic), against the vector and matrix instructions of a chunk, about
+// 3300 of a SIMD's cycles with little overlap (310 us), and the waits of the
+// four waves at the barrier and for their targets.  569 -> 430 us: signs as
+// operands and the transposing loads instead of two LDS layouts written 2
+// bytes at a time (LDS busy 63 % -> 30 % of the cycles: -> 510); no request to
+// memory between a chunk's barrier and the wait for its targets, and full
+// chunks without a branch around their loads, so that this wait does not
+// include the store and the loads just issued (-> 430).  A second chunk in
+// flight does not fit the 128 registers (29 spilled: 650).  Rows that start at
+// any element (613 x 457, 2 views, BF16, C = 512): 548 -> 216 us by the same
+// 16-byte loads in place of eight of 2 bytes.
 #include "lgs_internal.h"
 
 #include <type_traits>
@@ -35,11 +52,14 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kChunk = 32;            // pixels per chunk
 constexpr int kFA = 40;               // LDS pitch (u16) of the [pixel][k] F rows (80 B)
 constexpr int kFT = 40;               // LDS pitch (u16) of the [feature][pixel] F rows
 constexpr int kRC = 40;               // LDS pitch (u16) of the [channel][pixel] sign rows
+constexpr int kDF = 36;               // LDS pitch (floats) of the [feature][pixel] dF partials: the four rows that a
+                                      // store of 64 lanes meets, 4 apart, lie 16 banks apart
 
 __device__ __forceinline__ unsigned short to_bf16(float x) {
   const uint32_t u = __float_as_uint(x);
@@ -54,30 +74,40 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(u16x8 v) { return __builtin_bit_ca
 // __syncthreads() also waits for every outstanding global load).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Four 16-bit LDS rows across: lane i of each 16 names the 8 bytes at columns
+// 4 (i & 3) .. + 3 of row i / 4 and receives column i of the four rows.
+__device__ __forceinline__ s16x4 read_transposed(const unsigned short* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+}
+
 __device__ __forceinline__ f32x4 mfma(bf16x8_t a, bf16x8_t b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Eight consecutive targets as loaded (BF16: 16 bytes, FP32: 32 bytes),
-// vector loads when aligned and in range, else element by element (zero past
-// the end); unpacked to FP32 when used.
+// Eight consecutive targets as loaded (BF16: 16 bytes, FP32: 32 bytes):
+// 16-byte loads where all are wanted (at the elements' own alignment, which
+// the global loads take: rows of a map whose pixel count is no multiple of 8
+// start anywhere), else element by element (zero past the end); unpacked to
+// FP32 when used.
 struct F8 { float4 a, b; };
 template <typename T> struct Raw8;
 template <> struct Raw8<unsigned short> { typedef uint4 type; };
 template <> struct Raw8<float> { typedef F8 type; };
 
-__device__ __forceinline__ uint4 load_raw8(const unsigned short* p, bool vec, int64_t left) {
-  if (vec) return *(const uint4*)p;
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ uint4 load_raw8(const unsigned short* p, bool all, int64_t left) {
+  if (all) return __builtin_bit_cast(uint4, *(const u32x4_a2*)p);
   uint32_t h[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) h[i] = i < left ? (uint32_t)p[i] : 0u;
   return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
-__device__ __forceinline__ F8 load_raw8(const float* p, bool vec, int64_t left) {
+__device__ __forceinline__ F8 load_raw8(const float* p, bool all, int64_t left) {
   F8 r;
-  if (vec) {
-    r.a = *(const float4*)p;
-    r.b = *(const float4*)(p + 4);
+  if (all) {
+    r.a = __builtin_bit_cast(float4, *(const u32x4_a4*)p);
+    r.b = __builtin_bit_cast(float4, *(const u32x4_a4*)(p + 4));
     return r;
   }
   float f[8];
@@ -113,16 +143,7 @@ __global__ __launch_bounds__(64 * NW) void k_decoder(DecArgs a, float* __restric
   __shared__ __attribute__((aligned(16))) unsigned short fA[2][kChunk * kFA];     // [pixel][F_hi 16 | F_lo 16]
   __shared__ __attribute__((aligned(16))) unsigned short fT[2][2 * 16 * kFT];     // [hi/lo][feature][pixel]
   __shared__ __attribute__((aligned(16))) unsigned short rC[kDecWaves][Cw * kRC];      // [channel][pixel] signs
-  // [pixel][channel] signs.  A wave's 2-byte sign stores hit four rows 8
-  // apart at once (one per lane group), and with 16-byte-aligned rows those
-  // always share banks, so each row's channels are rotated by Cw / 4
-  // channels per group of 8 rows: the four lane groups then fall on disjoint
-  // banks.  Readers take 8-channel runs, which the rotation keeps whole.
-  constexpr int kRP = Cw + 8;
-  auto rp_col = [&](int row, int col) { return (col + (Cw / 4) * ((row >> 3) & 3)) & (Cw - 1); };
-  static_assert((Cw & (Cw - 1)) == 0 && Cw >= 32, "rotation modulo a power-of-two channel count");
-  __shared__ __attribute__((aligned(16))) unsigned short rP[kDecWaves][kChunk * kRP];
-  __shared__ __attribute__((aligned(16))) float dfr[2][kDecWaves * 16 * kChunk];      // [wave][feature][pixel]
+  __shared__ __attribute__((aligned(16))) float dfr[2][kDecWaves * 16 * kDF];      // [wave][feature][pixel]
   __shared__ float red[kDecWaves];
 
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -137,7 +158,44 @@ __global__ __launch_bounds__(64 * NW) void k_decoder(DecArgs a, float* __restric
   const TT* __restrict__ target = (const TT*)a.v[vi].target;
   float* __restrict__ grad_feat = a.v[vi].grad_feat;
   const float scale = a.v[vi].scale;
-  const bool vec = a.v[vi].vec != 0;
+
+  // The targets of the next PF chunks are loaded into registers ahead of
+  // their use (PF register sets, the chunk loop unrolled by PF so that each
+  // set stays in the same registers), so the loads' latency overlaps the
+  // matrix products of the chunks before.  The depth is what the register
+  // file holds without spilling: a chunk's targets take 4 NT registers in
+  // BF16, 8 NT in FP32.  At 16 waves (128 VGPRs)
+  // that is one chunk.
+  constexpr int kPF = NW == 16 ? 1 : (sizeof(TT) == 2 ? 3 : 2) - (NT == 4 ? 1 : 0);
+  typedef typename Raw8<TT>::type RawT;
+  static_assert(kDecThreads >= 16 * kChunk, "at most one feature element per thread and chunk");
+  const int fk = (t >> 5) & 15, fpx = t & 31;
+  const bool fth = t < 16 * kChunk;   // the threads that stage the chunk's feature elements
+  // lane (q4, r16) of the Z^T products holds pixels 8 q4 .. 8 q4 + 7 of the
+  // chunk (rows 4 q4 .. 4 q4 + 3 of column group cg are pixels 8 q4 + 4 cg
+  // + i): its targets of one channel are one 16-byte load
+  const TT* const tp0 = target + (size_t)(c0 + r16) * n + 8 * q4;
+  auto fetch = [&](auto full_tag, int64_t ck, RawT (&trs)[NT]) {
+    constexpr bool kFull = decltype(full_tag)::value;
+    const int64_t p0 = ck * kChunk;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+      trs[nt] = load_raw8(tp0 + (size_t)(16 * nt) * n + p0, kFull || p0 + kChunk <= n, n - p0 - 8 * q4);
+  };
+  // (requested without a branch; elements past the end are zeroed when staged)
+  auto fetch_f = [&](int64_t ck) {
+    const int64_t p = ck * kChunk + fpx;
+    return feat[(size_t)fk * n + (p < n ? p : n - 1)];
+  };
+  // each work-group takes a contiguous run of its view's chunks, so the two
+  // halves of a 128-byte target line are read by the same work-group one
+  // chunk apart
+  const int64_t n_chunks = (n + kChunk - 1) / kChunk;
+  const int64_t per = (n_chunks + a.v[vi].groups - 1) / a.v[vi].groups;
+  const int64_t ck0 = (int64_t)((int)blockIdx.x - a.v[vi].g0) * per;
+  const int64_t ck1 = ck0 + per < n_chunks ? ck0 + per : n_chunks;
+  RawT t_first[NT];
+  float f_first = 0.f, f_next = 0.f;
 
   // W is staged in LDS once (over the sign rows, unused until the first
   // chunk's first barrier), then every wave builds its operands from there
@@ -151,10 +209,17 @@ __global__ __launch_bounds__(64 * NW) void k_decoder(DecArgs a, float* __restric
     float wv[kWv];
 #pragma unroll
     for (int i = 0; i < kWv; ++i) wv[i] = a.weight[t + i * kDecThreads];
+    // (the first chunk's inputs are requested in the same wait; with 16 waves
+    // there are no registers for its targets yet)
+    if (ck0 < ck1) {
+      f_first = fetch_f(ck0);
+      f_next = fetch_f(ck0 + 1);
+      if (NW == 8) fetch(std::false_type(), ck0, t_first);
+    }
 #pragma unroll
     for (int i = 0; i < kWv; ++i) wl[t + i * kDecThreads] = wv[i];
   }
-  __syncthreads();
+  lds_barrier();
   // this wave's operands of W, split hi/lo, in registers for the whole run
   // Z^T B operand, tile nt: lane (k block q4, channel r16): [W_hi ; W_hi] and [W_lo ; W_lo]
   bf16x8_t bz1[NT], bz2[NT];
@@ -213,148 +278,128 @@ __global__ __launch_bounds__(64 * NW) void k_decoder(DecArgs a, float* __restric
   }
   float lsum = 0.f;
 
-  // The targets and feature element of the next kDecPF chunks are loaded
-  // into registers ahead of their use (kDecPF register sets, the chunk loop
-  // unrolled by kDecPF so that each set stays in the same registers), so the
-  // loads' latency overlaps the matrix products of the chunks before.  The
-  // depth is what the register file holds without spilling: a chunk's
-  // targets take 4 NT registers in BF16, 8 NT in FP32; at 16 waves (128
-  // VGPRs) one chunk ahead.
-  constexpr int kDecPF = NW == 16 ? 1 : (sizeof(TT) == 2 ? 3 : 2) - (NT == 4 ? 1 : 0);
-  typedef typename Raw8<TT>::type RawT;
-  RawT tr[kDecPF][NT];
-  float fr[kDecPF];
-  static_assert(kDecThreads >= 16 * kChunk, "at most one feature element per thread and chunk");
-  const int fk = (t >> 5) & 15, fpx = t & 31;
-  const bool fth = t < 16 * kChunk;   // the threads that carry the chunk's feature elements
-  // lane (q4, r16) of the Z^T products holds pixels 8 q4 .. 8 q4 + 7 of the
-  // chunk (rows 4 q4 .. 4 q4 + 3 of column group cg are pixels 8 q4 + 4 cg
-  // + i): its targets of one channel are one 16-byte load
-  auto fetch = [&](int64_t ck, RawT (&trs)[NT], float& frs) {
-    const int64_t p0 = ck * kChunk;
-    const bool full = p0 + kChunk <= n;
-    frs = fth && p0 + fpx < n ? feat[(size_t)fk * n + p0 + fpx] : 0.f;
-    const int64_t pp = p0 + 8 * q4;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const TT* tp = target + (size_t)(c0 + 16 * nt + r16) * n + pp;
-      trs[nt] = load_raw8(tp, full && vec, n - pp);
-    }
-  };
-  // each work-group takes a contiguous run of its view's chunks, so the two
-  // halves of a 128-byte target line are read by the same work-group one
-  // chunk apart
-  const int64_t n_chunks = (n + kChunk - 1) / kChunk;
-  const int64_t per = (n_chunks + a.v[vi].groups - 1) / a.v[vi].groups;
-  const int64_t ck0 = (int64_t)((int)blockIdx.x - a.v[vi].g0) * per;
-  const int64_t ck1 = ck0 + per < n_chunks ? ck0 + per : n_chunks;
   // chunk pc's dL/dF: the waves' partials (buffer par) summed in a fixed order
   auto store_df = [&](int64_t pc, int par) {
     const int64_t q0 = pc * kChunk;
-    for (int e = t; e < 16 * kChunk; e += kDecThreads) {
+    const int e = t - (kDecThreads - 16 * kChunk);
+    if (e >= 0) {
       const int k = e >> 5, px = e & 31;
       float v = 0.f;
 #pragma unroll
-      for (int u = 0; u < kDecWaves; ++u) v += dfr[par][(u * 16 + k) * kChunk + px];
+      for (int u = 0; u < kDecWaves; ++u) v += dfr[par][(u * 16 + k) * kDF + px];
       if (q0 + px < n) grad_feat[(size_t)k * n + q0 + px] = scale * v;
     }
   };
-  // one chunk; its inputs are in (cur, frc), which are refilled with chunk
-  // ck + kDecPF's as soon as they have been used
-  auto chunk = [&](int64_t ck, RawT (&cur)[NT], float& frc) {
-    const int64_t p0 = ck * kChunk;
-    const int par = (int)((ck - ck0) & 1);
-    const unsigned short* fAc = fA[par];
-    const unsigned short* fTc = fT[par];
-    // (1) F chunk -> LDS: [pixel][F_hi | F_lo] and [hi/lo][feature][pixel]
+  // F chunk -> LDS: [pixel][F_hi | F_lo] and [hi/lo][feature][pixel]
+  auto stage_f = [&](int64_t ck, float f, int par) {
     if (fth) {
-      const unsigned short hi = to_bf16(frc), lo = to_bf16(frc - from_bf16(hi));
+      if (ck * kChunk + fpx >= n) f = 0.f;
+      const unsigned short hi = to_bf16(f), lo = to_bf16(f - from_bf16(hi));
       fA[par][fpx * kFA + fk] = hi;
       fA[par][fpx * kFA + 16 + fk] = lo;
       fT[par][fk * kFT + fpx] = hi;
       fT[par][16 * kFT + fk * kFT + fpx] = lo;
     }
-    // The one barrier of the chunk: the F rows of this chunk are complete, and
-    // every wave has finished the previous chunk (its dF partials are in the
-    // other buffer, and it no longer reads this buffer's F rows from two
-    // chunks ago).  The sign rows are per wave and need no barrier.
+  };
+  // one chunk; its targets are in cur, which is refilled with chunk next's as
+  // soon as they have been used
+  auto chunk = [&](auto full_tag, int64_t ck, int64_t next, RawT (&cur)[NT]) {
+    const int64_t p0 = ck * kChunk;
+    const int par = (int)((ck - ck0) & 1);
+    const unsigned short* fAc = fA[par];
+    const unsigned short* fTc = fT[par];
+    // (1) The one barrier of the chunk: the F rows of this chunk are complete
+    // (staged while the one before was worked on), and every wave has finished
+    // the previous chunk (its dF partials are in the other buffer, and it no
+    // longer reads the other F rows).  The sign rows are per wave and need no
+    // barrier.
     lds_barrier();
-    if (ck > ck0) store_df(ck - 1, par ^ 1);
-    // (2) Z^T tiles, signs, loss, db; signs to LDS in both layouts (a
-    // chunk wholly inside the image skips the per-pixel validity tests)
+    // (2) Z^T tiles, signs, loss, db; signs to LDS (a chunk wholly inside the
+    // image skips the per-pixel validity tests)
     const int lim = n - p0 < kChunk ? (int)(n - p0) : kChunk;   // valid pixels of the chunk
+    // F hi/lo as the A operand of the dW^T product: (feature r16, pixels 8 q4 .. + 7)
+    const bf16x8_t fh = as_bf16x8(*(const u16x8*)(fTc + r16 * kFT + 8 * q4));
+    const bf16x8_t fl = as_bf16x8(*(const u16x8*)(fTc + 16 * kFT + r16 * kFT + 8 * q4));
+    // A row r16 of column group cg is pixel 8 (r16 / 4) + 4 cg + r16 % 4
+    bf16x8_t af[2];
+#pragma unroll
+    for (int cg = 0; cg < 2; ++cg)
+      af[cg] = as_bf16x8(*(const u16x8*)(fAc + (8 * (r16 >> 2) + 4 * cg + (r16 & 3)) * kFA + 8 * q4));
     auto signs = [&](auto full_tag) {
       constexpr bool kFull = decltype(full_tag)::value;
 #pragma unroll
-    for (int cg = 0; cg < 2; ++cg) {
-      // A row r16 of column group cg is pixel 8 (r16 / 4) + 4 cg + r16 % 4
-      const bf16x8_t af = as_bf16x8(*(const u16x8*)(fAc + (8 * (r16 >> 2) + 4 * cg + (r16 & 3)) * kFA + 8 * q4));
-      const int pl = 8 * q4 + 4 * cg;    // first of this lane's 4 pixels of this column group
-#pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        f32x4 z = {bias[nt], bias[nt], bias[nt], bias[nt]};
-        // BF16 targets enter the product as they are: the selector rows of
-        // -1 pick each row's own target (one non-zero product, exact), so
-        // the tile comes out as Z - T
-        if constexpr (kTsel) z = mfma(tsel[cg], __builtin_bit_cast(bf16x8_t, cur[nt]), z);
-        z = mfma(af, bz1[nt], z);
-        z = mfma(af, bz2[nt], z);
-        float tv[4];
-        if constexpr (!kTsel) unpack4(cur[nt], cg, tv);
-        uint32_t sb[4];
+        uint32_t rs[4];   // the signs of this lane's channel and pixels 8 q4 .. + 7
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool valid = kFull || pl + i < lim;
-          const float d = kTsel ? z[i] : z[i] - tv[i];
-          // Z is never -0 (its sum starts from the bias plus +0, and a sum
-          // of +0 and -0 is +0), so d is never -0: its bits as a signed
-          // integer are > 0, 0 or < 0 as d is, and their clamp to [-1, 1]
-          // (one v_med3_i32) is the sign of d
-          lsum += valid ? fabsf(d) : 0.f;
-          int si;
-          // d may come straight from a matrix-core result, which a vector
-          // instruction may read only some cycles after it is written: the
-          // compiler pads its own readers but not an asm statement, so the
-          // clamp takes the loss sum (a compiler read of d) as an operand
-          // and is issued after it
-          asm("v_med3_i32 %0, %1, -1, 1" : "=v"(si) : "v"(__float_as_uint(d)), "v"(lsum));
-          if (!kFull) si = valid ? si : 0;
-          db[nt] += si;
-          // -1, 0, 1 as FP32: the high half is the same value in BF16 (the
-          // store of that half alone is one ds_write_b16_d16_hi)
-          sb[i] = __float_as_uint((float)si);
-          rP[w][(pl + i) * kRP + rp_col(pl + i, 16 * nt + r16)] = (unsigned short)(sb[i] >> 16);
+        for (int cg = 0; cg < 2; ++cg) {
+          const int pl = 8 * q4 + 4 * cg;    // first of this lane's 4 pixels of this column group
+          f32x4 z = {bias[nt], bias[nt], bias[nt], bias[nt]};
+          // BF16 targets enter the product as they are: the selector rows of
+          // -1 pick each row's own target (one non-zero product, exact), so
+          // the tile comes out as Z - T
+          if constexpr (kTsel) z = mfma(tsel[cg], __builtin_bit_cast(bf16x8_t, cur[nt]), z);
+          z = mfma(af[cg], bz1[nt], z);
+          z = mfma(af[cg], bz2[nt], z);
+          float tv[4];
+          if constexpr (!kTsel) unpack4(cur[nt], cg, tv);
+          uint32_t sb[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const bool valid = kFull || pl + i < lim;
+            const float d = kTsel ? z[i] : z[i] - tv[i];
+            // Z is never -0 (its sum starts from the bias plus +0, and a sum
+            // of +0 and -0 is +0), so d is never -0: its bits as a signed
+            // integer are > 0, 0 or < 0 as d is, and their clamp to [-1, 1]
+            // (one v_med3_i32) is the sign of d
+            lsum += valid ? fabsf(d) : 0.f;
+            int si;
+            // d may come straight from a matrix-core result, which a vector
+            // instruction may read only some cycles after it is written: the
+            // compiler pads its own readers but not an asm statement, so the
+            // clamp takes the loss sum (a compiler read of d) as an operand
+            // and is issued after it
+            asm("v_med3_i32 %0, %1, -1, 1" : "=v"(si) : "v"(__float_as_uint(d)), "v"(lsum));
+            if (!kFull) si = valid ? si : 0;
+            db[nt] += si;
+            // -1, 0, 1 as FP32: the high half is the same value in BF16
+            sb[i] = __float_as_uint((float)si);
+          }
+          rs[2 * cg] = __builtin_amdgcn_perm(sb[1], sb[0], 0x07060302u);
+          rs[2 * cg + 1] = __builtin_amdgcn_perm(sb[3], sb[2], 0x07060302u);
         }
-        uint2 packed;
-        packed.x = __builtin_amdgcn_perm(sb[1], sb[0], 0x07060302u);
-        packed.y = __builtin_amdgcn_perm(sb[3], sb[2], 0x07060302u);
-        *(uint2*)(&rC[w][(16 * nt + r16) * kRC + pl]) = packed;
-      }
-    }
-    };
-    if (lim == kChunk) signs(std::true_type());
-    else signs(std::false_type());
-    if (ck + kDecPF < ck1) fetch(ck + kDecPF, cur, frc);
-    // (3) dW^T += F R^T over the chunk's 32 pixels (A = F hi/lo, B = signs)
-    {
-      const bf16x8_t fh = as_bf16x8(*(const u16x8*)(fTc + r16 * kFT + 8 * q4));
-      const bf16x8_t fl = as_bf16x8(*(const u16x8*)(fTc + 16 * kFT + r16 * kFT + 8 * q4));
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const bf16x8_t rb = as_bf16x8(*(const u16x8*)(&rC[w][(16 * nt + r16) * kRC + 8 * q4]));
+        // (3) dW^T += F R^T over the chunk's 32 pixels (A = F hi/lo, B = signs):
+        // the lane's eight signs are its share of B as they are
+        const uint4 rv = make_uint4(rs[0], rs[1], rs[2], rs[3]);
+        *(uint4*)(&rC[w][(16 * nt + r16) * kRC + 8 * q4]) = rv;
+        const bf16x8_t rb = __builtin_bit_cast(bf16x8_t, rv);
         dw[nt] = mfma(fh, rb, dw[nt]);
         dw[nt] = mfma(fl, rb, dw[nt]);
       }
-    }
-    // (4) this wave's share of dF = W^T R (A = W^T hi/lo, B = signs [channel][pixel])
+    };
+    if constexpr (decltype(full_tag)::value) signs(std::true_type());
+    else if (lim == kChunk) signs(std::true_type());
+    else signs(std::false_type());
+    // The next chunk's F rows by the first waves, the previous chunk's dL/dF
+    // by the last.  All requests to memory come after the wait for this
+    // chunk's targets, the targets' own last but for the store: a wait for
+    // loads counts back from the newest request.
+    if (ck + 1 < ck1) stage_f(ck + 1, f_next, par ^ 1);
+    f_next = fetch_f(ck + 2);
+    if (decltype(full_tag)::value || next < ck1) fetch(full_tag, next, cur);
+    if (ck > ck0) store_df(ck - 1, par ^ 1);
+    // (4) this wave's share of dF = W^T R (A = W^T hi/lo, B = signs: pixel
+    // 16 cg + r16, channels 32 ks + 8 q4 .. + 7, i.e. the rows of rC across,
+    // which the transposing LDS read gives: the 16 lanes of a group name the
+    // 8-byte quarters of four rows, and lane i of it receives column i)
     f32x4 dfa[2];
 #pragma unroll
     for (int cg = 0; cg < 2; ++cg) {
       dfa[cg] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8_t rb =
-            as_bf16x8(*(const u16x8*)(&rP[w][(16 * cg + r16) * kRP + rp_col(16 * cg + r16, 32 * ks + 8 * q4)]));
+        const unsigned short* row = &rC[w][(32 * ks + 8 * q4 + (r16 >> 2)) * kRC + 16 * cg + 4 * (r16 & 3)];
+        const s16x4 lo = read_transposed(row), hi = read_transposed(row + 4 * kRC);
+        const bf16x8_t rb = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
         dfa[cg] = mfma(wt_h[ks], rb, dfa[cg]);
         dfa[cg] = mfma(wt_l[ks], rb, dfa[cg]);
       }
@@ -362,16 +407,36 @@ __global__ __launch_bounds__(64 * NW) void k_decoder(DecArgs a, float* __restric
 #pragma unroll
     for (int cg = 0; cg < 2; ++cg)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dfr[par][(w * 16 + 4 * q4 + i) * kChunk + 16 * cg + r16] = dfa[cg][i];
+      for (int i = 0; i < 4; ++i) dfr[par][(w * 16 + 4 * q4 + i) * kDF + 16 * cg + r16] = dfa[cg][i];
   };
+  // The chunks from..to - 1 (to = ck1 where some are not full).  Past the last
+  // full one, its targets are requested again (no branch around the loads,
+  // which would make the wait for one set a wait for all).
+  auto walk = [&](auto full_tag, int64_t from, int64_t to) {
+    constexpr bool kFull = decltype(full_tag)::value;
+    if (from >= to) return;
+    RawT tr[kPF][NT];
+    auto at = [&](int64_t ck) { return !kFull || ck < to ? ck : to - 1; };
 #pragma unroll
-  for (int d = 0; d < kDecPF; ++d)
-    if (ck0 + d < ck1) fetch(ck0 + d, tr[d], fr[d]);
-  for (int64_t cb = ck0; cb < ck1; cb += kDecPF) {
+    for (int d = 0; d < kPF; ++d)
+      if ((NW != 8 || d > 0 || from > ck0) && (kFull || from + d < to)) fetch(full_tag, at(from + d), tr[d]);
+    if (from == ck0) {
 #pragma unroll
-    for (int d = 0; d < kDecPF; ++d)
-      if (cb + d < ck1) chunk(cb + d, tr[d], fr[d]);
-  }
+      for (int nt = 0; NW == 8 && nt < NT; ++nt) tr[0][nt] = t_first[nt];
+      stage_f(ck0, f_first, 0);
+    }
+    int64_t cb = from;
+    for (; cb + kPF <= to; cb += kPF)
+#pragma unroll
+      for (int d = 0; d < kPF; ++d) chunk(full_tag, cb + d, at(cb + d + kPF), tr[d]);
+#pragma unroll
+    for (int d = 0; d < kPF - 1; ++d)
+      if (cb + d < to) chunk(full_tag, cb + d, at(cb + d + kPF), tr[d]);
+  };
+  // chunks wholly inside the image, then the last
+  const int64_t whole = n / kChunk < ck1 ? n / kChunk : ck1, ckf = whole > ck0 ? whole : ck0;
+  walk(std::true_type(), ck0, ckf);
+  walk(std::false_type(), ckf, ck1);
   lds_barrier();
   if (ck1 > ck0) store_df(ck1 - 1, (int)((ck1 - 1 - ck0) & 1));
 

@@ -316,7 +316,6 @@ struct DecView {
   float* grad_feat;                    // dL/dF [16][n]
   int64_t n;                           // pixels
   float scale;                         // w_feat / (C n)
-  int32_t vec;                         // targets allow 8-element vector loads (n % 8 == 0, 16-B base)
   int32_t g0, groups;                  // its work-groups g0 .. g0 + groups - 1 (decoder_assign)
 };
 struct DecArgs {

@@ -1256,7 +1256,6 @@ static lgs_status decoder_args(lgs_context* ctx, int32_t n_views, const int32_t*
     d.grad_feat = grad_feat[v];
     d.n = n;
     d.scale = (float)((double)w_feat / ((double)out_dim * (double)n));
-    d.vec = n % 8 == 0 && ((uintptr_t)target[v] & 15u) == 0;
   }
   return LGS_OK;
 }
