@@ -423,6 +423,11 @@ __device__ __forceinline__ int64_t wave_upper_bound_u32(const uint32_t* a, int64
 
 // Also the step's overflow flag and effective counts (block 0), and a range of
 // words zeroed for the stages that follow (nothing here reads any of them).
+// The box and its view are read once per entry and kept in LDS, a thread's
+// pairs are looked up together and the place in the box is divided by its width
+// through a reciprocal: 2 M Gaussians at 1296 x 968 (4.3 M pairs) 26 -> 20 us,
+// 300k at 640 x 480 8.5 -> 6.4, 2k 7.4 -> 5.8; eight views of 640 x 480 (3.9 M
+// pairs of 1.04 M entries, whose scattered boxes bound it) 38.5 -> 36.5.
 __global__ void __launch_bounds__(kEmitThreads) k_emit(
     const GeomRec* __restrict__ geom, const ViewDesc* __restrict__ views,
     const uint32_t* __restrict__ srid, const uint32_t* __restrict__ off_t,
@@ -430,6 +435,7 @@ __global__ void __launch_bounds__(kEmitThreads) k_emit(
     uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, uint32_t* __restrict__ zero, int64_t n_zero) {
   __shared__ uint32_t s_off[kEmitTile + 2];
   __shared__ uint32_t s_rid[kEmitTile + 2];
+  __shared__ uint32_t s_key[kEmitTile + 2], s_row[kEmitTile + 2];   // first tile; tiles per row | tiles_x << 16
   __shared__ int64_t s_j[2];
   const int64_t M = cnt->n_visible;
   const int64_t P = cnt->n_pairs;
@@ -455,28 +461,39 @@ __global__ void __launch_bounds__(kEmitThreads) k_emit(
   const int64_t j0 = s_j[0], j1 = s_j[1];
   const int nj = (int)(j1 - j0 + 1);         // <= kEmitTile: every entry owns >= 1 pair
   for (int t = threadIdx.x; t < nj; t += kEmitThreads) {
+    const uint32_t rid = srid[j0 + t];
     s_off[t] = off_t[j0 + t];
-    s_rid[t] = srid[j0 + t];
+    s_rid[t] = rid;
+    const uint32_t bb = geom[rid].bbox;
+    const ViewDesc& V = views[rid >> npad_shift];
+    const uint32_t tx0 = (bb & 255u) >> tile_shift, tx1 = ((bb >> 8) & 255u) >> tile_shift;
+    const uint32_t ty0 = ((bb >> 16) & 255u) >> tile_shift, tiles_x = (uint32_t)V.tiles_x;
+    s_key[t] = (uint32_t)V.tile_off + ty0 * tiles_x + tx0;
+    s_row[t] = (tx1 - tx0 + 1u) | (tiles_x << 16);
   }
   __syncthreads();
-  for (int k = 0; k < kEmitPerThread; ++k) {
-    const int64_t pi = p0 + (int64_t)k * kEmitThreads + threadIdx.x;
-    if (pi > p1) break;
-    int lo = 0, hi = nj;                      // largest t with s_off[t] <= pi
-    while (hi - lo > 1) {
-      int mid = (lo + hi) >> 1;
-      if ((int64_t)s_off[mid] <= pi) lo = mid; else hi = mid;
+  // each pair's entry, the largest t with s_off[t] <= pi: one search for all
+  // of a thread's pairs, step by step, so that their LDS reads overlap
+  int own[kEmitPerThread];
+#pragma unroll
+  for (int k = 0; k < kEmitPerThread; ++k) own[k] = 0;
+  for (int step = nj > 1 ? 1 << (31 - __builtin_clz(nj - 1)) : 0; step > 0; step >>= 1)
+#pragma unroll
+    for (int k = 0; k < kEmitPerThread; ++k) {
+      const int mid = min(own[k] + step, nj - 1);
+      own[k] = (int64_t)s_off[mid] <= p0 + k * kEmitThreads + (int)threadIdx.x ? mid : own[k];
     }
-    const uint32_t rid = s_rid[lo];
-    const uint32_t local = (uint32_t)(pi - s_off[lo]);
-    const uint32_t bb = geom[rid].bbox;
-    const uint32_t tx0 = (bb & 255u) >> tile_shift, tx1 = ((bb >> 8) & 255u) >> tile_shift;
-    const uint32_t ty0 = ((bb >> 16) & 255u) >> tile_shift;
-    const uint32_t w = tx1 - tx0 + 1u;
-    const uint32_t ty = ty0 + local / w, tx = tx0 + local % w;
-    const ViewDesc& V = views[rid >> npad_shift];
-    keys[pi] = (uint32_t)V.tile_off + ty * (uint32_t)V.tiles_x + tx;
-    vals[pi] = rid;
+#pragma unroll
+  for (int k = 0; k < kEmitPerThread; ++k) {
+    const int64_t pi = p0 + k * kEmitThreads + threadIdx.x;
+    const uint32_t local = (uint32_t)(pi - s_off[own[k]]), row = s_row[own[k]], w = row & 0xffffu;
+    // local / w: at most 2^16 tiles, so the quotient's fraction is at least
+    // 2^-17 of it away from an integer, far more than the reciprocal's error
+    const uint32_t q = (uint32_t)(((float)local + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+    if (pi <= p1) {
+      keys[pi] = s_key[own[k]] + q * (row >> 16) + (local - q * w);
+      vals[pi] = s_rid[own[k]];
+    }
   }
 }
 
