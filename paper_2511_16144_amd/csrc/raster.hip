@@ -485,13 +485,18 @@ __device__ __forceinline__ int wave_max_i32(int x) {
 //     (exact products); else v_mfma_f32_4x4x1_16b_f32 takes one (FP32 fused
 //     multiply-adds).
 //   - the six geometric sums sum_p u[p] {1, X, Y, X^2, X Y, Y^2}, u =
-//     dL/dalpha alpha, over each 4 x 4 quarter of the block, X, Y the pixel's
-//     position from the quarter's centre: (6 x pixels) x (pixels x entries) in
-//     FP32 (v_mfma_f32_16x16x4_f32), once per batch of 16 entries; then each
-//     quarter's sums are moved to the entry's mean in the product's own lanes
-//     and added.  (Quarters, because the move cancels: over the whole block at
-//     once the gradients of small Gaussians were up to twice as far from FP64.)
-//     Some rows of A repeat so that every lane holds what its share needs.
+//     dL/dalpha alpha, X, Y the pixel's position from the block's centre:
+//     (6 x pixels) x (pixels x entries) in FP64 (v_mfma_f64_4x4x4_4b_f64, its
+//     four blocks four entries each), once per batch of 16 entries; then they
+//     are moved to the entry's mean.  The move cancels, the more the smaller the
+//     Gaussian is against its distance from the centre.  (Scale and
+//     rotation gradients of Gaussians of up to 1.2 px alone on their pixels are
+//     3e-7 to 6e-7 of their norm off with FP32 sums about the centres of 4 x 4
+//     quarters, 1.0e-7 to 1.3e-7 with FP32 sums about the mean, 0.8e-7 to 1.1e-7
+//     so.)  A row of pixels and its mirror image in the block's middle have the
+//     same {1, X, X^2, Y^2} and opposite {Y, X Y}, so products of the rows' sums
+//     and differences are half as many: 16 of 16 cycles for a batch, where the
+//     quarters' were 16 of 32.
 //   - the 20 colour partials sum_p g[p][c] w[p]: (channels x pixels) x (pixels
 //     x entries) on BF16 terms whose sums are exact, once per batch; a lane
 //     then holds four consecutive channels of one entry and stores them as
@@ -517,8 +522,11 @@ __host__ __device__ constexpr int bwd_wave_lds(int up_mode) {
   return kBatchBytes + (up_mode == UP_EXPLICIT ? 8 : 4) * kZRow * 2;
 }
 static_assert(32 * kZRow * 2 <= kBatchBytes, "the upstream rows fit");
-// ... and of the work-group: a quarter's basis, [6][16 pixels] FP32
-constexpr int kBasisBytes = 6 * 16 * 4;
+// ... and of the work-group: the moments' basis over a row's 8 pixels, FP64:
+// 1, X, X^2, then of each row distance k + 1/2 from the block's middle Y^2, Y and
+// X Y (4 rows each)
+constexpr int kBasisOne = 0, kBasisYY = 3, kBasisY = 7, kBasisXY = 11, kBasisRows = 15;
+constexpr int kBasisBytes = kBasisRows * 8 * 8;
 // FP32 -> BF16 bits, round to nearest even (finite inputs)
 __device__ __forceinline__ unsigned short bf16_rne(float x) {
   const uint32_t u = __float_as_uint(x);
@@ -526,10 +534,28 @@ __device__ __forceinline__ unsigned short bf16_rne(float x) {
 }
 __device__ __forceinline__ float bf16_to_f(unsigned short h) { return __uint_as_float((uint32_t)h << 16); }
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ int amdgcn_writelane(int val, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+
+// A value of each row of 16 lanes brought to every lane's column: rows 0 and 1,
+// the same of rows 2 and 3 in the upper half (even, odd); then the halves.
+__device__ __forceinline__ void exchange_rows(double x, double& even, double& odd) {
+  const u32x2_t w = __builtin_bit_cast(u32x2_t, x);
+  const auto a = __builtin_amdgcn_permlane16_swap(w[0], w[0], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(w[1], w[1], false, false);
+  even = __builtin_bit_cast(double, (u32x2_t){(uint32_t)a[0], (uint32_t)b[0]});
+  odd = __builtin_bit_cast(double, (u32x2_t){(uint32_t)a[1], (uint32_t)b[1]});
+}
+__device__ __forceinline__ void exchange_halves(double x, double& lower, double& upper) {
+  const u32x2_t w = __builtin_bit_cast(u32x2_t, x);
+  const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[0], false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(w[1], w[1], false, false);
+  lower = __builtin_bit_cast(double, (u32x2_t){(uint32_t)a[0], (uint32_t)b[0]});
+  upper = __builtin_bit_cast(double, (u32x2_t){(uint32_t)a[1], (uint32_t)b[1]});
+}
 
 // Four waves per SIMD (128 VGPRs; what the LDS allows too).
 template <bool BF16, int UPM, bool CNT>
@@ -552,7 +578,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
   constexpr bool kSignDF = UPM != UP_EXPLICIT;
   // gy's feature part (and RGB with the sign upstream) on BF16 products
   constexpr bool kDotGy = BF16 && kSignDF;
-  float* tab = lds_z;                                // [6][16] basis, the same from every wave
+  double* tab = (double*)lds_z;                      // [kBasisRows][8], the same from every wave
   float* ws = lds_z + kBasisBytes / 4 + (threadIdx.x >> 6) * (bwd_wave_lds(UPM) / 4);   // weight rows
   float* us = ws + kBatch * kWRow;                                                      // u rows
   lds_ptr wl = (lds_ptr)(ws + lane);                 // this lane's place in a row
@@ -575,12 +601,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
     partials += j * gr.slots * kSlotFloats;
     mask += j * gr.mask_stride;
   }
-  if (lane < 16) {
-    const float X = (float)(lane & 3) - 1.5f, Y = (float)(lane >> 2) - 1.5f;
-    const float b[6] = {1.f, X, Y, X * X, X * Y, Y * Y};
 #pragma unroll
-    for (int m = 0; m < 6; ++m) tab[m * 16 + lane] = b[m];
+  for (int h = 0; h < 2; ++h) {
+    const int i = lane + 64 * h, row = i >> 3, k = row < kBasisYY ? 0 : (row - kBasisYY) & 3;
+    const double X = (double)(i & 7) - 3.5, Y = (double)k + 0.5;
+    const double b = row == kBasisOne ? 1.0 : row == 1 ? X : row == 2 ? X * X : row < kBasisY ? Y * Y : row < kBasisXY ? Y : X * Y;
+    if (row < kBasisRows) tab[i] = b;
   }
+  asm volatile("" ::: "memory");
   // appearance of a group of four entries: lane 4 q + i loads channels 4 q ..
   // 4 q + 3 of entry i (q < 5; the lanes past them repeat the last channels)
   const __amdgpu_buffer_rsrc_t app_b = app_buffer(app);
@@ -720,8 +748,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
     // w_p (each weight term against the same upstream, so with a sign upstream
     // every product is exact and only the FP32 accumulation rounds), and the
     // moments of u.  Lane (grp, col) gets channels 4 grp .. 4 grp + 3 of entry
-    // col, channels 16 .. 19 in group 0, and the moments 1, X, Y, X^2 in group
-    // 1; 1, X, Y, X Y in group 2; 1, Y, Y, Y^2 in group 3.
+    // col, channels 16 .. 19 in group 0, and of the moments 1, X, X^2, Y^2 and
+    // Y, X Y, Y, X Y one each in the four groups.
     auto flush = [&]() {
       // (its lane constants are worked out here: the registers that they would
       // hold across the entry loop are short)
@@ -734,23 +762,29 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
       const float emx = ge->mx, emy = ge->my;
       const uint32_t ebb = ge->bbox, esb = slot_base[re];
       asm volatile("" ::: "memory");
-      f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f}, m[4];
+      f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
+      // K index: row distance grp; lane's row of A: col & 3
+      double me = 0.0, mo = 0.0;   // of the sums and of the differences of mirrored rows
       {
-        // K index: pixel (s, grp) of the quarter; the basis row that this
-        // lane's row of A repeats (rows 0-3 are not used)
-        const int trow = (int)(((col < 8 ? 0x32100000u : 0x52204210u) >> (4 * (col & 7))) & 15u);
-        const f32x4 ta = *(const f32x4*)(tab + trow * 16 + 4 * grp);
-        const float* ur = us + col * kWRow + 8 * grp;
-        f32x4 ub[4];
+        const int row = col & 3;
+        const double* te = tab + 8 * (row < 3 ? row : kBasisYY + grp);
+        const double* to = tab + 8 * ((row & 1 ? kBasisXY : kBasisY) + grp);
+        const float *ua = us + col * kWRow + 8 * (4 + grp), *ub = us + col * kWRow + 8 * (3 - grp);
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {   // quarter h: columns 4 (h & 1) .., rows 4 (h >> 1) .. of the block
-          ub[h] = *(const f32x4*)(ur + 32 * (h >> 1) + 4 * (h & 1));
-          m[h] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int x = 0; x < 8; x += 4) {
+          const f32x4 a = *(const f32x4*)(ua + x), b = *(const f32x4*)(ub + x);
+#pragma unroll
+          for (int i = 0; i < 4; i += 2) {
+            const f64x2 e = *(const f64x2*)(te + x + i), o = *(const f64x2*)(to + x + i);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const double p = (double)a[i + h], q = (double)b[i + h];
+              me = __builtin_amdgcn_mfma_f64_4x4x4f64(e[h], p + q, me, 0, 0, 0);
+              mo = __builtin_amdgcn_mfma_f64_4x4x4f64(o[h], p - q, mo, 0, 0, 0);
+            }
+          }
+          asm volatile("" ::: "memory");   // (half a row's operands at a time: no spills)
         }
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int h = 0; h < 4; ++h) m[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(ta[s], ub[h][s], m[h], 0, 0, 0);
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -808,35 +842,31 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
       asm volatile("" ::: "memory");
       const uint32_t ebx = ebb & 255u, eby = (ebb >> 16) & 255u;
       const uint32_t sl = esb + (by - eby) * (((ebb >> 8) & 255u) - ebx + 1u) + (bx - ebx);
-      // dx = X + xq, dy = Y + yq in quarter h; groups 1 and 3 move their second
-      // moment (X^2 along x, Y^2 along y) by the same steps, group 2 X Y
-      const float x0 = ((float)(8 * ((int)bx - (int)ebx)) - emx) + 1.5f;
-      const float y0 = ((float)(8 * ((int)by - (int)eby)) - emy) + 1.5f;
-      float g0 = 0.f, g1 = 0.f, g2 = 0.f, g3 = 0.f, gxy = 0.f;
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        const float xq = (h & 1) ? x0 + 4.f : x0, yq = (h >> 1) ? y0 + 4.f : y0;
-        const float pq = grp == 3 ? yq : xq;
-        const float f1 = __builtin_fmaf(pq, m[h][0], m[h][1]), f2 = __builtin_fmaf(yq, m[h][0], m[h][2]);
-        g0 += m[h][0];
-        g1 += f1;
-        g2 += f2;
-        g3 += __builtin_fmaf(pq, m[h][1] + f1, m[h][3]);
-        gxy += __builtin_fmaf(xq, f2, __builtin_fmaf(yq, m[h][1], m[h][3]));
-      }
+      // dx = X + x0, dy = Y + y0
+      const double x0 = (double)(8 * ((int)bx - (int)ebx)) - (double)emx + 3.5;
+      const double y0 = (double)(8 * ((int)by - (int)eby)) - (double)emy + 3.5;
+      double e02, e13, m0, mx, mxx, myy, my, mxy;
+      exchange_rows(me, e02, e13);
+      exchange_halves(e02, m0, mxx);
+      exchange_halves(e13, mx, myy);
+      exchange_rows(mo, my, mxy);
+      const double fx = __builtin_fma(x0, m0, mx), fy = __builtin_fma(y0, m0, my);
+      const double gxy = __builtin_fma(x0, fy, __builtin_fma(y0, mx, mxy));
+      // X^2 along x in group 1, Y^2 along y in group 3
+      const double g2 = grp == 3 ? __builtin_fma(y0, my + fy, myy) : __builtin_fma(x0, mx + fx, mxx);
       const float s0 = grp == 0 ? gscale[0] : gscale[2], s3 = grp == 0 ? gscale[1] : gscale[2];
       float* rec = partials + (size_t)sl * kSlotFloats;
       if (col < nb) {
         *(float4*)(rec + 4 * grp) = make_float4(c0[0] * s0, c0[1] * s0, c0[2] * s0, c0[3] * s3);
         if (grp < 2) {
           float4 v4;
-          v4.x = grp == 0 ? c1[0] * gscale[2] : g1;   // Sx
-          v4.y = grp == 0 ? c1[1] * gscale[2] : g2;   // Sy
-          v4.z = grp == 0 ? c1[2] * gscale[2] : g3;   // Sxx
-          v4.w = grp == 0 ? c1[3] * gscale[2] : g0;   // S0
+          v4.x = grp == 0 ? c1[0] * gscale[2] : (float)fx;   // Sx
+          v4.y = grp == 0 ? c1[1] * gscale[2] : (float)fy;   // Sy
+          v4.z = grp == 0 ? c1[2] * gscale[2] : (float)g2;   // Sxx
+          v4.w = grp == 0 ? c1[3] * gscale[2] : (float)m0;   // S0
           *(float4*)(rec + 16 + 4 * grp) = v4;
         } else {
-          rec[22 + grp] = grp == 2 ? gxy : g3;        // Sxy, Syy
+          rec[22 + grp] = (float)(grp == 2 ? gxy : g2);      // Sxy, Syy
         }
         if (grp == 0) mask[sl] = 1;
       }
