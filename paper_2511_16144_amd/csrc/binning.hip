@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(ScanArgs first, Scan
 constexpr int kFrontThreads = 1024, kFrontWaves = kFrontThreads / 64;
 constexpr int kFrontItems = (int)(kSmallFront / kFrontThreads);   // 4
 constexpr int kFrontBits = 8, kFrontPasses = 32 / kFrontBits;
-struct FrontLds {
+struct alignas(16) FrontLds {   // (cnt is cleared 16 bytes at a time)
   uint32_t key[kSmallFront];
   uint16_t id[kSmallFront];
   uint16_t cnt[kFrontWaves][1 << kFrontBits];   // a wave's keys of a digit, then those of the waves before it
@@ -228,6 +228,7 @@ struct FrontLds {
   uint32_t sh[2][kFrontWaves];
 };
 static_assert(sizeof(FrontLds) <= 160 * 1024, "the lists fit in LDS");
+static_assert(offsetof(FrontLds, cnt) % 16 == 0 && sizeof(FrontLds::cnt) % 16 == 0, "16-byte stores");
 
 // exclusive scans of two values per thread over the work-group
 __device__ __forceinline__ uint2 front_scan2(uint32_t x, uint32_t y, uint32_t (*sh)[kFrontWaves], uint2& total) {

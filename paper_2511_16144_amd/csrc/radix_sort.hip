@@ -169,7 +169,8 @@ __global__ void __launch_bounds__(THREADS) k_scatter(const uint32_t* __restrict_
   constexpr int kTile = THREADS * kIters, kWaves = THREADS / 64;
   constexpr int kOwn = 4;   // digits to a thread
   static_assert(kOwn * THREADS >= (1 << MAXBITS), "every digit has its thread");
-  __shared__ uint16_t cnt[kWaves][1 << MAXBITS];   // a wave's keys of a digit, then those of the waves before it
+  // a wave's keys of a digit, then those of the waves before it (two counts to a word where that pays)
+  __shared__ alignas(16) uint16_t cnt[kWaves][1 << MAXBITS];
   __shared__ uint32_t first[1 << MAXBITS];         // position of the block's first key of a digit
   __shared__ uint32_t sh[kWaves];
   const int64_t n = count_of(n_dev, n_max);
@@ -219,6 +220,9 @@ __global__ void __launch_bounds__(THREADS) k_scatter(const uint32_t* __restrict_
     }
   }
   for (int d = lane; d < g.D / 2; d += 64) ((uint32_t*)cnt[wave])[d] = 0u;
+  // (words and halves are distinct types to the compiler: without the fence it
+  // may count before it clears)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   uint64_t peers[kIters];

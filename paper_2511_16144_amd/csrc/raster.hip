@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
     app = (const char*)app + blockIdx.y * gr.app_stride;
     work_q += blockIdx.y * kQueueWords;
   }
-  extern __shared__ float lds_f[];
+  extern __shared__ __attribute__((aligned(16))) float lds_f[];
   float* ws = lds_f + (threadIdx.x >> 6) * (kFwdWaveLds / 4);
   unsigned short* ys = (unsigned short*)(ws + kFwdW);
   unsigned short* yz = ys + kFwdY;
@@ -570,7 +570,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
     const float* __restrict__ T_state, const uint32_t* __restrict__ slot_base,
     float* __restrict__ partials, uint8_t* __restrict__ mask) {
   const int lane = threadIdx.x & 63;
-  extern __shared__ float lds_z[];
+  extern __shared__ __attribute__((aligned(16))) float lds_z[];
   // upstream per channel: the sign of the L1 residual (formed here from the
   // forward's images and the targets; exact in BF16, the per-channel scale is
   // applied after the product) or a given FP32 value (split hi + lo)
