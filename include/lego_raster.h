@@ -90,7 +90,7 @@ typedef struct {
   float T_eps;      /* 1e-4    stop before T' < T_eps */
   float cutoff2;    /* 9.0     largest m2 that contributes */
   int32_t tile;     /* 16      binning tile side: 8, 16 or 32 */
-  int32_t chunk;    /* 4       8x8 pixel blocks per work-group (1, 2, 4, 8) */
+  int32_t chunk;    /* 4       8x8 pixel blocks per work-group (1, 2, 4; 8 runs as 4) */
   int32_t order;    /* 0       work order of the compositing kernels' per-XCD queues:
                      *         0 raster order, neighbouring tiles on different XCDs;
                      *         1 descending tile-list length; 2 descending list length

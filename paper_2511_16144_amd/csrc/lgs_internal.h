@@ -273,7 +273,7 @@ void launch_raster_fwd(const Settings& st, const Groups& gr, const ViewDesc* vie
                        const uint2* ranges, const uint32_t* vals, const GeomRec* geom,
                        const void* app, int app_bf16, uint32_t npad_mask,
                        const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt,
-                       uint32_t* work_q, int waves_per_group, int32_t* last_idx, float* T_state, int n_contrib,
+                       uint32_t* work_q, int chunk, int32_t* last_idx, float* T_state, int n_contrib,
                        hipStream_t s);   // n_contrib: some view's out table asks for contributor counts
 // Upstream of the backward compositing kernel: dL/dY given per channel
 // (upstream), the L1 loss gradient formed from the forward's images and the
@@ -285,7 +285,7 @@ void launch_raster_bwd(int up_mode, const Settings& st, const Groups& gr, const 
                        const uint2* ranges, const uint32_t* vals, const GeomRec* geom,
                        const void* app, int app_bf16, uint32_t npad_mask,
                        const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt, uint32_t* work_q,
-                       int waves_per_group, const int32_t* last_idx, const float* T_state,
+                       int chunk, const int32_t* last_idx, const float* T_state,
                        const uint32_t* slot_base, float* partials, uint8_t* mask, hipStream_t s);
 
 // mapping loss (L1 + D-SSIM) and its gradient: the colour channels (L1 and

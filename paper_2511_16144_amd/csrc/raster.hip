@@ -33,6 +33,7 @@
 // results are deterministic run to run.
 #include "lgs_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace lgs {
@@ -1232,18 +1233,24 @@ __global__ void __launch_bounds__(256, 8) k_seg_reduce(Groups gr, const uint32_t
   }
 }
 
+// Waves of a compositing work-group: settings.chunk, at most the four that the
+// kernels are compiled for (256 threads).  The waves take blocks from the queues
+// one by one, so the results and the blocks do not depend on it.
+constexpr int kMaxWaves = 4;
+int group_threads(int chunk) { return 64 * std::min(chunk, kMaxWaves); }
+
 }  // namespace
 
 template <bool BF16, bool CNT, bool NC>
 static void launch_fwd_t(const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* out, const uint2* ranges,
                          const uint32_t* vals, const GeomRec* geom, const void* app, uint32_t npad_mask,
                          const uint32_t* items, const uint32_t* qoff, int64_t n_items, Counters* cnt,
-                         uint32_t* work_q, int waves_per_group, int32_t* last_idx, float* T_state, hipStream_t s) {
-  const int threads = 64 * waves_per_group;
-  const size_t lds = BF16 ? (size_t)waves_per_group * kFwdWaveLds : 0;
+                         uint32_t* work_q, int chunk, int32_t* last_idx, float* T_state, hipStream_t s) {
+  const int threads = group_threads(chunk), waves = threads / 64;
+  const size_t lds = BF16 ? (size_t)waves * kFwdWaveLds : 0;
   static Residency known;
   int64_t grid = resident_groups(known, k_raster_fwd<BF16, CNT, NC>, threads, lds);
-  const int64_t need = (n_items + waves_per_group - 1) / waves_per_group;
+  const int64_t need = (n_items + waves - 1) / waves;
   if (grid > need) grid = need;
   if (grid < kQueues) grid = kQueues;   // every queue needs a workgroup (index mod kQueues) to drain it
   hipLaunchKernelGGL((k_raster_fwd<BF16, CNT, NC>), dim3((unsigned)grid, gr.count), dim3(threads), lds, s, st, gr, views, out,
@@ -1254,12 +1261,12 @@ static void launch_fwd_t(const Settings& st, const Groups& gr, const ViewDesc* v
 void launch_raster_fwd(const Settings& st, const Groups& gr, const ViewDesc* views, const ViewImages* out, const uint2* ranges,
                        const uint32_t* vals, const GeomRec* geom, const void* app, int app_bf16,
                        uint32_t npad_mask, const uint32_t* items, const uint32_t* qoff, int64_t n_items,
-                       Counters* cnt, uint32_t* work_q, int waves_per_group, int32_t* last_idx, float* T_state, int n_contrib,
+                       Counters* cnt, uint32_t* work_q, int chunk, int32_t* last_idx, float* T_state, int n_contrib,
                        hipStream_t s) {
   if (n_items <= 0) return;
 #define LGS_FWD(B, K, N)                                                                                     \
   launch_fwd_t<B, K, N>(st, gr, views, out, ranges, vals, geom, app, npad_mask, items, qoff, n_items, cnt,   \
-                        work_q, waves_per_group, last_idx, T_state, s)
+                        work_q, chunk, last_idx, T_state, s)
 #define LGS_FWD_N(B, K)        \
   if (n_contrib) LGS_FWD(B, K, true); \
   else LGS_FWD(B, K, false)
@@ -1279,13 +1286,13 @@ static void launch_bwd_t(const Settings& st, const Groups& gr, const ViewDesc* v
                          const ViewImages* fwd_out, const ViewImages* targets, const float* loss_w,
                          const uint2* ranges, const uint32_t* vals, const GeomRec* geom, const void* app,
                          uint32_t npad_mask, const uint32_t* items, const uint32_t* qoff, int64_t n_items,
-                         Counters* cnt, uint32_t* work_q, int waves_per_group, const int32_t* last_idx, const float* T_state,
+                         Counters* cnt, uint32_t* work_q, int chunk, const int32_t* last_idx, const float* T_state,
                          const uint32_t* slot_base, float* partials, uint8_t* mask, hipStream_t s) {
-  const int threads = 64 * waves_per_group;
-  const size_t lds = kBasisBytes + (size_t)waves_per_group * bwd_wave_lds(UPM);
+  const int threads = group_threads(chunk), waves = threads / 64;
+  const size_t lds = kBasisBytes + (size_t)waves * bwd_wave_lds(UPM);
   static Residency known;
   int64_t grid = resident_groups(known, k_raster_bwd<BF16, UPM, CNT>, threads, lds);
-  const int64_t need = (n_items + waves_per_group - 1) / waves_per_group;
+  const int64_t need = (n_items + waves - 1) / waves;
   if (grid > need) grid = need;
   if (grid < kQueues) grid = kQueues;   // every queue needs a workgroup (index mod kQueues) to drain it
   hipLaunchKernelGGL((k_raster_bwd<BF16, UPM, CNT>), dim3((unsigned)grid, gr.count), dim3(threads), lds, s, st, gr, views,
@@ -1297,16 +1304,16 @@ void launch_raster_bwd(int up_mode, const Settings& st, const Groups& gr, const 
                        const ViewImages* fwd_out, const ViewImages* targets, const float* loss_w,
                        const uint2* ranges, const uint32_t* vals, const GeomRec* geom, const void* app,
                        int app_bf16, uint32_t npad_mask, const uint32_t* items, const uint32_t* qoff,
-                       int64_t n_items, Counters* cnt, uint32_t* work_q, int waves_per_group, const int32_t* last_idx,
+                       int64_t n_items, Counters* cnt, uint32_t* work_q, int chunk, const int32_t* last_idx,
                        const float* T_state, const uint32_t* slot_base, float* partials, uint8_t* mask,
                        hipStream_t s) {
   if (n_items <= 0) return;
 #define LGS_BWD(B, M)                                                                                     \
   (st.count ? launch_bwd_t<B, M, true>(st, gr, views, upstream, fwd_out, targets, loss_w, ranges, vals, geom, app,  \
-                                       npad_mask, items, qoff, n_items, cnt, work_q, waves_per_group, last_idx,      \
+                                       npad_mask, items, qoff, n_items, cnt, work_q, chunk, last_idx,      \
                                        T_state, slot_base, partials, mask, s)                                 \
             : launch_bwd_t<B, M, false>(st, gr, views, upstream, fwd_out, targets, loss_w, ranges, vals, geom,  \
-                                        app, npad_mask, items, qoff, n_items, cnt, work_q, waves_per_group, last_idx, \
+                                        app, npad_mask, items, qoff, n_items, cnt, work_q, chunk, last_idx, \
                                         T_state, slot_base, partials, mask, s))
   if (app_bf16) {
     if (up_mode == UP_L1) LGS_BWD(true, UP_L1);
