@@ -106,6 +106,14 @@ void sweep_deferred(lgs_context* ctx) {
           d.end());
 }
 
+// hipMalloc that leaves no error behind when it fails (the caller tries
+// something else, and a launch check after it would report the old error)
+bool device_alloc(void** p, size_t bytes) {
+  if (hipMalloc(p, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 // A device block of at least `bytes` for work enqueued on `stream`: a cached
 // block (the stream first waits, on the device, for the block's previous
 // user) or a new allocation.
@@ -123,16 +131,17 @@ void* pool_alloc(lgs_context* ctx, size_t bytes, hipStream_t stream) {
   }
   // a new block between 4 and 17 MB takes hipMalloc 140 to 270 us, one of 17 MB
   // and more 30
+  const size_t asked = bytes;
   if (bytes > (4u << 20) && bytes < (17u << 20)) bytes = 17u << 20;
   void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    // drop the cache and retry once
+  if (!device_alloc(&p, bytes)) {
+    // drop the cache and retry, at last with no more than was asked for
     for (auto& kv : ctx->free_blocks) {
       if (kv.second.ready) hipEventSynchronize(kv.second.ready.get());
       hipFree(kv.second.p);
     }
     ctx->free_blocks.clear();
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    if (!device_alloc(&p, bytes) && (bytes == asked || !device_alloc(&p, bytes = asked))) return nullptr;
   }
   ctx->live[p] = bytes;
   return p;
@@ -479,15 +488,21 @@ void* w_alloc(Work* W, size_t bytes, bool& ok) {
   return p;
 }
 
-// Give the buffers back to the context without waiting: they (and the host
-// tables) become reusable once the work enqueued so far on the Work's stream
-// has run.
-void w_release(Work* W) {
+// Give the buffers from number `from` on back to the context without waiting:
+// they become reusable once the work enqueued so far on the Work's stream has
+// run (the returned event; null: it has).
+SharedEvent w_give_back(Work* W, size_t from) {
   SharedEvent ev = make_event();
   if (ev && hipEventRecord(ev.get(), W->stream) != hipSuccess) ev.reset();
   if (!ev) hipStreamSynchronize(W->stream);
-  for (void* p : W->bufs) pool_free(W->ctx, p, ev);
-  W->bufs.clear();
+  for (size_t i = from; i < W->bufs.size(); ++i) pool_free(W->ctx, W->bufs[i], ev);
+  W->bufs.resize(from);
+  return ev;
+}
+
+// All of them, and the host tables.
+void w_release(Work* W) {
+  const SharedEvent ev = w_give_back(W, 0);
   if (!W->host_keep.empty()) {
     W->ctx->deferred.push_back(DeferredHost{ev, std::move(W->host_keep)});
     W->host_keep.clear();
@@ -500,29 +515,45 @@ void w_release(Work* W) {
     }
 }
 
-// Buffers of a Work that share one block of the pool, each on a 256-byte line.
+// Buffers of a Work that share one block of the pool, each on a 256-byte line;
+// where no block holds them all, they get blocks of their own (those added as
+// `joined` stay behind the one before them).
 class Carve {
  public:
   template <class T>
-  void add(T*& p, size_t bytes) {
-    parts_.push_back({(void*)&p, total_});
+  void add(T*& p, size_t bytes, bool joined = false) {
+    parts_.push_back({(void*)&p, total_, joined});
     total_ += (bytes + 255) / 256 * 256;
   }
+  // all of the buffers, or none (and all pointers null)
   bool get(Work* W) {
+    const size_t held = W->bufs.size();
+    if (take(W, 0, parts_.size())) return true;
     bool ok = true;
-    char* base = (char*)w_alloc(W, total_, ok);
-    for (const Part& x : parts_) {
-      char* at = ok ? base + x.off : nullptr;
-      memcpy(x.p, &at, sizeof at);
+    for (size_t i = 0, j; ok && i < parts_.size(); i = j) {
+      for (j = i + 1; j < parts_.size() && parts_[j].joined;) ++j;
+      ok = take(W, i, j);
     }
-    return ok;
+    if (ok) return true;
+    for (const Part& x : parts_) set(x, nullptr);
+    w_give_back(W, held);
+    return false;
   }
 
  private:
   struct Part {
     void* p;   // the pointer to set
     size_t off;
+    bool joined;
   };
+  static void set(const Part& x, char* at) { memcpy(x.p, &at, sizeof at); }
+  bool take(Work* W, size_t i, size_t j) {
+    bool ok = true;
+    const size_t off = i < j ? parts_[i].off : 0, end = j < parts_.size() ? parts_[j].off : total_;
+    char* base = (char*)w_alloc(W, end - off, ok);
+    for (; ok && i < j; ++i) set(parts_[i], base + (parts_[i].off - off));
+    return ok;
+  }
   std::vector<Part> parts_;
   size_t total_ = 0;
 };
@@ -600,11 +631,11 @@ lgs_status w_alloc_front(Work* W) {
   // (uploaded together: views and out; fo, tgt and lossw)
   block.add(W->d_views, sizeof(ViewDesc) * V);
   const int G = W->G;
-  block.add(W->d_out, sizeof(ViewImages) * V * G);
+  block.add(W->d_out, sizeof(ViewImages) * V * G, true);
   block.add(W->d_up, sizeof(ViewImages) * V * G);
   block.add(W->d_fo, sizeof(ViewImages) * V * G);
-  block.add(W->d_tgt, sizeof(ViewImages) * V * G);
-  block.add(W->d_lossw, 16 * G);
+  block.add(W->d_tgt, sizeof(ViewImages) * V * G, true);
+  block.add(W->d_lossw, 16 * G, true);
   if (G > 1) block.add(W->scratch_img, sizeof(float) * 5 * npix);
   block.add(W->geom, sizeof(GeomRec) * n_rid);
   block.add(W->cnt_t, 4 * n_rid);
@@ -657,19 +688,23 @@ constexpr int64_t kGroupBytes = 1ll << 31;
 
 lgs_status w_alloc_bwd(Work* W) {
   if (W->bwd_alloc) return LGS_OK;
-  Carve block;
   const int64_t S = std::max<int64_t>(W->cap_slots, 1), R = std::max<int64_t>(W->n_rid, 1);
   // as many feature groups at once as keep their records within 2 GB (a frame
-  // large enough to pass that fills the chip with one)
+  // large enough to pass that fills the chip with one), fewer where memory for
+  // so many is not to be had
   W->gb = (int)std::min<int64_t>(W->G, std::max<int64_t>(1, kGroupBytes / (4 * (S * kSlotFloats + R * kPartials))));
   W->grad2d_stride = R * kPartials;
   W->mask_stride = (S + 8 + 255) / 256 * 256;
-  block.add(W->partials, sizeof(float) * kSlotFloats * S * W->gb);
-  block.add(W->mask, W->mask_stride * W->gb);
-  block.add(W->grad2d, sizeof(float) * W->grad2d_stride * W->gb);
-  block.add(W->ttmp, project_bwd_temp_bytes(W->n_rid, (int)W->plan.views.size()));
-  if (W->gb < W->G) block.add(W->geo_acc, sizeof(float) * 6 * R);
-  if (!block.get(W)) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (backward)");
+  for (;; W->gb /= 2) {
+    Carve block;
+    block.add(W->partials, sizeof(float) * kSlotFloats * S * W->gb);
+    block.add(W->mask, W->mask_stride * W->gb);
+    block.add(W->grad2d, sizeof(float) * W->grad2d_stride * W->gb);
+    block.add(W->ttmp, project_bwd_temp_bytes(W->n_rid, (int)W->plan.views.size()));
+    if (W->gb < W->G) block.add(W->geo_acc, sizeof(float) * 6 * R);
+    if (block.get(W)) break;
+    if (W->gb == 1) return fail(W->ctx, LGS_ERR_HIP, "device allocation failed (backward)");
+  }
   // the slot mask starts at zero (the first backward clears it, together with
   // its counters); every reduction leaves it at zero again
   W->mask_words = W->mask_stride * W->gb / 4;
