@@ -299,8 +299,8 @@ int loss_tiles_x(int W);
 void launch_loss_rgb(const LossView* views, const LossConsts& k, int64_t n_blocks, float2* partials,
                      hipStream_t s);
 // colour, depth and features in one launch
-void launch_loss(const LossView* views, const LossConsts& k, int64_t n_rgb, int64_t n_df, float2* part_rgb,
-                 float2* part_df, hipStream_t s);
+void launch_loss(const LossView* views, const LossConsts& k, int feat_dim, int64_t n_rgb, int64_t n_df,
+                 float2* part_rgb, float2* part_df, hipStream_t s);
 void launch_loss_terms(const LossView* views, int n_views, int ssim, const float2* part_rgb,
                        const float2* part_df, float* terms, hipStream_t s);
 

@@ -80,7 +80,8 @@ __device__ __forceinline__ void block_sum2(float& a, float& b, float* red) {
   b = (red[1] + red[3]) + (red[5] + red[7]);
 }
 
-// colour: work-group b's tile and channel
+// colour: work-group b's tile and channel (SSIM: lambda is not 0)
+template <bool SSIM>
 __device__ __forceinline__ void loss_rgb(const LossView* __restrict__ views, const LossConsts& k, int b, float* lds,
                                          float* red, float2* __restrict__ partials) {
   const int t = threadIdx.x;
@@ -96,7 +97,7 @@ __device__ __forceinline__ void loss_rgb(const LossView* __restrict__ views, con
     const float* __restrict__ X = V.x + (size_t)role * plane;
     const float* __restrict__ Y = V.xt + (size_t)role * plane;
     float* __restrict__ G = V.gx + (size_t)role * plane;
-    if (!k.ssim) {
+    if constexpr (!SSIM) {
       for (int e = t; e < kLT * kLT; e += kLossThreads) {
         const int gy = y0 + (e >> 5), gx = x0 + (e & 31);
         if (gy < H && gx < W) {
@@ -384,22 +385,29 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_rgb(const LossView* __res
                                                            float2* __restrict__ partials) {
   __shared__ float lds[kLdsFloats];
   __shared__ float red[8];
-  loss_rgb(views, k, (int)blockIdx.x, lds, red, partials);
+  loss_rgb<true>(views, k, (int)blockIdx.x, lds, red, partials);
 }
 
-// Both, in one launch: the colour work-groups are bound by their vector
-// instructions and the depth / feature ones by memory, so the two are mixed
+// Both, in one launch.  With the stencil the colour work-groups are bound by their
+// vector instructions and the depth / feature ones by memory, so the two are mixed
 // evenly over the grid (df work-group i is the first whose share of nd reaches
-// i + 1).
+// i + 1).  Without it (lambda 0) both are bound by memory, and colour work-groups
+// in between cost the streaming ones the locality of their planes: where there
+// are enough of those to fill the chip, and more than a few planes, they come
+// first (df_first).  Eight views of 640 x 480, lambda 0, us, mixed and so: D = 8
+// 81, 83; 16 135, 127; 64 446, 397; 128 861, 766 (as kernels of their own 103, 150,
+// 422, 789); one view of 157 x 119, D = 128: 88, 93.
+template <bool SSIM>
 __global__ __launch_bounds__(kLossThreads) void k_loss(const LossView* __restrict__ views, LossConsts k, uint32_t nb,
-                                                       uint32_t nd, float2* __restrict__ part_rgb,
+                                                       uint32_t nd, int df_first, float2* __restrict__ part_rgb,
                                                        float2* __restrict__ part_df) {
-  __shared__ float lds[kLdsFloats];
+  __shared__ float lds[SSIM ? kLdsFloats : 1];
   __shared__ float red[8];
   const uint64_t b = blockIdx.x, n = nb + nd;
-  const uint32_t before = (uint32_t)(b * nd / n);   // df work-groups before this one
-  if ((uint32_t)((b + 1) * nd / n) > before) loss_df(views, k.n_views, (int)before, red, part_df);
-  else loss_rgb(views, k, (int)(b - before), lds, red, part_rgb);
+  const uint32_t before = df_first ? min((uint32_t)b, nd) : (uint32_t)(b * nd / n);   // df work-groups before this one
+  const uint32_t through = df_first ? min((uint32_t)b + 1u, nd) : (uint32_t)((b + 1) * nd / n);
+  if (through > before) loss_df(views, k.n_views, (int)before, red, part_df);
+  else loss_rgb<SSIM>(views, k, (int)(b - before), lds, red, part_rgb);
 }
 
 // Per view: the four loss terms from the work-groups' partial sums, added in
@@ -455,11 +463,12 @@ void launch_loss_rgb(const LossView* views, const LossConsts& k, int64_t n_block
     hipLaunchKernelGGL(k_loss_rgb, dim3((unsigned)n_blocks), dim3(kLossThreads), 0, s, views, k, partials);
 }
 
-void launch_loss(const LossView* views, const LossConsts& k, int64_t n_rgb, int64_t n_df, float2* part_rgb,
-                 float2* part_df, hipStream_t s) {
+void launch_loss(const LossView* views, const LossConsts& k, int feat_dim, int64_t n_rgb, int64_t n_df,
+                 float2* part_rgb, float2* part_df, hipStream_t s) {
+  const int df_first = !k.ssim && feat_dim > 8 && n_df >= 256;
   if (n_rgb + n_df > 0)
-    hipLaunchKernelGGL(k_loss, dim3((unsigned)(n_rgb + n_df)), dim3(kLossThreads), 0, s, views, k, (uint32_t)n_rgb,
-                       (uint32_t)n_df, part_rgb, part_df);
+    hipLaunchKernelGGL(k.ssim ? k_loss<true> : k_loss<false>, dim3((unsigned)(n_rgb + n_df)), dim3(kLossThreads), 0, s,
+                       views, k, (uint32_t)n_rgb, (uint32_t)n_df, df_first, part_rgb, part_df);
 }
 
 void launch_loss_terms(const LossView* views, int n_views, int ssim, const float2* part_rgb,

@@ -1245,7 +1245,7 @@ lgs_status lgs_loss(lgs_context* ctx, int32_t n_views, const lgs_camera* cams, i
                               stream));
   HIP_TRY(ctx, hipEventRecord(ctx->loss_copied, stream));
   const LossConsts k = loss_consts(ssim_lambda, n_views);
-  launch_loss(ctx->loss_tab, k, nb, nd, ctx->loss_part, ctx->loss_part + nb, stream);
+  launch_loss(ctx->loss_tab, k, feat_dim, nb, nd, ctx->loss_part, ctx->loss_part + nb, stream);
   if (terms) launch_loss_terms(ctx->loss_tab, n_views, k.ssim, ctx->loss_part, ctx->loss_part + nb, terms, stream);
   HIP_TRY(ctx, hipGetLastError());
   return LGS_OK;
