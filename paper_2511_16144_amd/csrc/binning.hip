@@ -394,6 +394,7 @@ __global__ void __launch_bounds__(kFrontThreads) k_small_front(FrontLists f, uin
 constexpr int kEmitThreads = 256;
 constexpr int kEmitPerThread = 4;
 constexpr int kEmitTile = kEmitThreads * kEmitPerThread;   // 1024 pairs per block
+constexpr int kEmitZero = kEmitThreads * 16;               // words zeroed per block, at most
 
 // The first index i with a[i] > x (n if none) of a non-decreasing array,
 // found by one wave: each step the 64 lanes probe 64 evenly
@@ -621,7 +622,10 @@ void launch_small_front(const FrontLists& f, int64_t n_rid, Counters* cnt, hipSt
 void launch_emit(const GeomRec* geom, const ViewDesc* views, const uint32_t* srid, const uint32_t* off_t,
                  Counters* cnt, int64_t cap_pairs, int64_t cap_slots, int npad_shift,
                  int tile_shift, uint32_t* keys, uint32_t* vals, uint32_t* zero, int64_t n_zero, hipStream_t s) {
-  const int64_t blocks = std::max<int64_t>(1, (cap_pairs + kEmitTile - 1) / kEmitTile);
+  // enough blocks for the words to be zeroed, too (no pairs over the tiles of 8
+  // of eight views of 2048 x 2048: 107 -> 5 us)
+  const int64_t blocks = std::max<int64_t>({1, (cap_pairs + kEmitTile - 1) / kEmitTile,
+                                            (n_zero + kEmitZero - 1) / kEmitZero});
   hipLaunchKernelGGL(k_emit, dim3((unsigned)blocks), dim3(kEmitThreads), 0, s, geom, views, srid, off_t,
                      cnt, cap_pairs, cap_slots, npad_shift, tile_shift, keys, vals, zero, n_zero);
 }
