@@ -304,56 +304,101 @@ __global__ void __launch_bounds__(kPairThreads) k_prune_pairs(PruneArgs a, const
 }
 
 // The listed Gaussians, which have more than K neighbours within tau_dist: one
-// thread each, the K best (squared distance, index) pairs in a sorted list.
-template <bool BF16>
-__global__ void __launch_bounds__(256) k_prune_heavy(PruneArgs a, const uint32_t* __restrict__ start,
-                                                     const float4* __restrict__ pos,
-                                                     const Rec<BF16>* __restrict__ rec, uint8_t* __restrict__ sem,
-                                                     const uint32_t* __restrict__ heavy,
-                                                     const PruneCounters* __restrict__ pc) {
+// thread each, the K best (squared distance, index) pairs in a sorted list of
+// KMAX.  What bounds it is the chain of one thread, and in it the list's (a
+// candidate is carried past every entry): so candidates are read eight at a
+// time, those within tau_dist wait in LDS, and the wave inserts when a lane has
+// no more room, each lane its own next one.  A round for every candidate, which
+// one of 64 lanes is always near, takes three times as many.  One wave to a
+// work-group, as there may be few.  The whole pass, us, with cells sorted and a list
+// for every Gaussian / with a round for every candidate here / so: 60k of 10
+// neighbours each, K = 16 490, 590, 162; of 40, K = 32 940, 1090, 450; 20k of 1000,
+// K = 16 10930, 11040, 2710; 200k of 200, K = 16 5430, 4510, 1820.  (Room for 64
+// waiting: the last 2630, as fewer waves fit.)
+constexpr int kHeavyThreads = 64, kHeavyRoom = 32;
+template <bool BF16, int KMAX>
+__global__ void __launch_bounds__(kHeavyThreads) k_prune_heavy(PruneArgs a, const uint32_t* __restrict__ start,
+                                                               const float4* __restrict__ pos,
+                                                               const Rec<BF16>* __restrict__ rec,
+                                                               uint8_t* __restrict__ sem,
+                                                               const uint32_t* __restrict__ heavy,
+                                                               const PruneCounters* __restrict__ pc) {
+  constexpr uint32_t kAhead = 8;
+  __shared__ double wait_d[kHeavyRoom][kHeavyThreads];
+  __shared__ uint32_t wait_j[kHeavyRoom][kHeavyThreads];
   const uint32_t nh = pc->n_heavy, n_pos = start[a.buckets];
-  for (uint32_t h = blockIdx.x * 256u + threadIdx.x; h < nh; h += gridDim.x * 256u) {
-    const uint32_t s = heavy[h];
+  const int lane = threadIdx.x;
+  for (uint32_t h0 = blockIdx.x * kHeavyThreads; h0 < nh; h0 += gridDim.x * kHeavyThreads) {
+    const bool live = h0 + lane < nh;
+    const uint32_t s = heavy[live ? h0 + lane : nh - 1u];
     const float4 p = pos[s];
     const uint32_t i = __float_as_uint(p.w);
     int32_t c[3];
     cell_of(a, p.x, p.y, p.z, c);
     // ascending; unused = +inf
-    double bd[kPruneKMax];
-    uint32_t bj[kPruneKMax];
+    double bd[KMAX];
+    uint32_t bj[KMAX];
 #pragma unroll
-    for (int m = 0; m < kPruneKMax; ++m) {
+    for (int m = 0; m < KMAX; ++m) {
       bd[m] = INFINITY;
       bj[m] = 0xffffffffu;
     }
+    int waiting = 0;
 #pragma unroll 1
-    for (int r = 0; r < kRuns; ++r) {
-      uint32_t lo, hi;
-      run_of(a, c, r, start, n_pos, lo, hi);
-      for (uint32_t t = lo; t < hi; ++t) {
-        const float4 q = pos[min(t, t - n_pos)];
-        const uint32_t j = __float_as_uint(q.w);
-        const double d2 = dist2(p, q);
-        if (j == i || !(d2 < a.tau2)) continue;
-        // insert into the sorted list: carry the candidate down, swapping
-        // it with every entry it precedes (static indices: registers)
-        double cd = d2;
-        uint32_t cj = j;
+    for (int r = 0; r <= kRuns; ++r) {   // (after the runs: those still waiting)
+      uint32_t t = 0u, hi = 0u;
+      if (r < kRuns) run_of(a, c, r, start, n_pos, t, hi);
+      if (!live) hi = t;
+#pragma unroll 1
+      for (bool more = true; more;) {
+        more = __builtin_amdgcn_ballot_w64(t < hi) != 0ull;
+        if (more) {
+          float4 v[kAhead];
 #pragma unroll
-        for (int m = 0; m < kPruneKMax; ++m) {
-          const bool before = cd < bd[m] || (cd == bd[m] && cj < bj[m]);
-          const double td = bd[m];
-          const uint32_t tj = bj[m];
-          bd[m] = before ? cd : td;
-          bj[m] = before ? cj : tj;
-          cd = before ? td : cd;
-          cj = before ? tj : cj;
+          for (uint32_t q = 0; q < kAhead; ++q)   // (past the run's end: the Gaussian itself)
+            v[q] = pos[t < hi && t + q < hi ? min(t + q, t + q - n_pos) : s];
+          if (t < hi) t += kAhead;
+#pragma unroll
+          for (int q = 0; q < kAhead; ++q) {
+            const double d2 = dist2(p, v[q]);
+            const uint32_t j = __float_as_uint(v[q].w);
+            if (j != i && d2 < a.tau2) {
+              wait_d[waiting][lane] = d2;
+              wait_j[waiting][lane] = j;
+              ++waiting;
+            }
+          }
         }
+        if (r < kRuns && __builtin_amdgcn_ballot_w64(waiting > kHeavyRoom - (int)kAhead) == 0ull) continue;
+#pragma unroll 1
+        for (int q = 0; __builtin_amdgcn_ballot_w64(q < waiting) != 0ull; ++q) {
+          // carry the candidate down, swapping it with every entry it precedes
+          // (static indices: registers; a lane without one carries the end's mark)
+          const bool has = q < waiting;
+          double cd = has ? wait_d[q][lane] : INFINITY;
+          uint32_t cj = has ? wait_j[q][lane] : 0xffffffffu;
+          const bool in = cd < bd[KMAX - 1] || (cd == bd[KMAX - 1] && cj < bj[KMAX - 1]);
+          if (__builtin_amdgcn_ballot_w64(in) == 0ull) continue;
+#pragma unroll
+          for (int m = 0; m < KMAX; ++m) {
+            const bool before = cd < bd[m] || (cd == bd[m] && cj < bj[m]);
+            const double td = bd[m];
+            const uint32_t tj = bj[m];
+            bd[m] = before ? cd : td;
+            bj[m] = before ? cj : tj;
+            cd = before ? td : cd;
+            cj = before ? tj : cj;
+          }
+        }
+        waiting = 0;
       }
     }
+    static_assert(KMAX <= kHeavyRoom, "the list fits");
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) wait_j[m][lane] = bj[m];
 #pragma unroll 1
     for (int m = 0; m < a.k; ++m) {
-      const uint32_t j = bj[m];
+      const uint32_t j = wait_j[m][lane];
       if (j == 0xffffffffu) break;
       mark_if_redundant(a, rec, i, j, sem);
     }
@@ -424,7 +469,8 @@ void launch_t(const PruneArgs& a, const PruneWork& w, hipStream_t s) {
   const size_t lds = (size_t)(kRunWords + a.k) * kPairThreads * sizeof(uint32_t) + (size_t)kPairThreads * a.k;
   hipLaunchKernelGGL(k_prune_pairs<BF16>, dim3(blocks(a.n, kPairThreads)), dim3(kPairThreads), lds, s, a,
                      (const uint32_t*)w.start, (const float4*)w.pos, (const Rec<BF16>*)rec, w.sem, w.list, w.pc);
-  hipLaunchKernelGGL(k_prune_heavy<BF16>, dim3(std::min(blocks(a.n, 256), 2048u)), dim3(256), 0, s, a,
+  hipLaunchKernelGGL((a.k <= kPruneKMax / 2 ? k_prune_heavy<BF16, kPruneKMax / 2> : k_prune_heavy<BF16, kPruneKMax>),
+                     dim3(std::min(blocks(a.n, kHeavyThreads), 8192u)), dim3(kHeavyThreads), 0, s, a,
                      (const uint32_t*)w.start, (const float4*)w.pos, (const Rec<BF16>*)rec, w.sem,
                      (const uint32_t*)w.list, (const PruneCounters*)w.pc);
 }
