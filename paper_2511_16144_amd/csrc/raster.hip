@@ -700,9 +700,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
     float gscale[3] = {1.f, 1.f, 1.f};
     if (kSignDF) {
       const float HWf = (float)HW;
-      gscale[0] = kSignRGB ? loss_w[0] / (3.f * HWf) : 1.f;
-      gscale[1] = loss_w[1] / HWf;
-      gscale[2] = loss_w[2] / (16.f * HWf);
+      // (the rows hold g's sign, which is the weight's times the residual's)
+      gscale[0] = kSignRGB ? fabsf(loss_w[0]) / (3.f * HWf) : 1.f;
+      gscale[1] = fabsf(loss_w[1]) / HWf;
+      gscale[2] = fabsf(loss_w[2]) / (16.f * HWf);
     }
     asm volatile("" ::: "memory");   // (the last block's record reads come before)
 #pragma unroll
