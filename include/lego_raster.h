@@ -333,7 +333,7 @@ lgs_status lgs_decoder_l1_noalloc(lgs_context *ctx, int32_t width,
  *           prune where non-zero (overwritten)
  *   counts  NULL or host int64 [3]: redundant, geometric, pruned (either)
  * Distances and similarities are evaluated in FP64.  Synchronises with
- * `stream` (two small readbacks).  LGS_ERR_INVALID_ARG for bad parameters
+ * `stream` (one small readback).  LGS_ERR_INVALID_ARG for bad parameters
  * or NULL arrays; LGS_ERR_UNSUPPORTED when a mean lies more than 2^20 cells
  * of tau_dist from the origin along an axis. */
 typedef struct {

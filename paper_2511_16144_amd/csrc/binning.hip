@@ -101,8 +101,6 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(ScanArgs first, Sc
   if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-// one work-group scans the block sums in place (exclusive) and writes total
-
 template <int MODE>
 __global__ void __launch_bounds__(kScanThreads) k_scan_down(ScanArgs first, ScanArgs second, int64_t n_max) {
   const ScanArgs& A = blockIdx.y ? second : first;
@@ -447,7 +445,6 @@ __global__ void __launch_bounds__(kEmitThreads) k_emit(
     const bool ov = P > cap_pairs || (int64_t)cnt->n_slots > cap_slots;
     cnt->overflow = ov ? 1u : 0u;
     cnt->n_pairs_eff = ov ? 0u : cnt->n_pairs;
-    cnt->n_slots_eff = ov ? 0u : cnt->n_slots;
   }
   if (P > cap_pairs) return;                 // overflow: nothing valid is written
   const int64_t p0 = (int64_t)blockIdx.x * kEmitTile;

@@ -129,9 +129,8 @@ struct __attribute__((aligned(128))) Counters {
   uint32_t n_slots;     // S
   uint32_t overflow;    // set when P exceeds the pair capacity
   uint32_t n_pairs_eff; // n_pairs, or 0 after an overflow
-  uint32_t n_slots_eff; // n_slots, or 0 after an overflow
   uint32_t n_long;      // visible ids with more than kLongSlots slots
-  uint32_t pad1;
+  uint32_t pad1[2];
   // work actually done by the compositing kernels (one atomic per wave):
   // (pixel, entry) evaluations and contributions, the list entries a wave
   // visited (its records were loaded), forward and backward, and the

@@ -22,8 +22,9 @@
 // shows every lane finished.  Waves pop blocks from per-XCD work queues
 // (persistent grid).
 //
-// Backward.  Each wave restarts from the last contributor of its pixels and
-// walks the list backwards, recovering T before each entry as T / (1 - alpha)
+// Backward.  Each wave restarts from the last entry that any of its pixels can
+// have taken (the list's end unless they all terminated before it) and walks the
+// list backwards, recovering T before each entry as T / (1 - alpha)
 // and the weighted sum of what lies behind as a single running scalar.  The
 // sums over the wave's pixels, 6 geometric (the moments 1, dx, dy, dx^2, dx dy,
 // dy^2 of dL/dalpha alpha) and 20 colour / depth / feature partials, sum_p w_p
@@ -457,11 +458,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ?
     atomicAdd(&cnt->fwd_contrib, (unsigned long long)n_con);
     atomicAdd(&cnt->fwd_entries, (unsigned long long)n_ent);
   }
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 
 __device__ __forceinline__ int wave_max_i32(int x) {

@@ -333,9 +333,8 @@ std::vector<uint32_t> make_items(const Plan& P, int tile, bool spatial) {
   return items;
 }
 
-
-// feature channels of group g when the features have D channels
-// (a dimension above 16 is a multiple of 16: every group of it is whole)
+// the kernels' settings for features of D channels (a dimension above 16 is a
+// multiple of 16: every group of channels is whole)
 Settings dev_settings(const lgs_settings* st, int tile_shift, int D) {
   Settings s;
   s.z_near = st->z_near; s.eps2d = st->eps2d; s.fov_clamp = st->fov_clamp;
