@@ -13,7 +13,7 @@ namespace lgs {
 constexpr int kBlock = 8;
 constexpr int kMaxSide = 2048;          // 8-bit block coordinates in records
 constexpr int kChannels = 20;           // RGB 3 + depth 1 + feature 16
-constexpr int kPartials = 26;           // y 20, then the geometric sums Sx, Sy, Sxx, S0, Sxy, Syy
+constexpr int kPartials = 26;           // y 20, then the geometric sums Sp, Sy, Spp, S0, Spy, Syy (frame_shear)
 constexpr int kPartGeo = 20;            // the first of the geometric sums
 constexpr uint32_t kLongSlots = 512;   // a longer slot range is summed by a whole work-group
 constexpr int kSlotFloats = 32;         // a backward slot record: the kPartials floats padded to 128 bytes
@@ -72,6 +72,22 @@ struct __attribute__((aligned(32))) GeomRec {
   float mx, my, qa, qb2, qc, o, z;
   uint32_t bbox;
 };
+
+// The geometric sums are kept in FP32 in the Gaussian's own frame: of p = dx +
+// k dy, y = dy, k = Q_xy / Q_xx, in which the conic has no mixed term.  The
+// gradient of a thin Gaussian is what its short axis leaves of them, and in the
+// image's axes that is a difference of sums as much larger as the square of the
+// axes' ratio, each rounded on its own (up to 22 px long and 0.6 across, alone
+// on their pixels: 1e-6 to 4e-6 of the gradients' norm, here at most 3.7e-7;
+// rotations in rooms of near Gaussians: a quarter less).  The writer of the sums has the conic's
+// FP32 words from the record, their reader rounds its own FP64 conic: a k that
+// differs in its last bit costs what one of the sums' roundings would in the
+// image's axes.  (A gather of the records cost the reader 16 of 67 us on eight
+// views of 500k.)  A conic so flat that k is past FP64's reach keeps the axes.
+__device__ __forceinline__ float frame_shear(float qa, float qb2) {
+  const float k = 0.5f * qb2 * __builtin_amdgcn_rcpf(qa);
+  return fabsf(k) < 65536.f ? k : 0.f;
+}
 
 // The language features of dimension D are processed in groups of 16
 // channels (the last group of D = 8 has 8): the compositing kernels carry

@@ -253,8 +253,9 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   return x;
 }
 
-// grad2d layout per visible (view, Gaussian): [r, g, b, z, f0..f15, Sx, Sy,
-// Sxx, S0, Sxy, Syy] (26 FP32, the geometric sums from kPartGeo), where S_* =
+// grad2d layout per visible (view, Gaussian): [r, g, b, z, f0..f15, Sp, Sy,
+// Spp, S0, Spy, Syy] (26 FP32, the geometric sums from kPartGeo, in the frame
+// of frame_shear, from which Sx, Sxx and Sxy follow in FP64), where S_* =
 // sum over pixels of dL/dalpha * alpha (of pixels below the opacity clamp)
 // times dx, dy, dx^2, 1, dx dy, dy^2 (m2 = Q_xx dx^2 + 2 Q_xy dx dy + Q_yy
 // dy^2, dx = pixel - mean, dL/dm2 = -1/2 dL/dalpha alpha): so dL/dQ_xx = -1/2
@@ -319,7 +320,11 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
       // conic -> Sigma':  G_Sigma' = -Q Gq Q  (symmetric representation)
       const double inv = 1.0 / S.det;
       const double Qa = S.c * inv, Qb = -S.b * inv, Qc = S.a * inv;
-      const double ga_q = -0.5 * (double)G[2], gb_q = -0.5 * (double)G[4], gc_q = -0.5 * (double)G[5];
+      // the sums about the image's axes (k as from the record's words)
+      const double kq = (double)frame_shear((float)Qa, (float)(2.0 * Qb));
+      const double Sx = (double)G[0] - kq * (double)G[1], Sy = (double)G[1], Syy = (double)G[5];
+      const double Sxy = (double)G[4] - kq * Syy, Sxx = (double)G[2] - kq * ((double)G[4] + Sxy);
+      const double ga_q = -0.5 * Sxx, gb_q = -0.5 * Sxy, gc_q = -0.5 * Syy;
       // T1 = Gq Q
       const double t00 = ga_q * Qa + gb_q * Qb, t01 = ga_q * Qb + gb_q * Qc;
       const double t10 = gb_q * Qa + gc_q * Qb, t11 = gb_q * Qb + gc_q * Qc;
@@ -352,8 +357,8 @@ __global__ void __launch_bounds__(256) k_project_bwd_view(
         for (int j = 0; j < 3; ++j)
           gM[3 * i + j] += 2.0 * (GS[3 * i] * P.M[j] + GS[3 * i + 1] * P.M[3 + j] + GS[3 * i + 2] * P.M[6 + j]);
       // camera-space mean gradient: mean', Jacobian, depth channel
-      const double gmx = Qa * (double)G[0] + Qb * (double)G[1];
-      const double gmy = Qb * (double)G[0] + Qc * (double)G[1];
+      const double gmx = Qa * Sx + Qb * Sy;
+      const double gmy = Qb * Sx + Qc * Sy;
       double gx[3];
       gx[0] = gmx * V.fx * iz;
       gx[1] = gmy * V.fy * iz;

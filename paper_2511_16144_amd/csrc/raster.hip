@@ -26,8 +26,8 @@
 // have taken (the list's end unless they all terminated before it) and walks the
 // list backwards, recovering T before each entry as T / (1 - alpha)
 // and the weighted sum of what lies behind as a single running scalar.  The
-// sums over the wave's pixels, 6 geometric (the moments 1, dx, dy, dx^2, dx dy,
-// dy^2 of dL/dalpha alpha) and 20 colour / depth / feature partials, sum_p w_p
+// sums over the wave's pixels, 6 geometric (the moments of dL/dalpha alpha up to
+// the second in the Gaussian's frame) and 20 colour / depth / feature partials, sum_p w_p
 // g_p, are products on the matrix cores over batches of 16 entries.  Both go
 // to the entry's own (Gaussian, block) slot; a segmented
 // reduction over each Gaussian's slots then forms its gradient.  No atomics:
@@ -493,7 +493,9 @@ __device__ __forceinline__ int wave_max_i32(int x) {
 //     so.)  A row of pixels and its mirror image in the block's middle have the
 //     same {1, X, X^2, Y^2} and opposite {Y, X Y}, so products of the rows' sums
 //     and differences are half as many: 16 of 16 cycles for a batch, where the
-//     quarters' were 16 of 32.
+//     quarters' were 16 of 32.  Still in FP64 the sums go to the entry's own frame
+//     (frame_shear), in which they are rounded (eight views of 500k: 1085 ->
+//     1092 us).
 //   - the 20 colour partials sum_p g[p][c] w[p]: (channels x pixels) x (pixels
 //     x entries) on BF16 terms whose sums are exact, once per batch; a lane
 //     then holds four consecutive channels of one entry and stores them as
@@ -757,7 +759,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
       // the entries' geometry and slot bases again (used after the products)
       const uint32_t re = (uint32_t)__builtin_amdgcn_ds_bpermute(col * 4, (int)ridv);
       const GeomRec* __restrict__ ge = geom + re;
-      const float emx = ge->mx, emy = ge->my;
+      const float emx = ge->mx, emy = ge->my, eqa = ge->qa, eqb = ge->qb2;
       const uint32_t ebb = ge->bbox, esb = slot_base[re];
       asm volatile("" ::: "memory");
       f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
@@ -849,22 +851,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
       exchange_halves(e13, mx, myy);
       exchange_rows(mo, my, mxy);
       const double fx = __builtin_fma(x0, m0, mx), fy = __builtin_fma(y0, m0, my);
+      const double gxx = __builtin_fma(x0, mx + fx, mxx), gyy = __builtin_fma(y0, my + fy, myy);
       const double gxy = __builtin_fma(x0, fy, __builtin_fma(y0, mx, mxy));
-      // X^2 along x in group 1, Y^2 along y in group 3
-      const double g2 = grp == 3 ? __builtin_fma(y0, my + fy, myy) : __builtin_fma(x0, mx + fx, mxx);
+      // in the entry's frame
+      const double kq = (double)frame_shear(eqa, eqb);
+      const double fp = __builtin_fma(kq, fy, fx), gpy = __builtin_fma(kq, gyy, gxy);
+      const double gpp = __builtin_fma(kq, gxy + gpy, gxx);
       const float s0 = grp == 0 ? gscale[0] : gscale[2], s3 = grp == 0 ? gscale[1] : gscale[2];
       float* rec = partials + (size_t)sl * kSlotFloats;
       if (col < nb) {
         *(float4*)(rec + 4 * grp) = make_float4(c0[0] * s0, c0[1] * s0, c0[2] * s0, c0[3] * s3);
         if (grp < 2) {
           float4 v4;
-          v4.x = grp == 0 ? c1[0] * gscale[2] : (float)fx;   // Sx
+          v4.x = grp == 0 ? c1[0] * gscale[2] : (float)fp;   // Sp
           v4.y = grp == 0 ? c1[1] * gscale[2] : (float)fy;   // Sy
-          v4.z = grp == 0 ? c1[2] * gscale[2] : (float)g2;   // Sxx
+          v4.z = grp == 0 ? c1[2] * gscale[2] : (float)gpp;  // Spp
           v4.w = grp == 0 ? c1[3] * gscale[2] : (float)m0;   // S0
           *(float4*)(rec + 16 + 4 * grp) = v4;
         } else {
-          rec[22 + grp] = (float)(grp == 2 ? gxy : g2);      // Sxy, Syy
+          rec[22 + grp] = (float)(grp == 2 ? gpy : gyy);     // Spy, Syy
         }
         if (grp == 0) mask[sl] = 1;
       }
