@@ -503,12 +503,13 @@ __device__ __forceinline__ int wave_max_i32(int x) {
 // The vector and the matrix pipe of a SIMD hardly overlap here (their busy
 // cycles add up to nearly all of the kernel's), so a product is worth its place
 // only where it takes fewer cycles than the vector instructions it replaces.
-// Per visited entry 56 vector instructions (88 with the sums by lane exchanges
+// Per visited entry 59 vector instructions (88 with the sums by lane exchanges
 // and dot products and a batch of 8), 3 of them products, and 30 scalar ones.
-// 500k Gaussians, 8 views, BF16, fused L1: 1366 -> 1060 us; 300k, 640 x 480,
-// FP32: 242 -> 172 us; 2k, 128 x 96: 49 -> 31 us (there the records in flight
-// an entry ahead and a block's planes requested at once count).  Batches of 8
-// took 1190 us; five waves per SIMD in place of four changed nothing.
+// On one card, 500k Gaussians, 8 views, BF16, fused L1: 1385 -> 1100 us; 300k,
+// 640 x 480, FP32: 139 -> 107 us; 2k, 128 x 96: 47 -> 30 us (there the records
+// in flight an entry ahead and a block's planes requested at once count).
+// Batches of 8 took 12 % longer; five waves per SIMD in place of four changed
+// nothing.
 constexpr int kBatch = 16;                 // entries per batch
 constexpr int kZRow = 72;                  // bf16 per upstream row (64 pixels + pad; 144 B, 16-B aligned)
 constexpr int kWRow = 68;                  // floats per weight / u row (64 pixels + pad; 272 B, 16-B aligned)
